@@ -1,7 +1,6 @@
 // kernels_blend.hip -- silhouette blend (paper, Section 3.2, Algorithm 1),
-// softmax blend (Algorithm 2) and their backwards, for gfx950: the
-// silhouette blend spreads a pixel's slots over a group of lanes, the softmax
-// blend takes one lane per pixel.
+// softmax blend (Algorithm 2) and their backwards, for gfx950: both spread a
+// pixel's slots over a group of lanes.
 //
 // Silhouette:
 //   prob_k = sigmoid(-d_k / sigma) where the slot holds a face, else 0
@@ -154,11 +153,21 @@ __global__ __launch_bounds__(256) void blend_bwd_kernel(const int32_t* __restric
 
 // Softmax blend: prob_k = sigmoid(-d_k / sigma), zinv_k = (zfar - z_k) / (zfar - znear),
 // w_k = prob_k exp((zinv_k - max_j zinv_j) / gamma), image = sum_k w_k c_k / sum_k w_k.
-// Empty slots take no part; a pixel whose weights sum to 0 is 0.  CB is a
-// compile-time bound on the channel count C.
+// Empty slots take no part; a pixel whose weights sum to 0 is 0.
 // The exponent is evaluated as (min_j z_j - z_k) / ((zfar - znear) gamma),
 // which equals (zinv_k - max zinv) / gamma: forming zinv first would round
 // zfar - z (about zfar) and then divide that rounding by a small gamma.
+//
+// Bound by HBM (12 + 4 C bytes read a slot, in the backward up to as many
+// written again), so the slots are spread over lanes as in the silhouette
+// blend: a lane reads its four slots' ids, depths, distances and 4 C colours
+// as 16-byte words, consecutive lanes consecutive words, and only the
+// minimum, the weight sum and the C colour sums cross lanes.  Lanes whose four
+// slots are all empty read no depths, distances or colours.  With one lane
+// per pixel every load instruction touched 64 rows K C words apart and the
+// loads of one slot waited for the last one's: a forward and backward of
+// 4 x 512 x 512 pixels, K = 8, C = 3 took 534 us (87 + 435 in the kernels),
+// now 124 us, 4.7 TB/s of the bytes that it cannot do without.
 struct SoftmaxArgs {
     const int32_t* p2f;
     const float* z;
@@ -170,85 +179,200 @@ struct SoftmaxArgs {
     float zscale;  // 1 / ((zfar - znear) gamma)
 };
 
-// Smallest depth over the pixel's filled slots (the largest zinv); 0 when there are none.
-__device__ __forceinline__ float softmax_zmin(const SoftmaxArgs& a, int64_t p) {
-    float m = INFINITY;
-    for (int k = 0; k < a.K; ++k) {
-        const int64_t o = p * a.K + k;
-        if (a.p2f[o] >= 0) m = fminf(m, a.z[o]);
-    }
-    return m == INFINITY ? 0.0f : m;
-}
-
-__device__ __forceinline__ float softmax_weight(const SoftmaxArgs& a, int64_t o, float zmin) {
-    return sigmoidf(-a.d[o] * a.inv_sigma) * expf((zmin - a.z[o]) * a.zscale);
-}
-
-// Weight sum and the blended colour of pixel p.
-template <int CB>
-__device__ __forceinline__ float softmax_pixel(const SoftmaxArgs& a, int64_t p, float m, float (&out)[CB]) {
-    float W = 0.0f;
+// Smallest value and sum over the lanes of a segment.
+template <int L>
+__device__ __forceinline__ float blend_seg_min(float v) {
 #pragma unroll
-    for (int c = 0; c < CB; ++c) out[c] = 0.0f;
-    for (int k = 0; k < a.K; ++k) {
-        const int64_t o = p * a.K + k;
-        if (a.p2f[o] < 0) continue;
-        const float w = softmax_weight(a, o, m);
-        W += w;
+    for (int m = L / 2; m >= 1; m >>= 1) v = fminf(v, __shfl_xor(v, m, L));
+    return v;
+}
+template <int L>
+__device__ __forceinline__ float blend_seg_sum(float v) {
+#pragma unroll
+    for (int m = L / 2; m >= 1; m >>= 1) v += __shfl_xor(v, m, L);
+    return v;
+}
+
+// A lane's slots of one pixel and the pixel's blend.  CB: the channel count
+// if EXACT, else a bound on it.
+template <int L, int CB, bool EXACT>
+struct SoftmaxLane {
+    bool on[kBlendQ];
+    float x[kBlendQ];          // d / sigma
+    float w[kBlendQ];          // weights (0 for an empty slot)
+    float col[kBlendQ * CB];   // colours, slot-major (C channels a slot)
+    float out[CB];             // the pixel's blended colour
+    float W;                   // the pixel's weight sum
+
+    __device__ __forceinline__ void eval(const SoftmaxArgs& a, int64_t p, int sub) {
+        const int C = EXACT ? CB : a.C;
+        const int64_t o = p * a.K + kBlendQ * sub;
+        const bool full = p < a.P && kBlendQ * (sub + 1) <= a.K;
+        float z[kBlendQ];
+        bool any = false;
+        if (full) {
+            const bi32x4 vi = *reinterpret_cast<const bi32x4*>(a.p2f + o);
+#pragma unroll
+            for (int i = 0; i < kBlendQ; ++i) on[i] = vi[i] >= 0;
+        } else {
+#pragma unroll
+            for (int i = 0; i < kBlendQ; ++i) on[i] = p < a.P && kBlendQ * sub + i < a.K && a.p2f[o + i] >= 0;
+        }
+#pragma unroll
+        for (int i = 0; i < kBlendQ; ++i) {
+            any = any || on[i];
+            z[i] = x[i] = 0.0f;
+        }
+#pragma unroll
+        for (int c = 0; c < kBlendQ * CB; ++c) col[c] = 0.0f;
+        if (any) {
+            if (full) {
+                const bf32x4 vz = *reinterpret_cast<const bf32x4*>(a.z + o);
+                const bf32x4 vd = *reinterpret_cast<const bf32x4*>(a.d + o);
+#pragma unroll
+                for (int i = 0; i < kBlendQ; ++i) {
+                    z[i] = vz[i];
+                    x[i] = vd[i] * a.inv_sigma;
+                }
+                if constexpr (EXACT) {
+#pragma unroll
+                    for (int c = 0; c < CB; ++c) {  // 4 C words: C loads of four
+                        const bf32x4 v = *reinterpret_cast<const bf32x4*>(a.col + o * CB + 4 * c);
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) col[4 * c + j] = v[j];
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < kBlendQ; ++i)
+#pragma unroll
+                        for (int c = 0; c < CB; ++c)
+                            if (c < C) col[i * CB + c] = a.col[(o + i) * C + c];
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < kBlendQ; ++i) {
+                    if (!on[i]) continue;
+                    z[i] = a.z[o + i];
+                    x[i] = a.d[o + i] * a.inv_sigma;
+#pragma unroll
+                    for (int c = 0; c < CB; ++c)
+                        if (c < C) col[i * CB + c] = a.col[(o + i) * C + c];
+                }
+            }
+        }
+        // smallest depth over the pixel's filled slots (the largest zinv); 0 when there are none
+        float m = INFINITY;
+#pragma unroll
+        for (int i = 0; i < kBlendQ; ++i)
+            if (on[i]) m = fminf(m, z[i]);
+        m = blend_seg_min<L>(m);
+        if (m == INFINITY) m = 0.0f;
+        W = 0.0f;
+#pragma unroll
+        for (int c = 0; c < CB; ++c) out[c] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < kBlendQ; ++i) {
+            w[i] = 0.0f;
+            if (!on[i]) continue;
+            w[i] = sigmoidf(-x[i]) * expf((m - z[i]) * a.zscale);
+            W += w[i];
+#pragma unroll
+            for (int c = 0; c < CB; ++c) out[c] = fmaf(w[i], col[i * CB + c], out[c]);
+        }
+        W = blend_seg_sum<L>(W);
+        const float inv = W > 0.0f ? 1.0f / W : 0.0f;
 #pragma unroll
         for (int c = 0; c < CB; ++c)
-            if (c < a.C) out[c] = fmaf(w, a.col[o * a.C + c], out[c]);
+            if (EXACT || c < C) out[c] = blend_seg_sum<L>(out[c]) * inv;
     }
-    const float inv = W > 0.0f ? 1.0f / W : 0.0f;
-#pragma unroll
-    for (int c = 0; c < CB; ++c) out[c] *= inv;
-    return W;
-}
+};
 
-template <int CB>
+template <int L, int CB, bool EXACT>
 __global__ __launch_bounds__(256) void softmax_fwd_kernel(SoftmaxArgs a, float* __restrict__ img) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= a.P) return;
-    float out[CB];
-    softmax_pixel<CB>(a, p, softmax_zmin(a, p), out);
+    constexpr int PPW = 64 / L;
+    const int C = EXACT ? CB : a.C;
+    const int lane = threadIdx.x & 63, sub = lane & (L - 1), grp = lane / L;
+    const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+    for (int64_t p0 = wave * PPW; p0 < a.P; p0 += nwaves * PPW) {
+        const int64_t p = p0 + grp;
+        SoftmaxLane<L, CB, EXACT> s;
+        s.eval(a, p, sub);
+        if (sub == 0 && p < a.P) {
 #pragma unroll
-    for (int c = 0; c < CB; ++c)
-        if (c < a.C) img[p * a.C + c] = out[c];
+            for (int c = 0; c < CB; ++c)
+                if (EXACT || c < C) img[p * C + c] = s.out[c];
+        }
+    }
 }
 
 // With G_k = sum_c g_c (c_kc - image_c) / W:
 //   dL/dd_k = -G_k w_k (1 - prob_k) / sigma, dL/dz_k = -G_k w_k / (gamma (zfar - znear)),
 //   dL/dc_kc = g_c w_k / W.  The max-zinv shift cancels in the normalised weights.
-template <int CB>
+template <int L, int CB, bool EXACT>
 __global__ __launch_bounds__(256) void softmax_bwd_kernel(SoftmaxArgs a, const float* __restrict__ gimg,
                                                           float* __restrict__ gz, float* __restrict__ gd,
                                                           float* __restrict__ gc) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= a.P) return;
-    const float m = softmax_zmin(a, p);
-    float out[CB];
-    const float W = softmax_pixel<CB>(a, p, m, out);
-    const float inv = W > 0.0f ? 1.0f / W : 0.0f;
-    float g[CB];
+    constexpr int PPW = 64 / L;
+    const int C = EXACT ? CB : a.C;
+    const int lane = threadIdx.x & 63, sub = lane & (L - 1), grp = lane / L;
+    const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+    for (int64_t p0 = wave * PPW; p0 < a.P; p0 += nwaves * PPW) {
+        const int64_t p = p0 + grp;
+        float g[CB];
 #pragma unroll
-    for (int c = 0; c < CB; ++c) g[c] = c < a.C ? gimg[p * a.C + c] : 0.0f;
-    for (int k = 0; k < a.K; ++k) {
-        const int64_t o = p * a.K + k;
-        float w = 0.0f, G = 0.0f, om = 0.0f;
-        if (a.p2f[o] >= 0 && W > 0.0f) {
-            w = softmax_weight(a, o, m);
-            om = sigmoidf(a.d[o] * a.inv_sigma);
+        for (int c = 0; c < CB; ++c) g[c] = (p < a.P && (EXACT || c < C)) ? gimg[p * C + c] : 0.0f;
+        SoftmaxLane<L, CB, EXACT> s;
+        s.eval(a, p, sub);
+        const float inv = s.W > 0.0f ? 1.0f / s.W : 0.0f;
+        float od[kBlendQ], oz[kBlendQ], oc[kBlendQ * CB];
 #pragma unroll
-            for (int c = 0; c < CB; ++c)
-                if (c < a.C) G = fmaf(g[c], a.col[o * a.C + c] - out[c], G);
-            G *= inv;
+        for (int i = 0; i < kBlendQ; ++i) {
+            float w = 0.0f, G = 0.0f, om = 0.0f;
+            if (s.on[i] && s.W > 0.0f) {
+                w = s.w[i];
+                om = sigmoidf(s.x[i]);
+#pragma unroll
+                for (int c = 0; c < CB; ++c)
+                    if (EXACT || c < C) G = fmaf(g[c], s.col[i * CB + c] - s.out[c], G);
+                G *= inv;
+            }
+            od[i] = -G * w * om * a.inv_sigma;
+            oz[i] = -G * w * a.zscale;
+#pragma unroll
+            for (int c = 0; c < CB; ++c) oc[i * CB + c] = g[c] * w * inv;
         }
-        if (gd) gd[o] = -G * w * om * a.inv_sigma;
-        if (gz) gz[o] = -G * w * a.zscale;
-        if (gc) {
+        const int64_t o = p * a.K + kBlendQ * sub;
+        if (p < a.P && kBlendQ * (sub + 1) <= a.K) {
+            if (gd) *reinterpret_cast<bf32x4*>(gd + o) = bf32x4{od[0], od[1], od[2], od[3]};
+            if (gz) *reinterpret_cast<bf32x4*>(gz + o) = bf32x4{oz[0], oz[1], oz[2], oz[3]};
+            if (gc) {
+                if constexpr (EXACT) {
 #pragma unroll
-            for (int c = 0; c < CB; ++c)
-                if (c < a.C) gc[o * a.C + c] = g[c] * w * inv;
+                    for (int c = 0; c < CB; ++c)
+                        *reinterpret_cast<bf32x4*>(gc + o * CB + 4 * c) =
+                            bf32x4{oc[4 * c], oc[4 * c + 1], oc[4 * c + 2], oc[4 * c + 3]};
+                } else {
+#pragma unroll
+                    for (int i = 0; i < kBlendQ; ++i)
+#pragma unroll
+                        for (int c = 0; c < CB; ++c)
+                            if (c < C) gc[(o + i) * C + c] = oc[i * CB + c];
+                }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < kBlendQ; ++i) {
+                if (!(p < a.P && kBlendQ * sub + i < a.K)) continue;
+                if (gd) gd[o + i] = od[i];
+                if (gz) gz[o + i] = oz[i];
+                if (gc) {
+#pragma unroll
+                    for (int c = 0; c < CB; ++c)
+                        if (EXACT || c < C) gc[(o + i) * C + c] = oc[i * CB + c];
+                }
+            }
         }
     }
 }
@@ -268,31 +392,6 @@ static SoftmaxArgs softmax_args(const int32_t* p2f, const float* z, const float*
     return a;
 }
 
-hipError_t launch_softmax_fwd(const int32_t* p2f, const float* z, const float* d, const float* col, int64_t P, int K,
-                              int C, float sigma, float gamma, float znear, float zfar, float* img, hipStream_t s) {
-    if (P == 0) return hipSuccess;
-    const SoftmaxArgs a = softmax_args(p2f, z, d, col, P, K, C, sigma, gamma, znear, zfar);
-    const dim3 grid((unsigned)((P + 255) / 256));
-    if (C <= 4)
-        hipLaunchKernelGGL(softmax_fwd_kernel<4>, grid, dim3(256), 0, s, a, img);
-    else
-        hipLaunchKernelGGL(softmax_fwd_kernel<8>, grid, dim3(256), 0, s, a, img);
-    return hipGetLastError();
-}
-
-hipError_t launch_softmax_bwd(const int32_t* p2f, const float* z, const float* d, const float* col, int64_t P, int K,
-                              int C, float sigma, float gamma, float znear, float zfar, const float* gimg, float* gz,
-                              float* gd, float* gc, hipStream_t s) {
-    if (P == 0) return hipSuccess;
-    const SoftmaxArgs a = softmax_args(p2f, z, d, col, P, K, C, sigma, gamma, znear, zfar);
-    const dim3 grid((unsigned)((P + 255) / 256));
-    if (C <= 4)
-        hipLaunchKernelGGL(softmax_bwd_kernel<4>, grid, dim3(256), 0, s, a, gimg, gz, gd, gc);
-    else
-        hipLaunchKernelGGL(softmax_bwd_kernel<8>, grid, dim3(256), 0, s, a, gimg, gz, gd, gc);
-    return hipGetLastError();
-}
-
 // lanes per pixel: the power of two L with 4 L >= K (K <= 64)
 static int blend_lanes(int K) {
     int L = 1;
@@ -305,6 +404,54 @@ static unsigned blend_grid(int64_t P, int L) {
     int64_t blocks = (waves + 3) / 4;
     if (blocks > 65536) blocks = 65536;
     return (unsigned)(blocks > 0 ? blocks : 1);
+}
+
+template <int CB, bool EXACT>
+static hipError_t softmax_launch(const SoftmaxArgs& a, bool bwd, float* img, const float* gimg, float* gz, float* gd,
+                                 float* gc, hipStream_t s) {
+    const int L = blend_lanes(a.K);
+    const dim3 grid(blend_grid(a.P, L));
+#define RAST_SOFTMAX(LL)                                                                                            \
+    case LL:                                                                                                        \
+        if (bwd)                                                                                                    \
+            hipLaunchKernelGGL((softmax_bwd_kernel<LL, CB, EXACT>), grid, dim3(256), 0, s, a, gimg, gz, gd, gc);    \
+        else                                                                                                        \
+            hipLaunchKernelGGL((softmax_fwd_kernel<LL, CB, EXACT>), grid, dim3(256), 0, s, a, img);                 \
+        break;
+    switch (L) {
+        RAST_SOFTMAX(1) RAST_SOFTMAX(2) RAST_SOFTMAX(4) RAST_SOFTMAX(8) RAST_SOFTMAX(16)
+        default: return hipErrorInvalidValue;
+    }
+#undef RAST_SOFTMAX
+    return hipGetLastError();
+}
+
+// Channel counts 1, 3 and 4 (masks, colours, colours with alpha) have
+// instances of their own, whose colours move as 16-byte words; the others
+// move them a word at a time.
+static hipError_t softmax_dispatch(const SoftmaxArgs& a, bool bwd, float* img, const float* gimg, float* gz,
+                                   float* gd, float* gc, hipStream_t s) {
+    switch (a.C) {
+        case 1: return softmax_launch<1, true>(a, bwd, img, gimg, gz, gd, gc, s);
+        case 3: return softmax_launch<3, true>(a, bwd, img, gimg, gz, gd, gc, s);
+        case 4: return softmax_launch<4, true>(a, bwd, img, gimg, gz, gd, gc, s);
+        default: return softmax_launch<8, false>(a, bwd, img, gimg, gz, gd, gc, s);
+    }
+}
+
+hipError_t launch_softmax_fwd(const int32_t* p2f, const float* z, const float* d, const float* col, int64_t P, int K,
+                              int C, float sigma, float gamma, float znear, float zfar, float* img, hipStream_t s) {
+    if (P == 0) return hipSuccess;
+    const SoftmaxArgs a = softmax_args(p2f, z, d, col, P, K, C, sigma, gamma, znear, zfar);
+    return softmax_dispatch(a, false, img, nullptr, nullptr, nullptr, nullptr, s);
+}
+
+hipError_t launch_softmax_bwd(const int32_t* p2f, const float* z, const float* d, const float* col, int64_t P, int K,
+                              int C, float sigma, float gamma, float znear, float zfar, const float* gimg, float* gz,
+                              float* gd, float* gc, hipStream_t s) {
+    if (P == 0) return hipSuccess;
+    const SoftmaxArgs a = softmax_args(p2f, z, d, col, P, K, C, sigma, gamma, znear, zfar);
+    return softmax_dispatch(a, true, nullptr, gimg, gz, gd, gc, s);
 }
 
 hipError_t launch_blend_fwd(const int32_t* p2f, const float* d, int64_t P, int K, float sigma, float* alpha,
