@@ -6,11 +6,11 @@
 // sums the chain rule into the nine vertex coordinates of its face.  Two
 // forms.  The binned form (the forward's bins): one workgroup per bin, the
 // bin's faces in LDS, exact fixed-point sums per face (described with its
-// kernels below).  The per-face form (no bins): the thread that owns face f
-// scans the pixels of f's blur-grown bounding box (the only pixels whose
-// slots the forward can fill with f), finds the slot holding f in each and
-// sums in registers -- no atomics per slot; a workgroup then merges its 256
-// faces' contributions per vertex in an LDS hash table and issues one float
+// kernels below).  The per-face form (no bins): sixteen lanes scan the pixels
+// of face f's blur-grown bounding box (the only pixels whose slots the
+// forward can fill with f), find the slot holding f in each and sum in
+// registers -- no atomics per slot; a workgroup then merges its faces'
+// contributions per vertex in an LDS hash table and issues one float
 // atomic per (vertex, coordinate).  Faces whose box exceeds kBigArea pixels
 // are handed to a second kernel in which a whole workgroup scans one face's
 // box.
@@ -278,7 +278,19 @@ __device__ __forceinline__ void lds_add(int* keys, float* vals, float* grad, int
     atomicAdd(grad + 3 * (int64_t)v + 2, z);
 }
 
-__global__ __launch_bounds__(kBwdBlock) void bwd_faces_kernel(BwdArgs a) {
+// A face's box is scanned by kFaceLanes lanes side by side (consecutive
+// pixels of a row: consecutive id lists), whose sums meet in a butterfly; a
+// group of lanes takes `per` faces in turn, a workgroup 16 per of them, and
+// `per` is chosen so that small meshes still fill the chip.  Bound by the
+// latency of the id lists' reads.  With one lane per face 2,880 faces were 12
+// workgroups and each lane walked its 80 or so pixels alone: 330 us, now 26 us
+// (three meshes of up to 1,280 faces, 130 x 75 pixels, K = 5).
+constexpr int kFaceLanes = 16;
+constexpr int kFaceGroups = kBwdBlock / kFaceLanes;
+constexpr int kFaceMaxPer = kBwdBlock / kFaceGroups;  // 3 x 256 vertices at most fit the table
+static_assert(3 * kFaceGroups * kFaceMaxPer <= kHash, "a workgroup's vertices fit its table");
+
+__global__ __launch_bounds__(kBwdBlock) void bwd_faces_kernel(BwdArgs a, int per) {
     __shared__ int keys[kHash];
     __shared__ float vals[3 * kHash];
     for (int i = threadIdx.x; i < kHash; i += kBwdBlock) {
@@ -286,36 +298,48 @@ __global__ __launch_bounds__(kBwdBlock) void bwd_faces_kernel(BwdArgs a) {
         vals[3 * i] = vals[3 * i + 1] = vals[3 * i + 2] = 0.0f;
     }
     __syncthreads();
-    const int64_t f = (int64_t)blockIdx.x * kBwdBlock + threadIdx.x;
-    FaceGrad g;
-#pragma unroll
-    for (int j = 0; j < 3; ++j) g.gx[j] = g.gy[j] = g.gzv[j] = 0.0f;
-    int vi[3] = {-1, -1, -1};
-    bool have = false;
-    if (f < a.F) {
+    const int sub = threadIdx.x & (kFaceLanes - 1), grp = threadIdx.x / kFaceLanes;
+    for (int it = 0; it < per; ++it) {
+        const int64_t f = ((int64_t)blockIdx.x * per + it) * kFaceGroups + grp;
         FaceRec R;
+        int vi[3];
         float vz[3];
         int n;
-        if (load_face(a, f, R, vi, vz, n)) {
-            int c0, c1, r0, r1;
-            pix_range(R.bb.x, R.bb.y, a.W, c0, c1);
-            pix_range(R.bb.z, R.bb.w, a.H, r0, r1);
-            if (c1 >= c0 && r1 >= r0) {
-                int area = (c1 - c0 + 1) * (r1 - r0 + 1);
-                if (area > kBigArea) {
-                    int pos = atomicAdd(&a.hdr[kHdrBigCount], 1);
-                    a.big[pos] = (int)f;
-                } else {
-                    for (int r = r0; r <= r1; ++r)
-                        for (int c = c0; c <= c1; ++c) scan_pixel(a, R, vz, (int)f, n, r, c, g);
-                    have = true;
-                }
+        if (f >= a.F || !load_face(a, f, R, vi, vz, n)) continue;  // (uniform over the group)
+        int c0, c1, r0, r1;
+        pix_range(R.bb.x, R.bb.y, a.W, c0, c1);
+        pix_range(R.bb.z, R.bb.w, a.H, r0, r1);
+        if (c1 < c0 || r1 < r0) continue;
+        const int w = c1 - c0 + 1;
+        const int64_t area = (int64_t)w * (r1 - r0 + 1);
+        if (area > kBigArea) {
+            if (sub == 0) a.big[atomicAdd(&a.hdr[kHdrBigCount], 1)] = (int)f;
+            continue;
+        }
+        FaceGrad g;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) g.gx[j] = g.gy[j] = g.gzv[j] = 0.0f;
+        const float inv_w = 1.0f / (float)w;
+        for (int q = sub; q < (int)area; q += kFaceLanes) {
+            const int dr = stage_pixel(q, inv_w);  // q / w (q <= kBigArea: the estimate is exact)
+            scan_pixel(a, R, vz, (int)f, n, r0 + dr, c0 + q - dr * w, g);
+        }
+#pragma unroll
+        for (int o = kFaceLanes / 2; o > 0; o >>= 1) {
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                g.gx[j] += __shfl_xor(g.gx[j], o, kFaceLanes);
+                g.gy[j] += __shfl_xor(g.gy[j], o, kFaceLanes);
+                g.gzv[j] += __shfl_xor(g.gzv[j], o, kFaceLanes);
             }
         }
-    }
-    if (have) {
-#pragma unroll
-        for (int j = 0; j < 3; ++j) lds_add(keys, vals, a.grad, vi[j], g.gx[j], g.gy[j], g.gzv[j]);
+        if (sub < 3) {
+            const int v = sub == 0 ? vi[0] : (sub == 1 ? vi[1] : vi[2]);
+            const float x = sub == 0 ? g.gx[0] : (sub == 1 ? g.gx[1] : g.gx[2]);
+            const float y = sub == 0 ? g.gy[0] : (sub == 1 ? g.gy[1] : g.gy[2]);
+            const float z = sub == 0 ? g.gzv[0] : (sub == 1 ? g.gzv[1] : g.gzv[2]);
+            lds_add(keys, vals, a.grad, v, x, y, z);
+        }
     }
     __syncthreads();
     for (int i = threadIdx.x; i < kHash; i += kBwdBlock) {
@@ -917,8 +941,8 @@ __global__ __launch_bounds__(kBwdBlock) void bwd_face_sum_kernel(BwdArgs a) {
     }
 }
 
-// Zeroes grad_verts (n3v floats) and the row masks (nmask words), and the
-// recorded largest face sum.
+// Zeroes grad_verts (n3v floats) and nmask words (the row masks, or the
+// header), and the recorded largest face sum.
 __global__ void bwd_prep_kernel(float* __restrict__ grad, int64_t n3v, int* __restrict__ mask, int64_t nmask,
                                 int* __restrict__ term) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -935,12 +959,16 @@ hipError_t launch_backward(const float* verts, int64_t V, const int32_t* faces, 
                            bool reuse, const BinSig& sig, hipStream_t s, hipEvent_t eb, hipEvent_t ee) {
     reuse = reuse && bs > 0;
     hipError_t e = hipSuccess;
-    // the binned form clears grad_verts together with its row masks (below)
+    // the binned form clears grad_verts together with its row masks (below);
+    // the per-face form clears it with the header, in one launch
     if (bs == 0 || F == 0) {
-        e = launch_fill_f32(grad, V * 3, 0.0f, s);
+        const int64_t n = V * 3 > kHdrWords ? V * 3 : kHdrWords;
+        const unsigned g = (unsigned)(n < 256 * 1024 ? (n + 255) / 256 : 1024);
+        hipLaunchKernelGGL(bwd_prep_kernel, dim3(g), dim3(256), 0, s, grad, V * 3, hdr, (int64_t)(reuse ? 0 : kHdrWords),
+                           hdr + kHdrTermMax);
+        e = hipGetLastError();
         if (e != hipSuccess) return e;
-    }
-    if (!reuse) {
+    } else if (!reuse) {
         e = launch_fill_i32(hdr, kHdrWords, 0, s);
         if (e != hipSuccess) return e;
     }
@@ -1004,7 +1032,12 @@ hipError_t launch_backward(const float* verts, int64_t V, const int32_t* faces, 
         return hipGetLastError();
     }
     if (eb) (void)hipEventRecord(eb, s);
-    hipLaunchKernelGGL(bwd_faces_kernel, dim3((unsigned)((F + kBwdBlock - 1) / kBwdBlock)), dim3(kBwdBlock), 0, s, a);
+    // faces a group of lanes takes in turn: as many as merge in one table once
+    // there are workgroups enough (1,024, four a compute unit)
+    int per = (int)(F / (1024 * kFaceGroups));
+    per = per < 1 ? 1 : (per > kFaceMaxPer ? kFaceMaxPer : per);
+    const int64_t fpw = (int64_t)per * kFaceGroups;
+    hipLaunchKernelGGL(bwd_faces_kernel, dim3((unsigned)((F + fpw - 1) / fpw)), dim3(kBwdBlock), 0, s, a, per);
     hipLaunchKernelGGL(bwd_big_faces_kernel, dim3(512), dim3(kBwdBlock), 0, s, a);
     if (ee) (void)hipEventRecord(ee, s);
     return hipGetLastError();

@@ -48,3 +48,21 @@ def test_softmax_lane_groups(K, P, C):
     tol = (2e-6 * C * gmax / (99.0 * 1e-2), 2e-6 * C * gmax / 1e-4, 1e-5 * gmax)
     for x, r, e in zip(got, refs, tol):
         assert np.abs(x.cpu().numpy() - r).max() <= e
+
+
+# The per-face backward: sixteen lanes a face, sixteen faces a workgroup at a
+# time, more of them in turn above 16,384 faces, boxes above 256 pixels in
+# the cooperative kernel.  Levels 0 and 1 mix both at this size; two spheres of
+# level 5 (40,960 faces) take two faces in turn.  The suite's gradient bound.
+@pytest.mark.parametrize("level,n,image,K", [(0, 1, 33, 3), (0, 3, 40, 4), (1, 2, 45, 7), (3, 3, 37, 5), (5, 2, 24, 8)])
+def test_per_face_backward_splits(level, n, image, K):
+    from _util import compare_grad, run_bwd, threads, tie_masked_grads
+    from paper_2007_08501_amd import meshgen
+    b = meshgen.make_config(2, n_override=n, level_override=level, image_override=image)
+    b.faces_per_pixel = K
+    o = oracle.rasterize(b.verts, b.faces, b.first_idx, b.num_faces, b.image_size, b.blur_radius, K,
+                         nthreads=threads())
+    g = tie_masked_grads(b, o["p2f"], *meshgen.upstream_grads(b))
+    ref = oracle.backward(b.verts, b.faces, b.image_size, o["p2f"], *g)
+    got = run_bwd(b, _t(o["p2f"].astype(np.int32)), *g, bs=0)
+    compare_grad(got.cpu().numpy(), ref, f"level {level}")
