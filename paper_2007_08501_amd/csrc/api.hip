@@ -175,8 +175,8 @@ static int fwd_impl(const float* verts_packed, int64_t V, const int32_t* faces_p
     hipError_t e = rast::launch_header_init(
         hdr, bin_signature(F, N, H, W, bin_size, bin_size > 0 ? max_faces_per_bin : 0, blur_radius, options), s);
     if (e != hipSuccess) return RAST_EHIP;
-    e = rast::launch_face_setup(verts_packed, V, faces_packed, F, mesh_to_face_first_idx, num_faces_per_mesh, N,
-                                sqrtf(blur_radius), options, recs, hdr, s);
+    e = rast::launch_face_setup(verts_packed, V, faces_packed, F, mesh_to_face_first_idx, num_faces_per_mesh, N, H,
+                                W, sqrtf(blur_radius), options, recs, hdr, s);
     if (e != hipSuccess) return RAST_EHIP;
     int* counts = nullptr;
     int* lists = nullptr;
@@ -289,8 +289,8 @@ int rast_bin_count(const float* verts_packed, int64_t V, const int32_t* faces_pa
     rast::FaceRec* recs = (rast::FaceRec*)(ws + L.recs);
     hipError_t e = rast::launch_fill_i32(hdr, rast::kHdrWords, 0, s);
     if (e != hipSuccess) return RAST_EHIP;
-    e = rast::launch_face_setup(verts_packed, V, faces_packed, F, mesh_to_face_first_idx, num_faces_per_mesh, N,
-                                sqrtf(blur_radius), 0, recs, hdr, s);
+    e = rast::launch_face_setup(verts_packed, V, faces_packed, F, mesh_to_face_first_idx, num_faces_per_mesh, N, H,
+                                W, sqrtf(blur_radius), 0, recs, hdr, s);
     if (e != hipSuccess) return RAST_EHIP;
     // M = 0: count only, no list writes
     return hip_rc(rast::launch_binning(recs, F, N, H, W, bin_size, 0, (int*)(ws + L.counts), nullptr, hdr, s));

@@ -87,8 +87,9 @@ struct FaceRec {
     float il0;       // 1 / |b - a|^2
     float il1, il2;  // 1 / |c - b|^2, 1 / |a - c|^2
     float pad_[2];
-    float4 bb;   // xmin, xmax, ymin, ymax: xy box grown by sqrt(blur) plus a pad;
-                 // empty (+inf, -inf) for faces that never count
+    int4 px;     // c0, c1, r0, r1: pixel columns and rows whose centres the xy box, grown by
+                 // sqrt(blur) plus a pad, may contain (pix_range); c1 < c0 or r1 < r0 for
+                 // faces that count nowhere on the image
     __device__ __forceinline__ int mesh() const { return mesh_; }
     __device__ __forceinline__ bool ok() const { return mesh_ >= 0; }
 };
@@ -97,12 +98,14 @@ __device__ __forceinline__ bool finite3(float a, float b, float c) {
     return isfinite(a) && isfinite(b) && isfinite(c);
 }
 
-// Builds the record of face (a, b, c).  rb = sqrt(blur_radius) in NDC units.
+__device__ __forceinline__ void pix_range(float vmin, float vmax, int size, int& lo, int& hi);
+
+// Builds the record of face (a, b, c) for H x W images.  rb = sqrt(blur_radius) in NDC units.
 // Under the options a back face (E > 0: clockwise as the image is displayed,
 // +x being to the left) or, with the perspective correction, a face with a
 // vertex at z <= 0 never counts.
 __device__ __forceinline__ FaceRec make_rec(float ax, float ay, float az, float bx, float by, float bz, float cx,
-                                            float cy, float cz, float rb, int mesh, int opts = 0) {
+                                            float cy, float cz, float rb, int H, int W, int mesh, int opts = 0) {
     FaceRec R;
     R.pa = make_double2(ax, ay);
     R.ab = make_double2((double)bx - (double)ax, (double)by - (double)ay);
@@ -128,10 +131,10 @@ __device__ __forceinline__ FaceRec make_rec(float ax, float ay, float az, float 
         // FP32 squared distance is < blur is never farther than rb*(1+1e-6)+1e-7.
         float pad = rb * 1e-4f + 1e-6f;
         float g = rb + pad;
-        R.bb = make_float4(fminf(ax, fminf(bx, cx)) - g, fmaxf(ax, fmaxf(bx, cx)) + g,
-                           fminf(ay, fminf(by, cy)) - g, fmaxf(ay, fmaxf(by, cy)) + g);
+        pix_range(fminf(ax, fminf(bx, cx)) - g, fmaxf(ax, fmaxf(bx, cx)) + g, W, R.px.x, R.px.y);
+        pix_range(fminf(ay, fminf(by, cy)) - g, fmaxf(ay, fmaxf(by, cy)) + g, H, R.px.z, R.px.w);
     } else {
-        R.bb = make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY);
+        R.px = make_int4(0, -1, 0, -1);
     }
     return R;
 }
@@ -232,10 +235,6 @@ __device__ __forceinline__ void eval_full(const Rec& R, const Pix& p, Eval& o) {
     eval_dist(R, o);
 }
 
-__device__ __forceinline__ bool in_bbox(const FaceRec& R, const Pix& p) {
-    return p.xf >= R.bb.x && p.xf <= R.bb.y && p.yf >= R.bb.z && p.yf <= R.bb.w;
-}
-
 // The options' barycentrics and depth from the raw ones (az the depth of
 // vertex a, dz1 / dz2 those of b and c relative to it): with the
 // perspective correction w_i <- (w_i / z_i) / sum_j (w_j / z_j), then with
@@ -316,25 +315,20 @@ __device__ __forceinline__ void pix_range(float vmin, float vmax, int size, int&
 }
 
 // Bins [bx0, bx1] x [by0, by1] (bin_size bs) whose pixels may count a face
-// with grown box bb; false when the face counts nowhere on the H x W image
-// (a face that never counts has an empty box).  The binning pass and the
-// backward use this same function, so they agree on every face's bins.
-__device__ __forceinline__ bool face_bins_of_box(const float4 bb, int H, int W, int bs, int& bx0, int& bx1, int& by0,
-                                                 int& by1) {
-    int c0, c1, r0, r1;
-    pix_range(bb.x, bb.y, W, c0, c1);
-    pix_range(bb.z, bb.w, H, r0, r1);
-    if (c1 < c0 || r1 < r0) return false;
-    bx0 = c0 / bs;
-    bx1 = c1 / bs;
-    by0 = r0 / bs;
-    by1 = r1 / bs;
+// with pixel ranges px; false when it counts nowhere on the image (a face
+// that never counts has empty ranges).  The binning pass and the backward use
+// this same function, so they agree on every face's bins.
+__device__ __forceinline__ bool face_bins_of_px(const int4 px, int bs, int& bx0, int& bx1, int& by0, int& by1) {
+    if (px.y < px.x || px.w < px.z) return false;
+    bx0 = px.x / bs;
+    bx1 = px.y / bs;
+    by0 = px.z / bs;
+    by1 = px.w / bs;
     return true;
 }
-__device__ __forceinline__ bool face_bins(const FaceRec& R, int H, int W, int bs, int& bx0, int& bx1, int& by0,
-                                          int& by1) {
+__device__ __forceinline__ bool face_bins(const FaceRec& R, int bs, int& bx0, int& bx1, int& by0, int& by1) {
     if (!R.ok()) return false;
-    return face_bins_of_box(R.bb, H, W, bs, bx0, bx1, by0, by1);
+    return face_bins_of_px(R.px, bs, bx0, bx1, by0, by1);
 }
 
 // Sort key: ascending z, then ascending face id, as one unsigned 64-bit
@@ -472,38 +466,40 @@ __device__ __forceinline__ int wave_max(int v) {
 // element e of a pass that stages `per` values per pixel: pixel e / per
 __device__ __forceinline__ int stage_pixel(int e, float inv_per) { return (int)(((float)e + 0.5f) * inv_per); }
 
-// Pixels of the 8x8 tile (x0, y0) whose centres the box [bb.x, bb.y] x
-// [bb.z, bb.w] may contain, from the same conservative pixel ranges as the
-// binning (an empty box gives 0).
-__device__ __forceinline__ uint64_t tile_mask(const float4 bb, int H, int W, int x0, int y0, float tx_lo, float tx_hi,
-                                              float ty_lo, float ty_hi) {
-    // most faces of a single-pass tile miss it: reject those on the box alone
-    if (bb.y < tx_lo || bb.x > tx_hi || bb.w < ty_lo || bb.z > ty_hi) return 0ull;
-    int c0, c1, r0, r1;
-    pix_range(bb.x, bb.y, W, c0, c1);
-    pix_range(bb.z, bb.w, H, r0, r1);
-    c0 = max(c0 - x0, 0);
-    c1 = min(c1 - x0, kTile - 1);
-    r0 = max(r0 - y0, 0);
-    r1 = min(r1 - y0, kTile - 1);
+// Pixels of the 8x8 tile (x0, y0) inside a face's pixel ranges (bit r * 8 + c).
+__device__ __forceinline__ uint64_t tile_mask(const int4 px, int x0, int y0) {
+    const int c0 = max(px.x - x0, 0), c1 = min(px.y - x0, kTile - 1);
+    const int r0 = max(px.z - y0, 0), r1 = min(px.w - y0, kTile - 1);
     if (c1 < c0 || r1 < r0) return 0ull;
-    const uint64_t cols = (uint64_t)((0xffu >> (kTile - 1 - (c1 - c0))) << c0) * 0x0101010101010101ull;
+    const uint32_t cols = (0xffu >> (kTile - 1 - (c1 - c0))) << c0;
+    const uint32_t cols4 = __builtin_amdgcn_perm(cols, cols, 0u);  // the byte in all four bytes
     const uint64_t rows = (~0ull >> (8 * (kTile - 1 - r1))) & (~0ull << (8 * r0));
-    return cols & rows;
+    return (((uint64_t)cols4 << 32) | cols4) & rows;
 }
 
 // Pixels of the 8x8 tile (x0, y0) that a face may count for, by its three
 // edge lines: a pixel counts only inside the triangle or within sqrt(blur)
 // of it, and the triangle lies on the inner side of each edge line, so a
-// pixel more than rg = sqrt(blur) (1 + 1e-4) + 1e-6 outside any one line
-// cannot count (rg is the box pad's radius: it covers the FP32 error of the
-// distance test).  Per line i the edge function at pixel (r, c) of the tile
-// is e_i(r, c) = e_i(0, 0) - c (2/W) A_i - r (2/H) B_i (A_i, B_i its x and y
-// coefficients), and the kept columns of row r are those with
-// sgn(E) e_i > -rg |edge_i|, a half-line in c.  e_i(0, 0), the thresholds
-// the row terms and the column bounds are FP64 (their rounding is far below
-// the margin rg leaves over the test's own error); only the clamped bound is
-// converted.  Conservative: every pixel the test accepts is kept.
+// pixel more than sqrt(blur) outside any one line cannot count.  Per line i
+// the edge function at pixel (r, c) of the tile is e_i(r, c) = e_i(0, 0) -
+// c (2/W) A_i - r (2/H) B_i (A_i, B_i its x and y coefficients), and the kept
+// columns of row r are those with sgn(E) e_i > -rg |edge_i|, a half-line in
+// c: c g_i < k_i - r h_i with g_i = sgn(E) (2/W) A_i, h_i = sgn(E) (2/H) B_i,
+// k_i = sgn(E) e_i(0, 0) + rg |edge_i|.
+//
+// Only a mask of candidates: the exact test follows, so every bound may err
+// towards keeping a pixel, and all but e_i(0, 0) and the edge vectors (whose
+// differences cancel) is FP32.  As distances from the line, its errors are
+// a few 2^-24 of the distances that occur at a pixel near the bound, at most
+// rg + 23 / min(H, W) across a tile; rg (edge_radius) carries 2^-20 of that
+// beyond what the exact test's own FP32 error needs, more than ten times
+// those.  A line parallel to the rows (g = 0) gets a slope of 1e-25, far
+// below any that matters.  Faces with coordinates beyond 1e3 from the tile
+// keep their whole box.
+// This mask is computed per face and tile and was a third of the fine pass's
+// instructions when it was FP64 throughout with correctly rounded roots and
+// quotients (about 700 of 1,900 vector instructions per chunk of faces, now
+// 200).
 struct EdgeGeo {
     double2 pa, ab, ac;
     double E;
@@ -512,55 +508,60 @@ __device__ __forceinline__ double2 f4_as_d2(const float4 v) {
     return make_double2(__hiloint2double(__float_as_int(v.y), __float_as_int(v.x)),
                         __hiloint2double(__float_as_int(v.w), __float_as_int(v.z)));
 }
-template <class Rec>
-__device__ __forceinline__ uint64_t edge_mask(const Rec& R, double rg, int H, int W, int x0, int y0) {
-    const double px = 1.0 - (double)(2 * x0 + 1) / (double)W, py = 1.0 - (double)(2 * y0 + 1) / (double)H;
-    const double dx = px - R.pa.x, dy = py - R.pa.y;
-    const double sg = R.E > 0.0 ? 1.0 : -1.0;
+// Radius of the mask: sqrt(blur) and the margins above.
+__device__ __forceinline__ float edge_radius(float blur, int H, int W) {
+    const float rg = sqrtf(blur) * (1.0f + 1e-4f) + 1e-6f;
+    return rg + (rg + 23.0f / (float)min(H, W)) * 0x1p-20f;
+}
+// (px, py): centre of the tile's first pixel; sx = 2/W, sy = 2/H.
+__device__ __forceinline__ uint64_t edge_mask(const EdgeGeo& G, float rg, double px, double py, float sx, float sy) {
+    const double dx = px - G.pa.x, dy = py - G.pa.y;
     // e1 = cross(p - a, c - a), e2 = cross(b - a, p - a), e0 = E - e1 - e2
-    const double e1 = dx * R.ac.y - dy * R.ac.x;
-    const double e2 = R.ab.x * dy - R.ab.y * dx;
-    const double e0 = (R.E - e1) - e2;
-    const double A1 = R.ac.y, B1 = -R.ac.x, A2 = -R.ab.y, B2 = R.ab.x;
-    const double A0 = -(A1 + A2), B0 = -(B1 + B2);
+    const double e1 = fma(dx, G.ac.y, -(dy * G.ac.x));
+    const double e2 = fma(G.ab.x, dy, -(G.ab.y * dx));
+    const double e0 = (G.E - e1) - e2;
+    const float abx = (float)G.ab.x, aby = (float)G.ab.y, acx = (float)G.ac.x, acy = (float)G.ac.y;
+    const float bcx = (float)(G.ac.x - G.ab.x), bcy = (float)(G.ac.y - G.ab.y);
+    const float far = fmaxf(fmaxf(fmaxf(fabsf(abx), fabsf(aby)), fmaxf(fabsf(acx), fabsf(acy))),
+                            fmaxf(fabsf((float)dx), fabsf((float)dy)));
+    if (!(far < 1e3f)) return ~0ull;
+    const float sg = G.E > 0.0 ? 1.0f : -1.0f;
+    const float ssx = sg * sx, ssy = sg * sy;
     // edge lengths: e0 <-> (b, c), e1 <-> (c, a), e2 <-> (a, b)
-    const double bcx = R.ac.x - R.ab.x, bcy = R.ac.y - R.ab.y;
-    const double l0 = sqrt(bcx * bcx + bcy * bcy), l1 = sqrt(R.ac.x * R.ac.x + R.ac.y * R.ac.y),
-                 l2 = sqrt(R.ab.x * R.ab.x + R.ab.y * R.ab.y);
-    const double sx = 2.0 / (double)W, sy = 2.0 / (double)H;
-    // keep (r, c) iff c * g_i < k_i - r * h_i for all i, with
-    //   g_i = sg sx A_i,  k_i = sg e_i(0,0) + rg l_i,  h_i = sg sy B_i
-    const double g[3] = {sg * sx * A0, sg * sx * A1, sg * sx * A2};
-    const double k[3] = {sg * e0 + rg * l0, sg * e1 + rg * l1, sg * e2 + rg * l2};
-    const double h[3] = {sg * sy * B0, sg * sy * B1, sg * sy * B2};
-    double ig[3];
+    const float l0 = __builtin_amdgcn_sqrtf(fmaf(bcx, bcx, bcy * bcy));
+    const float l1 = __builtin_amdgcn_sqrtf(fmaf(acx, acx, acy * acy));
+    const float l2 = __builtin_amdgcn_sqrtf(fmaf(abx, abx, aby * aby));
+    const float k[3] = {fmaf(rg, l0, sg * (float)e0), fmaf(rg, l1, sg * (float)e1), fmaf(rg, l2, sg * (float)e2)};
+    const float g[3] = {-ssx * bcy, ssx * acy, -ssx * aby};
+    const float h[3] = {ssy * bcx, -ssy * acx, ssy * abx};
+    // Per row r and edge: b = (k - r h) / g bounds c from above (g > 0) or
+    // below (g < 0).  Kept as n = b + 1 and m = 8 - b, so that floor(b) + 1 and
+    // 8 - ceil(b) are truncations of numbers in [0, 8]; the bound an edge
+    // does not give is 16.
+    float n0[3], n1[3], m0[3], m1[3];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) ig[i] = g[i] != 0.0 ? 1.0 / g[i] : 0.0;
-    uint64_t m = 0ull;
+    for (int i = 0; i < 3; ++i) {
+        const float gi = fabsf(g[i]) < 1e-25f ? 1e-25f : g[i];
+        const float ig = __builtin_amdgcn_rcpf(gi);
+        const float b0 = k[i] * ig, b1 = -h[i] * ig;
+        const bool up = gi > 0.0f;
+        n0[i] = up ? b0 + 1.0f : 16.0f;
+        n1[i] = up ? b1 : 0.0f;
+        m0[i] = up ? 16.0f : 8.0f - b0;
+        m1[i] = up ? 0.0f : -b1;
+    }
+    uint32_t half[2] = {0u, 0u};
 #pragma unroll
     for (int r = 0; r < kTile; ++r) {
-        float lo = 0.0f, hi = (float)(kTile - 1);
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const double kr = k[i] - (double)r * h[i];
-            if (g[i] == 0.0) {
-                if (!(kr > 0.0)) hi = -1.0f;  // the whole row is outside this line
-            } else {
-                // the row's bound on c, clamped to [-2, 9] before the conversion
-                const float b = (float)fmin(fmax(kr * ig[i], -2.0), 9.0);
-                if (g[i] > 0.0)
-                    hi = fminf(hi, floorf(b));  // c <= k / g (c = k / g kept: conservative)
-                else
-                    lo = fmaxf(lo, ceilf(b));
-            }
-        }
-        if (lo <= hi) {
-            const int a = (int)lo, z = (int)hi;
-            const uint32_t row = (0xffu >> (kTile - 1 - z)) & (0xffu << a);
-            m |= (uint64_t)row << (8 * r);
-        }
+        const float fr = (float)r;
+        const float n = fminf(fminf(fmaf(fr, n1[0], n0[0]), fmaf(fr, n1[1], n0[1])), fmaf(fr, n1[2], n0[2]));
+        const float m = fminf(fminf(fmaf(fr, m1[0], m0[0]), fmaf(fr, m1[1], m0[1])), fmaf(fr, m1[2], m0[2]));
+        const int hi1 = (int)__builtin_amdgcn_fmed3f(n, 0.0f, 8.0f);      // columns below hi1 ...
+        const int lo = 8 - (int)__builtin_amdgcn_fmed3f(m, 0.0f, 8.0f);   // ... from lo on
+        const uint32_t row = ((1u << max(hi1 - lo, 0)) - 1u) << lo;
+        half[r >> 2] |= row << (8 * (r & 3));
     }
-    return m;
+    return ((uint64_t)half[1] << 32) | half[0];
 }
 
 // One global atomic per distinct bucket of a wave (tiles of a wave mostly

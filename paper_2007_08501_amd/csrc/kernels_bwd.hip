@@ -250,7 +250,8 @@ __device__ __forceinline__ bool load_face(const BwdArgs& a, int64_t f, FaceRec& 
     const float* P0 = a.verts + 3 * (int64_t)vi[0];
     const float* P1 = a.verts + 3 * (int64_t)vi[1];
     const float* P2 = a.verts + 3 * (int64_t)vi[2];
-    R = make_rec(P0[0], P0[1], P0[2], P1[0], P1[1], P1[2], P2[0], P2[1], P2[2], a.rb, n, a.opts);
+    R = make_rec(P0[0], P0[1], P0[2], P1[0], P1[1], P1[2], P2[0], P2[1], P2[2], a.rb, a.H, a.W, n,
+                 a.opts);
     vz[0] = P0[2];
     vz[1] = P1[2];
     vz[2] = P2[2];
@@ -306,9 +307,7 @@ __global__ __launch_bounds__(kBwdBlock) void bwd_faces_kernel(BwdArgs a, int per
         float vz[3];
         int n;
         if (f >= a.F || !load_face(a, f, R, vi, vz, n)) continue;  // (uniform over the group)
-        int c0, c1, r0, r1;
-        pix_range(R.bb.x, R.bb.y, a.W, c0, c1);
-        pix_range(R.bb.z, R.bb.w, a.H, r0, r1);
+        const int c0 = R.px.x, c1 = R.px.y, r0 = R.px.z, r1 = R.px.w;
         if (c1 < c0 || r1 < r0) continue;
         const int w = c1 - c0 + 1;
         const int64_t area = (int64_t)w * (r1 - r0 + 1);
@@ -375,9 +374,7 @@ __global__ __launch_bounds__(kBwdBlock) void bwd_big_faces_kernel(BwdArgs a) {
         for (int j = 0; j < 3; ++j) g.gx[j] = g.gy[j] = g.gzv[j] = 0.0f;
         bool ok = load_face(a, f, R, vi, vz, n);
         if (ok) {
-            int c0, c1, r0, r1;
-            pix_range(R.bb.x, R.bb.y, a.W, c0, c1);
-            pix_range(R.bb.z, R.bb.w, a.H, r0, r1);
+            const int c0 = R.px.x, c1 = R.px.y, r0 = R.px.z, r1 = R.px.w;
             const int w = c1 - c0 + 1;
             const int64_t area = (c1 >= c0 && r1 >= r0) ? (int64_t)w * (r1 - r0 + 1) : 0;
             for (int64_t q = threadIdx.x; q < area; q += kBwdBlock) {
@@ -591,7 +588,7 @@ __device__ __forceinline__ void add_slot(const BwdArgs& a, const BinRec& R, int 
 // lies outside its range).
 __device__ __forceinline__ int partial_row(const BwdArgs& a, const FaceRec& G, int f, int bx, int by) {
     int bx0, bx1, by0, by1;
-    if (!face_bins(G, a.H, a.W, a.bs, bx0, bx1, by0, by1)) return -2;
+    if (!face_bins(G, a.bs, bx0, bx1, by0, by1)) return -2;
     const int nb = (bx1 - bx0 + 1) * (by1 - by0 + 1);
     if (nb > kMaxPartials) return -1;
     if (bx < bx0 || bx > bx1 || by < by0 || by > by1) return -2;
@@ -1008,7 +1005,7 @@ hipError_t launch_backward(const float* verts, int64_t V, const int32_t* faces, 
         // the same face setup and binning as the forward (unless the forward's
         // are reused), then the two passes
         if (!reuse) {
-            e = launch_face_setup(verts, V, faces, F, first, nf, N, a.rb, opts, recs, hdr, s);
+            e = launch_face_setup(verts, V, faces, F, first, nf, N, H, W, a.rb, opts, recs, hdr, s);
             if (e != hipSuccess) return e;
             e = launch_binning(recs, F, N, H, W, bs, M, counts, lists, hdr, s);
             if (e != hipSuccess) return e;

@@ -84,8 +84,8 @@ hipError_t launch_fill_f32(float* p, int64_t n, float v, hipStream_t s) {
 __global__ __launch_bounds__(256) void face_setup_kernel(const float* __restrict__ verts, int64_t V,
                                                          const int32_t* __restrict__ faces, int64_t F,
                                                          const int64_t* __restrict__ first,
-                                                         const int64_t* __restrict__ nf, int N, float rb, int opts,
-                                                         FaceRec* __restrict__ recs, int* __restrict__ hdr) {
+                                                         const int64_t* __restrict__ nf, int N, int H, int W, float rb,
+                                                         int opts, FaceRec* __restrict__ recs, int* __restrict__ hdr) {
     __shared__ FaceRec srec[256];
     const int64_t f0 = (int64_t)blockIdx.x * blockDim.x;
     int64_t f = f0 + threadIdx.x;
@@ -107,12 +107,13 @@ __global__ __launch_bounds__(256) void face_setup_kernel(const float* __restrict
             i0 = i1 = i2 = 0;
         }
         if (V == 0) {
-            srec[threadIdx.x] = make_rec(0, 0, 0, 0, 0, 0, 0, 0, 0, rb, -1);
+            srec[threadIdx.x] = make_rec(0, 0, 0, 0, 0, 0, 0, 0, 0, rb, H, W, -1);
         } else {
             const float* a = verts + 3 * (int64_t)i0;
             const float* b = verts + 3 * (int64_t)i1;
             const float* c = verts + 3 * (int64_t)i2;
-            srec[threadIdx.x] = make_rec(a[0], a[1], a[2], b[0], b[1], b[2], c[0], c[1], c[2], rb, mesh, opts);
+            srec[threadIdx.x] =
+                make_rec(a[0], a[1], a[2], b[0], b[1], b[2], c[0], c[1], c[2], rb, H, W, mesh, opts);
         }
     }
     __syncthreads();
@@ -125,11 +126,12 @@ __global__ __launch_bounds__(256) void face_setup_kernel(const float* __restrict
 }
 
 hipError_t launch_face_setup(const float* verts, int64_t V, const int32_t* faces, int64_t F, const int64_t* first,
-                             const int64_t* nf, int N, float rb, int opts, FaceRec* recs, int* hdr, hipStream_t s) {
+                             const int64_t* nf, int N, int H, int W, float rb, int opts, FaceRec* recs, int* hdr,
+                             hipStream_t s) {
     int64_t n = F > N ? F : N;
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(face_setup_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, verts, V, faces, F,
-                       first, nf, N, rb, opts, recs, hdr);
+                       first, nf, N, H, W, rb, opts, recs, hdr);
     return hipGetLastError();
 }
 
@@ -154,8 +156,8 @@ __device__ __forceinline__ uint32_t bin_hash(int64_t b) {
 }
 static_assert(kBinHash == 1024, "bin_hash yields 10 bits");
 
-__global__ __launch_bounds__(256) void bin_faces_kernel(const FaceRec* __restrict__ recs, int64_t F, int H, int W,
-                                                        int bs, int nby, int nbx, int M, int* __restrict__ counts,
+__global__ __launch_bounds__(256) void bin_faces_kernel(const FaceRec* __restrict__ recs, int64_t F, int bs,
+                                                        int nby, int nbx, int M, int* __restrict__ counts,
                                                         int* __restrict__ lists, int* __restrict__ hdr) {
     __shared__ unsigned long long hkey[kBinHash];  // bin + 1 (0: empty)
     __shared__ int wmax[4];
@@ -170,7 +172,7 @@ __global__ __launch_bounds__(256) void bin_faces_kernel(const FaceRec* __restric
     if (f < F) {
         const FaceRec& R = recs[f];
         int bx1, by1;
-        if (R.ok() && face_bins_of_box(R.bb, H, W, bs, bx0, bx1, by0, by1)) {
+        if (face_bins(R, bs, bx0, bx1, by0, by1)) {
             n = R.mesh();
             nbw = bx1 - bx0 + 1;
             nb = nbw * (by1 - by0 + 1);
@@ -258,8 +260,8 @@ hipError_t launch_binning(const FaceRec* recs, int64_t F, int N, int H, int W, i
     hipError_t e = launch_fill_i32(counts, nbins, 0, s);
     if (e != hipSuccess) return e;
     if (F > 0) {
-        hipLaunchKernelGGL(bin_faces_kernel, dim3((unsigned)((F + 255) / 256)), dim3(256), 0, s, recs, F, H, W, bs, nby,
-                           nbx, M, counts, lists, hdr);
+        hipLaunchKernelGGL(bin_faces_kernel, dim3((unsigned)((F + 255) / 256)), dim3(256), 0, s, recs, F, bs, nby, nbx,
+                           M, counts, lists, hdr);
     }
     return hipGetLastError();
 }
@@ -289,9 +291,9 @@ struct FineArgs {
     float* dists;
 };
 
-// LDS of one tile's wave: a chunk of up to 64 candidate faces that overlap the
-// tile (the gather gives every lane one list entry, so a chunk is exactly one
-// wave wide), and the room the write-out staging needs beyond them.
+// LDS of one tile's wave: a block of up to 64 candidate faces that overlap the
+// tile (the gather gives every lane one list entry and the transpose one
+// record), reused at the end to stage one output array at a time.
 constexpr int kChunk = tile_layout::kChunk;
 
 // A face as the tile pass keeps it in LDS: the geometry the pixel tests read
@@ -307,11 +309,11 @@ struct TileRec {
 };
 static_assert(sizeof(TileRec) == tile_layout::kTileRecBytes, "tile record layout");
 
-struct TileLds {
+union TileLds {
     TileRec rec[kChunk];
-    unsigned char spare[tile_layout::kSpareBytes];  // (staging of the write-out)
+    float stage[tile_layout::kBlockBytes / 4];
 };
-static_assert(sizeof(TileLds) == tile_layout::kLdsBytes, "tile LDS layout");
+static_assert(sizeof(TileLds) == tile_layout::kBlockBytes, "tile LDS layout");
 
 // Writes the tile's fragments from the per-lane queues.  Values are staged in
 // LDS per pixel and then stored by consecutive lanes to consecutive
@@ -320,182 +322,211 @@ static_assert(sizeof(TileLds) == tile_layout::kLdsBytes, "tile LDS layout");
 // words; written slot by slot, each cache line would be completed by K
 // separate instructions with loads in between and could be evicted half
 // written.  Ids and depths come straight from the keys; barycentrics and
-// distances are recomputed from the face records.
+// distances are recomputed from the face records.  One array is staged at a
+// time: the block then is no larger than the candidate faces need (6.4 KB),
+// so that the registers and not the LDS bound the waves of a compute unit.
 constexpr int kStageG1 = tile_layout::kStageG1;  // slots per pass for ids and depths
 constexpr int kStageG2 = tile_layout::kStageG2;  // slots per pass for barycentrics and distances
 
-// EXACT: K equals the bucket size KB, so every group width, stride and index
+// Stores of four consecutive words.  For a queue of K = KB slots (K a multiple
+// of 4, 16-byte aligned outputs) the ids and depths are streamed past the
+// caches (the "nt" hint): those passes write whole lines, and streaming them
+// leaves L2 to the face records the tile waves share; the barycentric and
+// distance passes write part lines per pass and are stored normally, so that
+// L2 completes their lines.  Other K start a pixel's run at any word.
+typedef float nt_f4 __attribute__((ext_vector_type(4)));
+typedef float f4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+template <bool ALIGNED, bool STREAM>
+__device__ __forceinline__ void store4(float* p, float x, float y, float z, float w) {
+    if constexpr (ALIGNED && STREAM)
+        __builtin_nontemporal_store(nt_f4{x, y, z, w}, reinterpret_cast<nt_f4*>(p));
+    else if constexpr (ALIGNED)
+        *reinterpret_cast<nt_f4*>(p) = nt_f4{x, y, z, w};
+    else
+        *reinterpret_cast<f4_a4*>(p) = f4_a4{x, y, z, w};
+}
+
+// The tile's place in an output array of n words a slot.
+struct TileOut {
+    int K, rowK;     // slots a pixel, slots an image row
+    int rows, cols;  // of the tile inside the image
+};
+
+// Stores G slots from slot g0 of every pixel of the tile, staged at
+// stage[pixel * S ...], n words each: quads of four words, one a lane.
+template <int G, int S, int n, bool ALIGNED, bool STREAM>
+__device__ __forceinline__ void store_staged(float* __restrict__ out, const float* stage, const TileOut& t, int g0) {
+    constexpr int Q = n * G / 4;  // quads a pixel
+    const int lane = threadIdx.x & 63;
+    const int left = n * (t.K - g0);  // words of the pass
+    int px = lane / Q, q = lane - px * Q;
+#pragma unroll
+    for (int e0 = 0; e0 < 64 * Q; e0 += 64) {
+        const int r = px >> 3, c = px & 7;
+        if (r < t.rows && c < t.cols) {
+            const float* src = stage + px * S + 4 * q;
+            float* dst = out + (n * (r * t.rowK + c * t.K + g0) + 4 * q);
+            if (ALIGNED || 4 * q + 4 <= left) {
+                store4<ALIGNED, STREAM>(dst, src[0], src[1], src[2], src[3]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+                    if (4 * q + i < left) dst[i] = src[i];
+            }
+        }
+        px += 64 / Q;
+        q += 64 % Q;
+        if (64 % Q != 0 && q >= Q) {
+            q -= Q;
+            ++px;
+        }
+    }
+}
+
+// Fills the tile's runs of an array of n words a slot with one value (a tile
+// that no face reaches).
+template <int KB, int n, bool ALIGNED>
+__device__ __forceinline__ void fill_rows(float* __restrict__ out, const TileOut& t, float v) {
+    const int lane = threadIdx.x & 63;
+    if constexpr (ALIGNED) {
+        constexpr int Q = n * KB * kTile / 4;  // quads of a full row
+        const int nq = n * KB * t.cols / 4;
+#pragma unroll
+        for (int e0 = 0; e0 < kTile * Q; e0 += 64) {
+            const int e = e0 + lane;
+            const int r = e / Q, q = e - r * Q;
+            if (e < kTile * Q && r < t.rows && q < nq)
+                store4<true, true>(out + (n * r * t.rowK + 4 * q), v, v, v, v);
+        }
+    } else {
+        const int w = n * t.cols * t.K;
+        for (int r = 0; r < t.rows; ++r) {
+            float* dst = out + n * r * t.rowK;
+            for (int i = 4 * lane; i < w; i += 256) {
+                if (i + 4 <= w) {
+                    store4<false, false>(dst + i, v, v, v, v);
+                } else {
+                    for (int j = i; j < w; ++j) dst[j] = v;
+                }
+            }
+        }
+    }
+}
+
+// Barycentrics and signed distance of the face of a key at pixel p (-1 for an empty slot).
+template <bool OPT>
+__device__ __forceinline__ void slot_values(const FineArgs& a, uint64_t key, const Pix& p, float& w0, float& w1,
+                                            float& w2, float& d) {
+    w0 = w1 = w2 = d = -1.0f;
+    if (key != kEmptyKey) {
+        const FaceRec R = a.recs[(uint32_t)key];
+        Eval ev;
+        eval_full(R, p, ev);
+        w0 = ev.w0;
+        w1 = ev.w1;
+        w2 = ev.w2;
+        if (OPT) {
+            float zf;
+            apply_opts(a.opts, R.az, R.dz1, R.dz2, w0, w1, w2, zf);
+        }
+        d = ev.inside ? -ev.d2 : ev.d2;
+    }
+}
+__device__ __forceinline__ int key_id(uint64_t key) { return key == kEmptyKey ? -1 : (int)(uint32_t)key; }
+__device__ __forceinline__ float key_z(uint64_t key) {
+    return key == kEmptyKey ? -1.0f : __uint_as_float((uint32_t)(key >> 32));
+}
+
+// EXACT: K equals the queue size KB, so every group width, stride and index
 // below is a compile-time constant (the common case); otherwise K < KB is a
 // run-time value.  Addresses are 32-bit offsets from the tile's first
 // fragment, a wave-uniform base.
 // OPT: the rasterizer options that change barycentrics and depth are on
 // (a separate instantiation, so that the default path carries no test for them).
-// Non-temporal 16-byte stores (the "nt" hint: streamed past the caches).
-// The id and depth passes write whole lines (a tile row of either array is
-// 8 K contiguous words), so streaming them leaves L2 to the face records the
-// tile waves share; the barycentric and distance passes write part lines
-// per pass and are stored normally, so that L2 completes their lines.
-typedef float nt_f4 __attribute__((ext_vector_type(4)));
-typedef int nt_i4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void nt_store(int4 v, int* p) {
-    const nt_i4 w = {v.x, v.y, v.z, v.w};
-    __builtin_nontemporal_store(w, reinterpret_cast<nt_i4*>(p));
-}
-__device__ __forceinline__ void nt_store(float4 v, float* p) {
-    const nt_f4 w = {v.x, v.y, v.z, v.w};
-    __builtin_nontemporal_store(w, reinterpret_cast<nt_f4*>(p));
-}
-
 template <int KB, bool EXACT, bool OPT>
 __device__ __forceinline__ void write_fragments(const FineArgs& a, TileLds& L, const TopK<KB>& top, const Pix& p,
                                                 int n, int tx, int ty) {
     const int lane = threadIdx.x & 63;
-    const int K = EXACT ? KB : a.K;
-    const int rows = min(kTile, a.H - ty * kTile), cols = min(kTile, a.W - tx * kTile);
-    const int64_t pix0 = ((int64_t)n * a.H + ty * kTile) * a.W + tx * kTile;
-    const int rowK = a.W * K;  // fragments per image row
-    // EXACT with K a multiple of 4 (the launcher also checked that the four
-    // outputs are 16-byte aligned): 16-byte stores of four slots
-    constexpr bool V4 = EXACT && (KB % 4 == 0);
-    int32_t* const p2f_t = a.p2f + pix0 * K;
-    float* const zbuf_t = a.zbuf + pix0 * K;
-    float* const dist_t = a.dists + pix0 * K;
-    float* const bary_t = a.bary + pix0 * K * 3;
-    static_assert(sizeof(TileLds) >= sizeof(float) * 64 * 2 * (kStageG1 + 1), "id/depth staging exceeds the tile LDS");
-    static_assert(sizeof(TileLds) >= sizeof(float) * 64 * (4 * kStageG2 + 2), "bary/dist staging exceeds the tile LDS");
-    float* stage = reinterpret_cast<float*>(&L);
-    // ids and depths
-    {
-        constexpr int G = KB < kStageG1 ? KB : kStageG1;
-        constexpr int S = G + 1;  // odd stride: lane-major writes hit distinct banks
-        int* sid = reinterpret_cast<int*>(stage);
-        float* sz = stage + 64 * S;
+    const TileOut t{EXACT ? KB : a.K, a.W * (EXACT ? KB : a.K), min(kTile, a.H - ty * kTile),
+                    min(kTile, a.W - tx * kTile)};
+    const int64_t slot0 = (((int64_t)n * a.H + ty * kTile) * a.W + tx * kTile) * t.K;
+    float* const p2f_t = reinterpret_cast<float*>(a.p2f) + slot0;  // (ids move as bit patterns)
+    float* const zbuf_t = a.zbuf + slot0;
+    float* const dist_t = a.dists + slot0;
+    float* const bary_t = a.bary + 3 * slot0;
+    if constexpr (KB < 4) {
+        // one or two slots: a lane's own few words, no staging
+        if ((lane >> 3) < t.rows && (lane & 7) < t.cols) {
+            const int o = (lane >> 3) * t.rowK + (lane & 7) * KB;
 #pragma unroll
-        for (int g0 = 0; g0 < KB; g0 += G) {
-            if (g0 >= K) continue;  // K is uniform: the whole wave skips
-#pragma unroll
-            for (int k = 0; k < G; ++k) {
-                const uint64_t key = top.q[g0 + k];
-                const bool empty = key == kEmptyKey;
-                sid[lane * S + k] = empty ? -1 : (int)(uint32_t)key;
-                sz[lane * S + k] = empty ? -1.0f : __uint_as_float((uint32_t)(key >> 32));
+            for (int k = 0; k < KB; ++k) {
+                float w0, w1, w2, d;
+                slot_values<OPT>(a, top.q[k], p, w0, w1, w2, d);
+                p2f_t[o + k] = __int_as_float(key_id(top.q[k]));
+                zbuf_t[o + k] = key_z(top.q[k]);
+                dist_t[o + k] = d;
+                bary_t[3 * (o + k) + 0] = w0;
+                bary_t[3 * (o + k) + 1] = w1;
+                bary_t[3 * (o + k) + 2] = w2;
             }
-            __syncthreads();
-            if constexpr (V4) {
-                // four consecutive slots of one pixel per lane and store
-                constexpr int Q = G / 4;
-#pragma unroll
-                for (int e0 = 0; e0 < 64 * Q; e0 += 64) {
-                    const int e = e0 + lane;
-                    const int px = e / Q, q = e - px * Q;
-                    const int r = px >> 3, c = px & 7;
-                    if (r < rows && c < cols) {
-                        const int o = r * rowK + c * K + g0 + 4 * q;
-                        const int* si = sid + px * S + 4 * q;
-                        const float* zi = sz + px * S + 4 * q;
-                        nt_store(make_int4(si[0], si[1], si[2], si[3]), p2f_t + o);
-                        nt_store(make_float4(zi[0], zi[1], zi[2], zi[3]), zbuf_t + o);
-                    }
-                }
-            } else {
-                const int gw = min(G, K - g0);
-                const float inv = 1.0f / (float)gw;
-#pragma unroll
-                for (int e0 = 0; e0 < 64 * G; e0 += 64) {
-                    const int e = e0 + lane;
-                    if (e >= 64 * gw) break;
-                    const int px = EXACT ? e / gw : stage_pixel(e, inv);
-                    const int k = e - px * gw;
-                    const int r = px >> 3, c = px & 7;
-                    if (r < rows && c < cols) {
-                        const int o = r * rowK + c * K + g0 + k;
-                        p2f_t[o] = sid[px * S + k];
-                        zbuf_t[o] = sz[px * S + k];
-                    }
-                }
-            }
-            __syncthreads();
         }
-    }
-    // barycentrics and signed distances
-    {
-        constexpr int G = KB < kStageG2 ? KB : kStageG2;
-        constexpr int SB = 3 * G + 1, SD = G + 1;
-        float* sb = stage;
-        float* sd = stage + 64 * SB;
+    } else {
+        // (for EXACT the launcher has checked that the four outputs are 16-byte aligned)
+        static_assert(KB % 4 == 0, "queues of four or more slots are multiples of four");
+        if (__ballot(top.q[0] != kEmptyKey) == 0ull) {
+            fill_rows<KB, 1, EXACT>(p2f_t, t, __int_as_float(-1));
+            fill_rows<KB, 1, EXACT>(zbuf_t, t, -1.0f);
+            fill_rows<KB, 3, EXACT>(bary_t, t, -1.0f);
+            fill_rows<KB, 1, EXACT>(dist_t, t, -1.0f);
+            return;
+        }
+        float* const st = L.stage;
+        // ids, then depths
+        {
+            constexpr int G = KB < kStageG1 ? KB : kStageG1;
+            constexpr int S = G + 1;  // odd stride: lane-major writes hit distinct banks
+            static_assert(64 * S * 4 <= (int)sizeof(TileLds), "id/depth staging exceeds the tile LDS");
 #pragma unroll
-        for (int g0 = 0; g0 < KB; g0 += G) {
-            if (g0 >= K) continue;
+            for (int g0 = 0; g0 < KB; g0 += G) {
+                if (g0 >= t.K) continue;  // K is uniform: the whole wave skips
 #pragma unroll
-            for (int k = 0; k < G; ++k) {
-                const uint64_t key = top.q[g0 + k];
-                float w0 = -1.0f, w1 = -1.0f, w2 = -1.0f, d = -1.0f;
-                if (key != kEmptyKey) {
-                    const FaceRec R = a.recs[(uint32_t)key];
-                    Eval ev;
-                    eval_full(R, p, ev);
-                    w0 = ev.w0;
-                    w1 = ev.w1;
-                    w2 = ev.w2;
-                    if (OPT) {
-                        float zf;
-                        apply_opts(a.opts, R.az, R.dz1, R.dz2, w0, w1, w2, zf);
-                    }
-                    d = ev.inside ? -ev.d2 : ev.d2;
-                }
-                sb[lane * SB + 3 * k + 0] = w0;
-                sb[lane * SB + 3 * k + 1] = w1;
-                sb[lane * SB + 3 * k + 2] = w2;
-                sd[lane * SD + k] = d;
+                for (int k = 0; k < G; ++k) st[lane * S + k] = __int_as_float(key_id(top.q[g0 + k]));
+                __syncthreads();
+                store_staged<G, S, 1, EXACT, true>(p2f_t, st, t, g0);
+                __syncthreads();
+#pragma unroll
+                for (int k = 0; k < G; ++k) st[lane * S + k] = key_z(top.q[g0 + k]);
+                __syncthreads();
+                store_staged<G, S, 1, EXACT, true>(zbuf_t, st, t, g0);
+                __syncthreads();
             }
-            __syncthreads();
-            if constexpr (V4) {
-                constexpr int QB = 3 * G / 4, QD = G / 4;
+        }
+        // barycentrics and signed distances
+        {
+            constexpr int G = KB < kStageG2 ? KB : kStageG2;
+            constexpr int SB = 3 * G + 1, SD = G + 1;
+            static_assert(64 * SB * 4 <= (int)sizeof(TileLds), "bary staging exceeds the tile LDS");
 #pragma unroll
-                for (int e0 = 0; e0 < 64 * QB; e0 += 64) {
-                    const int e = e0 + lane;
-                    const int px = e / QB, q = e - px * QB;
-                    const int r = px >> 3, c = px & 7;
-                    if (r < rows && c < cols) {
-                        const float* bi = sb + px * SB + 4 * q;
-                        *reinterpret_cast<float4*>(bary_t + 3 * (r * rowK + c * K + g0) + 4 * q) =
-                            make_float4(bi[0], bi[1], bi[2], bi[3]);
-                    }
-                }
+            for (int g0 = 0; g0 < KB; g0 += G) {
+                if (g0 >= t.K) continue;
+                float d[G];
 #pragma unroll
-                for (int e0 = 0; e0 < 64 * QD; e0 += 64) {
-                    const int e = e0 + lane;
-                    const int px = e / QD, q = e - px * QD;
-                    const int r = px >> 3, c = px & 7;
-                    if (r < rows && c < cols) {
-                        const float* di = sd + px * SD + 4 * q;
-                        *reinterpret_cast<float4*>(dist_t + r * rowK + c * K + g0 + 4 * q) =
-                            make_float4(di[0], di[1], di[2], di[3]);
-                    }
+                for (int k = 0; k < G; ++k) {
+                    float w0, w1, w2;
+                    slot_values<OPT>(a, top.q[g0 + k], p, w0, w1, w2, d[k]);
+                    st[lane * SB + 3 * k + 0] = w0;
+                    st[lane * SB + 3 * k + 1] = w1;
+                    st[lane * SB + 3 * k + 2] = w2;
                 }
-            } else {
-                const int gw = min(G, K - g0);
-                const float inv3 = 1.0f / (float)(3 * gw), inv1 = 1.0f / (float)gw;
+                __syncthreads();
+                store_staged<G, SB, 3, EXACT, false>(bary_t, st, t, g0);
+                __syncthreads();
 #pragma unroll
-                for (int e0 = 0; e0 < 64 * 3 * G; e0 += 64) {
-                    const int e = e0 + lane;
-                    if (e >= 64 * 3 * gw) break;
-                    const int px = EXACT ? e / (3 * gw) : stage_pixel(e, inv3);
-                    const int m = e - px * 3 * gw;
-                    const int r = px >> 3, c = px & 7;
-                    if (r < rows && c < cols) bary_t[3 * (r * rowK + c * K + g0) + m] = sb[px * SB + m];
-                }
-#pragma unroll
-                for (int e0 = 0; e0 < 64 * G; e0 += 64) {
-                    const int e = e0 + lane;
-                    if (e >= 64 * gw) break;
-                    const int px = EXACT ? e / gw : stage_pixel(e, inv1);
-                    const int k = e - px * gw;
-                    const int r = px >> 3, c = px & 7;
-                    if (r < rows && c < cols) dist_t[r * rowK + c * K + g0 + k] = sd[px * SD + k];
-                }
+                for (int k = 0; k < G; ++k) st[lane * SD + k] = d[k];
+                __syncthreads();
+                store_staged<G, SD, 1, EXACT, false>(dist_t, st, t, g0);
+                __syncthreads();
             }
-            __syncthreads();
         }
     }
 }
@@ -505,46 +536,113 @@ __device__ __forceinline__ void write_fragments(const FineArgs& a, TileLds& L, c
 // j the lanes i and i ^ j exchange the off-diagonal j x j blocks of their
 // 2j x 2j block (the lane with bit j clear keeps its low groups of j bits
 // and takes the partner's low groups into its high ones, the other keeps its
-// high groups and takes the partner's high groups into its low ones).
-__device__ __forceinline__ uint64_t transpose64(uint64_t x, int lane) {
-    constexpr uint64_t kLow[6] = {0x5555555555555555ull, 0x3333333333333333ull, 0x0f0f0f0f0f0f0f0full,
-                                  0x00ff00ff00ff00ffull, 0x0000ffff0000ffffull, 0x00000000ffffffffull};
+// high groups and takes the partner's high groups into its low ones).  All in
+// vector registers: stages 32 and 16 are the half-wave and half-row swaps,
+// the others fetch the partner's words with DPP; about 30 instructions,
+// where shuffles through the LDS took 70 and twelve LDS operations.
+struct Transpose64 {
+    uint32_t sel8;          // byte selector of stage 8
+    uint32_t keep[3];       // stages 4, 2, 1: the bits a lane keeps
+    uint32_t rot[3];        // and the rotation that brings the partner's bits
+    __device__ __forceinline__ void init(int lane) {
+        // v_perm bytes: 0-3 from the lane's own word, 4-7 from the partner's
+        sel8 = (lane & 8) ? 0x03070105u : 0x06020400u;
+        const uint32_t low[3] = {0x0f0f0f0fu, 0x33333333u, 0x55555555u};
 #pragma unroll
-    for (int s = 5; s >= 0; --s) {
-        const int j = 1 << s;
-        const uint64_t m = kLow[s];
-        const uint64_t y = __shfl_xor(x, j);
-        x = (lane & j) ? ((x & ~m) | ((y & ~m) >> j)) : ((x & m) | ((y & m) << j));
+        for (int i = 0; i < 3; ++i) {
+            const int j = 4 >> i;
+            keep[i] = (lane & j) ? ~low[i] : low[i];
+            rot[i] = (lane & j) ? (uint32_t)j : 32u - (uint32_t)j;
+        }
     }
-    return x;
-}
+    template <int kCtrl>
+    static __device__ __forceinline__ uint32_t dpp(uint32_t v) {
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, 0xf, 0xf, true);
+    }
+    __device__ __forceinline__ uint32_t mix(uint32_t x, uint32_t y, int i) const {
+        const uint32_t t = __builtin_amdgcn_alignbit(y, y, rot[i]);
+        return (x & keep[i]) | (t & ~keep[i]);
+    }
+    __device__ __forceinline__ uint64_t operator()(uint64_t v) const {
+        uint32_t x = (uint32_t)v, y = (uint32_t)(v >> 32);
+        // 32: the upper half-wave's low words against the lower half-wave's high words
+        const auto s32 = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+        x = s32[0];
+        y = s32[1];
+        // 16: the same for 16-bit halves between the rows of a half-wave
+        const uint32_t lo = __builtin_amdgcn_perm(y, x, 0x05040100u), hi = __builtin_amdgcn_perm(y, x, 0x07060302u);
+        const auto s16 = __builtin_amdgcn_permlane16_swap(lo, hi, false, false);
+        x = __builtin_amdgcn_perm(s16[1], s16[0], 0x05040100u);
+        y = __builtin_amdgcn_perm(s16[1], s16[0], 0x07060302u);
+        // 8: partner lane ^ 8 (a rotation of the row by 8)
+        x = __builtin_amdgcn_perm(dpp<0x128>(x), x, sel8);
+        y = __builtin_amdgcn_perm(dpp<0x128>(y), y, sel8);
+        // 4: lane ^ 4 is the half-row mirror (^ 7) of the quad mirror (^ 3)
+        x = mix(x, dpp<0x141>(dpp<0x1b>(x)), 0);
+        y = mix(y, dpp<0x141>(dpp<0x1b>(y)), 0);
+        // 2 and 1: quad permutations
+        x = mix(x, dpp<0x4e>(x), 1);
+        y = mix(y, dpp<0x4e>(y), 1);
+        x = mix(x, dpp<0xb1>(x), 2);
+        y = mix(y, dpp<0xb1>(y), 2);
+        return ((uint64_t)y << 32) | x;
+    }
+};
 
-// One wave rasterizes one 8x8 tile in three steps per chunk of 64 faces:
-//  1. gather the chunk's face records, keep those whose box (narrowed by the
-//     edge lines) may cover a pixel of the tile (wave ballot + prefix count
-//     compacts them into LDS), each with its 64-bit mask of such pixels;
-//  2. transpose the kept faces' masks across the wave (lane j holds record
-//     j's mask), so that lane p holds the chunk's faces that may cover pixel p;
+// One wave rasterizes one 8x8 tile:
+//  1. gather the face records of the list a wave-wide chunk at a time and
+//     keep those whose pixel ranges (narrowed by the edge lines) cover a pixel
+//     of the tile: a wave ballot and prefix count append them to the LDS
+//     block, each with its 64-bit mask of such pixels;
+//  2. when the block is full (64 records) or the list ends, transpose the kept
+//     faces' masks across the wave (lane j holds record j's mask), so that
+//     lane p holds the faces that may cover pixel p;
 //  3. every lane walks only its own faces, runs the full test and inserts
 //     the faces that count into its register top-K.
 // Step 3 is where the arithmetic is; gathering each pixel's candidates first
-// keeps lanes from idling on faces that miss their pixel.
+// keeps lanes from idling on faces that miss their pixel, and filling the
+// block over several chunks first keeps the rounds of step 3 full (a tile of
+// a 16-pixel bin keeps a third of the bin's list).  Faces of a chunk that no
+// longer fit are gathered again after the test: holding their records in
+// registers across it would cost a wave per SIMD.
+template <int KB, bool OPT>
+__device__ __forceinline__ void test_kept(const FineArgs& a, const TileLds& L, const Transpose64& T, TopK<KB>& top,
+                                          const Pix& p, int m) {
+    const int lane = threadIdx.x & 63;
+    __syncthreads();
+    uint64_t mine = T(lane < m ? L.rec[lane].mask : 0ull);
+    // eight candidates per round; the round count is the wave's longest
+    // list, so the loop is uniform and the queue stays in place across rounds
+    const int nmax = wave_max(__popcll(mine));
+    for (int i0 = 0; i0 < nmax; i0 += 8) {
+        uint64_t b[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            uint64_t key = kEmptyKey;
+            if (mine != 0ull) {
+                const int j = __ffsll((unsigned long long)mine) - 1;
+                mine &= mine - 1;
+                float z;
+                if (face_counts_in_box(L.rec[j], p, a.blur, z, OPT ? a.opts : 0)) key = make_key(z, L.rec[j].fid);
+            }
+            b[u] = key;
+        }
+        top.push8(b);
+    }
+    __syncthreads();
+}
+
 template <int KB, bool BINNED, bool EXACT, bool OPT>
 __device__ __forceinline__ void raster_tile(const FineArgs& a, TileLds& L, int n, int tx, int ty) {
     const int lane = threadIdx.x & 63;
-    const int r = ty * kTile + (lane >> 3);
-    const int c = tx * kTile + (lane & 7);
-    const Pix p = make_pix(r, c, a.H, a.W);
-    // extent of the tile's pixel centres (x decreases with c, y with r), less a
-    // margin so that the float test never rejects what the pixel ranges keep
-    const int c_last = min(tx * kTile + kTile - 1, a.W - 1);
-    const int r_last = min(ty * kTile + kTile - 1, a.H - 1);
-    const float mx = 0.1f / (float)a.W, my = 0.1f / (float)a.H;  // 0.05 px, looser than pix_range (0.01 px)
-    const float tx_hi = pix_x(tx * kTile, a.W) + mx, tx_lo = pix_x(c_last, a.W) - mx;
-    const float ty_hi = pix_y(ty * kTile, a.H) + my, ty_lo = pix_y(r_last, a.H) - my;
+    const int x0 = tx * kTile, y0 = ty * kTile;
+    const Pix p = make_pix(y0 + (lane >> 3), x0 + (lane & 7), a.H, a.W);
+    // the tile's first pixel centre (lane 0's), for the edge masks
+    const double px0 = 1.0 - (double)(2 * x0 + 1) / (double)a.W, py0 = 1.0 - (double)(2 * y0 + 1) / (double)a.H;
+    const float sx = 2.0f / (float)a.W, sy = 2.0f / (float)a.H, rg = edge_radius(a.blur, a.H, a.W);
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    // radius beyond which a pixel outside an edge line cannot count (see edge_mask)
-    const double rg = (double)sqrtf(a.blur) * (1.0 + 1e-4) + 1e-6;
+    Transpose64 T;
+    T.init(lane);
 
     TopK<KB> top;
     top.init();
@@ -563,28 +661,29 @@ __device__ __forceinline__ void raster_tile(const FineArgs& a, TileLds& L, int n
         base = lo;
         cnt = hi > lo ? hi - lo : 0;
     }
-    for (int64_t c0 = 0; c0 < cnt; c0 += kChunk) {
-        // 1. gather and compact the chunk's faces that overlap the tile
+    int64_t c0 = 0;
+    uint64_t todo = ~0ull;  // lanes of the chunk at c0 still to be gathered
+    int m = 0;              // records in the block
+    while (c0 < cnt) {
+        // 1. gather and compact the faces that overlap the tile
         const int64_t e = c0 + lane;
-        const bool in_list = e < cnt;
+        const bool in_list = e < cnt && ((todo >> lane) & 1ull);
         const int fid = in_list ? (BINNED ? list[e] : (int)(base + e)) : 0;
         // the record as seven 16-byte words (pa | ab | ac | E, a.z, mesh |
-        // dz1, dz2, 1/E, il0 | il1, il2, pad | grown box)
+        // dz1, dz2, 1/E, il0 | il1, il2, pad | pixel ranges)
         static_assert(sizeof(FaceRec) == 7 * sizeof(float4), "face record layout");
         const float4* rsrc = reinterpret_cast<const float4*>(a.recs + (in_list ? fid : (BINNED ? list[0] : (int)base)));
         const float4 rv0 = rsrc[0], rv1 = rsrc[1], rv2 = rsrc[2], rv3 = rsrc[3], rv4 = rsrc[4], rv5 = rsrc[5];
-        const float4 rv6 = rsrc[6];
-        uint64_t pm = in_list ? tile_mask(rv6, a.H, a.W, tx * kTile, ty * kTile, tx_lo, tx_hi, ty_lo, ty_hi) : 0ull;
+        const int4 rv6 = reinterpret_cast<const int4*>(rsrc)[6];
+        uint64_t pm = in_list ? tile_mask(rv6, x0, y0) : 0ull;
         if (pm != 0ull) {
-            // narrow the box's pixels to those near or inside the triangle
+            // narrow the ranges' pixels to those near or inside the triangle
             const EdgeGeo G{f4_as_d2(rv0), f4_as_d2(rv1), f4_as_d2(rv2), f4_as_d2(rv3).x};
-            pm &= edge_mask(G, rg, a.H, a.W, tx * kTile, ty * kTile);
+            pm &= edge_mask(G, rg, px0, py0, sx, sy);
         }
-        const bool keep = pm != 0ull;
-        const uint64_t kept = __ballot(keep);
-        const int m = __popcll(kept);
-        if (keep) {
-            const int dst = __popcll(kept & lt_mask);
+        const uint64_t kept = __ballot(pm != 0ull);
+        const int dst = m + __popcll(kept & lt_mask);
+        if (pm != 0ull && dst < kChunk) {
             float4* rdst = reinterpret_cast<float4*>(&L.rec[dst]);
             rdst[0] = rv0;
             rdst[1] = rv1;
@@ -594,33 +693,14 @@ __device__ __forceinline__ void raster_tile(const FineArgs& a, TileLds& L, int n
             rdst[5] = make_float4(rv5.y, __int_as_float(fid), __uint_as_float((uint32_t)pm),
                                   __uint_as_float((uint32_t)(pm >> 32)));  // il2, id, mask
         }
-        __syncthreads();
-        // 2. per lane, the faces whose boxes may contain the lane's pixel: lane
-        //    j holds kept face j's pixel mask (row j of a 64x64 bit matrix);
-        //    the transpose gives lane p the faces of pixel p
-        uint64_t mine = lane < m ? L.rec[lane].mask : 0ull;
-        mine = transpose64(mine, lane);
-        const int nl = __popcll(mine);
-        // 3. full test of the lane's own candidates, eight per round; the
-        //    round count is the wave's longest list, so the loop is uniform
-        //    and the queue stays in place across rounds
-        const int nmax = wave_max(nl);
-        for (int i0 = 0; i0 < nmax; i0 += 8) {
-            uint64_t b[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                uint64_t key = kEmptyKey;
-                if (mine != 0ull) {
-                    const int j = __ffsll((unsigned long long)mine) - 1;
-                    mine &= mine - 1;
-                    float z;
-                    if (face_counts_in_box(L.rec[j], p, a.blur, z, OPT ? a.opts : 0)) key = make_key(z, L.rec[j].fid);
-                }
-                b[u] = key;
-            }
-            top.push8(b);
+        m += __popcll(kept);
+        // a full block leaves the rest of the chunk for after the test
+        todo = m > kChunk ? kept & __ballot(dst >= kChunk) : ~0ull;
+        c0 += m > kChunk ? 0 : kChunk;
+        if (m > kChunk || c0 >= cnt) {  // (uniform)
+            test_kept<KB, OPT>(a, L, T, top, p, min(m, kChunk));
+            m = 0;
         }
-        __syncthreads();
     }
     write_fragments<KB, EXACT, OPT>(a, L, top, p, n, tx, ty);
 }

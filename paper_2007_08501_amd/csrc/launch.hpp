@@ -15,7 +15,8 @@ hipError_t launch_header_init(int* hdr, const BinSig& sig, hipStream_t s);
 hipError_t launch_status_out(const int* hdr, int32_t* out, hipStream_t s);
 
 hipError_t launch_face_setup(const float* verts, int64_t V, const int32_t* faces, int64_t F, const int64_t* first,
-                             const int64_t* nf, int N, float rb, int opts, FaceRec* recs, int* hdr, hipStream_t s);
+                             const int64_t* nf, int N, int H, int W, float rb, int opts, FaceRec* recs, int* hdr,
+                             hipStream_t s);
 
 hipError_t launch_binning(const FaceRec* recs, int64_t F, int N, int H, int W, int bs, int M, int* counts, int* lists,
                           int* hdr, hipStream_t s);

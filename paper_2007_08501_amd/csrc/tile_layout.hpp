@@ -35,5 +35,12 @@ constexpr int stage_words_g2(int kb) {
 static_assert(4 * stage_words_g1(64) <= kLdsBytes, "id/depth staging exceeds the tile LDS");
 static_assert(4 * stage_words_g2(64) <= kLdsBytes, "bary/dist staging exceeds the tile LDS");
 
+// The kernel's block: one output array is staged at a time, which never
+// takes more than the records plus one word a lane (three barycentrics of
+// kStageG2 slots).
+constexpr int kBlockBytes = kRecBytes + 4 * kLanes;
+static_assert(4 * kLanes * (kStageG1 + 1) <= kBlockBytes, "id or depth staging exceeds the kernel's block");
+static_assert(4 * kLanes * (3 * kStageG2 + 1) <= kBlockBytes, "barycentric staging exceeds the kernel's block");
+
 }  // namespace tile_layout
 }  // namespace rast
