@@ -18,6 +18,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 namespace rast {
@@ -508,10 +509,10 @@ __device__ __forceinline__ double2 f4_as_d2(const float4 v) {
     return make_double2(__hiloint2double(__float_as_int(v.y), __float_as_int(v.x)),
                         __hiloint2double(__float_as_int(v.w), __float_as_int(v.z)));
 }
-// Radius of the mask: sqrt(blur) and the margins above.
-__device__ __forceinline__ float edge_radius(float blur, int H, int W) {
+// Radius of the mask: sqrt(blur) and the margins above (computed by the host, once a call).
+inline float edge_radius(float blur, int H, int W) {
     const float rg = sqrtf(blur) * (1.0f + 1e-4f) + 1e-6f;
-    return rg + (rg + 23.0f / (float)min(H, W)) * 0x1p-20f;
+    return rg + (rg + 23.0f / (float)(H < W ? H : W)) * 0x1p-20f;
 }
 // (px, py): centre of the tile's first pixel; sx = 2/W, sy = 2/H.
 __device__ __forceinline__ uint64_t edge_mask(const EdgeGeo& G, float rg, double px, double py, float sx, float sy) {

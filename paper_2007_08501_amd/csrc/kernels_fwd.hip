@@ -282,7 +282,8 @@ struct FineArgs {
     int64_t F;
     int N, H, W, K;
     float blur;
-    int opts;  // rasterizer options (kOpt*)
+    float rg, sx, sy;  // edge_radius(), 2 / W, 2 / H (for the edge masks)
+    int opts;          // rasterizer options (kOpt*)
     int bs, nby, nbx, M;
     int tiles_x, tiles_y;
     int32_t* p2f;
@@ -590,21 +591,30 @@ struct Transpose64 {
 };
 
 // One wave rasterizes one 8x8 tile:
-//  1. gather the face records of the list a wave-wide chunk at a time and
-//     keep those whose pixel ranges (narrowed by the edge lines) cover a pixel
-//     of the tile: a wave ballot and prefix count append them to the LDS
+//  1. where the list is longer than the tile needs (a bin of several tiles, or
+//     a whole mesh), read only the pixel ranges of its faces, a wave-wide chunk
+//     at a time, and push the ids of those that reach the tile together into
+//     full lanes (each lane's place from a ballot, moved by ds_permute);
+//  2. gather the records of up to 64 such faces, one a lane, narrow each one's
+//     pixels by its edge lines, and append those that keep a pixel to the LDS
 //     block, each with its 64-bit mask of such pixels;
-//  2. when the block is full (64 records) or the list ends, transpose the kept
+//  3. when the block is full (64 records) or the list ends, transpose the kept
 //     faces' masks across the wave (lane j holds record j's mask), so that
 //     lane p holds the faces that may cover pixel p;
-//  3. every lane walks only its own faces, runs the full test and inserts
+//  4. every lane walks only its own faces, runs the full test and inserts
 //     the faces that count into its register top-K.
-// Step 3 is where the arithmetic is; gathering each pixel's candidates first
-// keeps lanes from idling on faces that miss their pixel, and filling the
-// block over several chunks first keeps the rounds of step 3 full (a tile of
-// a 16-pixel bin keeps a third of the bin's list).  Faces of a chunk that no
-// longer fit are gathered again after the test: holding their records in
+// Step 4 is where the arithmetic is; gathering each pixel's candidates first
+// keeps lanes from idling on faces that miss their pixel, and steps 1 and 3
+// keep the lanes of the edge masks and the rounds of step 4 full (a tile of
+// a 16-pixel bin needs a third of the bin's list).  Faces that no longer fit
+// the block are gathered again after the test: holding their records in
 // registers across it would cost a wave per SIMD.
+__device__ __forceinline__ double first_lane(double v) {
+    const int lo = __builtin_amdgcn_readfirstlane(__double2loint(v));
+    const int hi = __builtin_amdgcn_readfirstlane(__double2hiint(v));
+    return __hiloint2double(hi, lo);
+}
+
 template <int KB, bool OPT>
 __device__ __forceinline__ void test_kept(const FineArgs& a, const TileLds& L, const Transpose64& T, TopK<KB>& top,
                                           const Pix& p, int m) {
@@ -638,8 +648,7 @@ __device__ __forceinline__ void raster_tile(const FineArgs& a, TileLds& L, int n
     const int x0 = tx * kTile, y0 = ty * kTile;
     const Pix p = make_pix(y0 + (lane >> 3), x0 + (lane & 7), a.H, a.W);
     // the tile's first pixel centre (lane 0's), for the edge masks
-    const double px0 = 1.0 - (double)(2 * x0 + 1) / (double)a.W, py0 = 1.0 - (double)(2 * y0 + 1) / (double)a.H;
-    const float sx = 2.0f / (float)a.W, sy = 2.0f / (float)a.H, rg = edge_radius(a.blur, a.H, a.W);
+    const double px0 = first_lane(p.x), py0 = first_lane(p.y);
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     Transpose64 T;
     T.init(lane);
@@ -661,25 +670,61 @@ __device__ __forceinline__ void raster_tile(const FineArgs& a, TileLds& L, int n
         base = lo;
         cnt = hi > lo ? hi - lo : 0;
     }
-    int64_t c0 = 0;
-    uint64_t todo = ~0ull;  // lanes of the chunk at c0 still to be gathered
-    int m = 0;              // records in the block
-    while (c0 < cnt) {
-        // 1. gather and compact the faces that overlap the tile
-        const int64_t e = c0 + lane;
-        const bool in_list = e < cnt && ((todo >> lane) & 1ull);
-        const int fid = in_list ? (BINNED ? list[e] : (int)(base + e)) : 0;
+    int64_t c0 = 0;       // list entries read
+    int pend = 0, np = 0; // ids waiting to be gathered: lane i < np holds the i-th
+    int batch = 0;        // the lane's id of the present batch
+    uint64_t todo = 0ull; // lanes of the batch still to be gathered
+    bool last = cnt == 0; // nothing comes after this batch
+    int m = 0;            // records in the block
+    while (cnt > 0) {
+        if (todo == 0ull) {
+            // 1. the next batch of ids
+            int over = 0;  // ids past the 64th
+            if (BINNED && a.bs == kTile) {
+                pend = c0 + lane < cnt ? list[c0 + lane] : 0;
+                np = (int)min((int64_t)kChunk, cnt - c0);
+                c0 += kChunk;
+            } else {
+                while (np < kChunk && c0 < cnt) {
+                    const int64_t e = c0 + lane;
+                    const int id = e < cnt ? (BINNED ? list[e] : (int)(base + e)) : -1;
+                    bool hit = false;
+                    if (id >= 0) {
+                        const int4 q = a.recs[id].px;
+                        hit = q.x < x0 + kTile && q.y >= x0 && q.z < y0 + kTile && q.w >= y0 && q.x <= q.y && q.z <= q.w;
+                    }
+                    const uint64_t hits = __ballot(hit);
+                    const int add = __popcll(hits);
+                    // every hit goes to its place (modulo 64), the other lanes
+                    // to the first place after them, which is not read
+                    const int to = (np + (hit ? __popcll(hits & lt_mask) : add)) & (kChunk - 1);
+                    const int v = __builtin_amdgcn_ds_permute(4 * to, id);
+                    if (lane >= np && lane < np + add) pend = v;
+                    if (lane < np + add - kChunk) over = v;
+                    np += add;
+                    c0 += kChunk;
+                }
+            }
+            batch = pend;
+            const int nb = min(np, kChunk);
+            todo = nb == kChunk ? ~0ull : (1ull << nb) - 1ull;
+            np -= nb;
+            pend = over;
+            last = c0 >= cnt && np == 0;
+        }
+        // 2. gather and compact the faces that overlap the tile
+        const bool mine = (todo >> lane) & 1ull;
+        uint64_t pm = 0ull;
         // the record as seven 16-byte words (pa | ab | ac | E, a.z, mesh |
         // dz1, dz2, 1/E, il0 | il1, il2, pad | pixel ranges)
         static_assert(sizeof(FaceRec) == 7 * sizeof(float4), "face record layout");
-        const float4* rsrc = reinterpret_cast<const float4*>(a.recs + (in_list ? fid : (BINNED ? list[0] : (int)base)));
+        const float4* rsrc = reinterpret_cast<const float4*>(a.recs + (mine ? batch : 0));
         const float4 rv0 = rsrc[0], rv1 = rsrc[1], rv2 = rsrc[2], rv3 = rsrc[3], rv4 = rsrc[4], rv5 = rsrc[5];
-        const int4 rv6 = reinterpret_cast<const int4*>(rsrc)[6];
-        uint64_t pm = in_list ? tile_mask(rv6, x0, y0) : 0ull;
+        if (mine) pm = tile_mask(reinterpret_cast<const int4*>(rsrc)[6], x0, y0);
         if (pm != 0ull) {
             // narrow the ranges' pixels to those near or inside the triangle
             const EdgeGeo G{f4_as_d2(rv0), f4_as_d2(rv1), f4_as_d2(rv2), f4_as_d2(rv3).x};
-            pm &= edge_mask(G, rg, px0, py0, sx, sy);
+            pm &= edge_mask(G, a.rg, px0, py0, a.sx, a.sy);
         }
         const uint64_t kept = __ballot(pm != 0ull);
         const int dst = m + __popcll(kept & lt_mask);
@@ -690,17 +735,18 @@ __device__ __forceinline__ void raster_tile(const FineArgs& a, TileLds& L, int n
             rdst[2] = rv2;
             rdst[3] = make_float4(rv3.x, rv3.y, rv3.z, rv4.x);  // E | a.z, dz1
             rdst[4] = make_float4(rv4.y, rv4.z, rv4.w, rv5.x);  // dz2, 1/E, il0, il1
-            rdst[5] = make_float4(rv5.y, __int_as_float(fid), __uint_as_float((uint32_t)pm),
+            rdst[5] = make_float4(rv5.y, __int_as_float(batch), __uint_as_float((uint32_t)pm),
                                   __uint_as_float((uint32_t)(pm >> 32)));  // il2, id, mask
         }
         m += __popcll(kept);
-        // a full block leaves the rest of the chunk for after the test
-        todo = m > kChunk ? kept & __ballot(dst >= kChunk) : ~0ull;
-        c0 += m > kChunk ? 0 : kChunk;
-        if (m > kChunk || c0 >= cnt) {  // (uniform)
+        // a full block leaves the rest of the batch for after the test
+        todo = m > kChunk ? kept & __ballot(dst >= kChunk) : 0ull;
+        const bool end = todo == 0ull && last;
+        if (m > kChunk || (end && m > 0)) {  // (uniform)
             test_kept<KB, OPT>(a, L, T, top, p, min(m, kChunk));
             m = 0;
         }
+        if (end) break;
     }
     write_fragments<KB, EXACT, OPT>(a, L, top, p, n, tx, ty);
 }
@@ -846,6 +892,9 @@ hipError_t launch_fine(const FaceRec* recs, const int64_t* first, const int64_t*
     a.W = W;
     a.K = K;
     a.blur = blur;
+    a.rg = edge_radius(blur, H, W);
+    a.sx = 2.0f / (float)W;
+    a.sy = 2.0f / (float)H;
     a.opts = opts;
     a.bs = bs > 0 ? bs : kTile;
     a.nby = bs > 0 ? (H + bs - 1) / bs : 0;
