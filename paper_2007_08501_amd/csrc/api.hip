@@ -257,7 +257,7 @@ int rasterize_meshes_bwd(const float* verts_packed, int64_t V, const int32_t* fa
         verts_packed, V, faces_packed, F, mesh_to_face_first_idx, num_faces_per_mesh, N, H, W, faces_per_pixel,
         blur_radius, options, bin_size, max_faces_per_bin, pix_to_face, grad_zbuf, grad_bary, grad_dists, grad_verts,
         (int*)(ws + L.hdr), (rast::FaceRec*)(ws + L.recs), (int*)(ws + L.counts), (int*)(ws + L.lists),
-        (float*)(ws + L.partial), (int*)(ws + L.big), (flags & RAST_BWD_REUSE_FORWARD) != 0,
+        (int*)(ws + L.order), (float*)(ws + L.partial), (int*)(ws + L.big), (flags & RAST_BWD_REUSE_FORWARD) != 0,
         bin_signature(F, N, H, W, bin_size, bin_size > 0 ? max_faces_per_bin : 0, blur_radius, options), s,
         tl_events.begin[RAST_KERNEL_BWD], tl_events.end[RAST_KERNEL_BWD]));
 }

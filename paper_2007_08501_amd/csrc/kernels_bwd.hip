@@ -4,8 +4,8 @@
 // Fragment data avoid recomputing face-pixel intersections); the backward
 // recomputes barycentrics, z and the nearest edge of every filled slot and
 // sums the chain rule into the nine vertex coordinates of its face.  Two
-// forms.  The binned form (the forward's bins): one workgroup per bin, the
-// bin's faces in LDS, exact fixed-point sums per face (described with its
+// forms.  The binned form (the forward's bins): one workgroup per cell of
+// pixels, the cell's faces in LDS, FP64 sums per face (described with its
 // kernels below).  The per-face form (no bins): sixteen lanes scan the pixels
 // of face f's blur-grown bounding box (the only pixels whose slots the
 // forward can fill with f), find the slot holding f in each and sum in
@@ -23,6 +23,8 @@
 //   dists = s d2 (s = -1 inside, +1 outside); on the nearest edge (s0, t) with
 //   nearest point Q = R_s0 + u (R_t - R_s0) (relative to p):
 //   d d2/d s0 = 2 (1-u) Q,  d d2/d t = 2 u Q.
+#include <algorithm>
+
 #include "../../include/rast.h"
 #include "device.hpp"
 #include "launch.hpp"
@@ -53,9 +55,13 @@ struct BwdArgs {
     const FaceRec* recs;
     const int* counts;
     const int* lists;
-    float* partial;    // (F, 4, 9): a face's nine coordinate sums in the i-th bin of its range
+    float* partial;    // (F, 4, 9): a face's nine coordinate sums in the i-th cell of its range
     unsigned char* pmask;  // (F, 4): partial row written by this call (the binned form; shares big's memory)
     int bs, nby, nbx, M;
+    int* crowded;          // cells left to the second kernel (shares the forward's tile order's memory)
+    float inv_k;           // 1 / K
+    int lgw, lgh;          // the binned form's cells: log2 of their width and height in pixels
+    int ncy, ncx;          // rows and columns of cells per image
     int reuse;         // records and bins come from the forward: check its signature first
     BinSig sig;        // the signature this call expects
 };
@@ -258,18 +264,26 @@ __device__ __forceinline__ bool load_face(const BwdArgs& a, int64_t f, FaceRec& 
     return R.ok();
 }
 
-__device__ __forceinline__ uint32_t vhash(int v) { return ((uint32_t)v * 2654435761u) >> (32 - 10); }
+// Sixteen consecutive vertices keep their order in the table (the faces of a
+// workgroup mostly share runs of vertices), so that the flush's atomics of
+// neighbouring lanes fall into the same lines.
+__device__ __forceinline__ uint32_t vhash(int v) {
+    return (((((uint32_t)v >> 4) * 2654435761u) >> (32 - 6)) << 4) | ((uint32_t)v & 15u);
+}
+static_assert(kHash == 1 << 10, "vhash yields 10 bits");
 
 // Merges (vertex, grad3) into the workgroup's LDS table; falls back to a global
-// atomic when the table is full.
-__device__ __forceinline__ void lds_add(int* keys, float* vals, float* grad, int v, float x, float y, float z) {
+// atomic when the table is full.  The sums are FP64: LDS has FP64 atomics in
+// hardware, FP32 ones are a compare-and-swap loop (measured over random words:
+// 2.66 ms for 537 M FP32 adds, 0.29 ms for as many FP64 ones).
+__device__ __forceinline__ void lds_add(int* keys, double* vals, float* grad, int v, float x, float y, float z) {
     uint32_t h = vhash(v);
     for (int probe = 0; probe < kHash; ++probe) {
         int prev = atomicCAS(&keys[h], -1, v);
         if (prev == -1 || prev == v) {
-            atomicAdd(&vals[3 * h + 0], x);
-            atomicAdd(&vals[3 * h + 1], y);
-            atomicAdd(&vals[3 * h + 2], z);
+            atomicAdd(&vals[3 * h + 0], (double)x);
+            atomicAdd(&vals[3 * h + 1], (double)y);
+            atomicAdd(&vals[3 * h + 2], (double)z);
             return;
         }
         h = (h + 1) & (kHash - 1);
@@ -277,6 +291,23 @@ __device__ __forceinline__ void lds_add(int* keys, float* vals, float* grad, int
     atomicAdd(grad + 3 * (int64_t)v + 0, x);
     atomicAdd(grad + 3 * (int64_t)v + 1, y);
     atomicAdd(grad + 3 * (int64_t)v + 2, z);
+}
+
+__device__ __forceinline__ void clear_table(int* keys, double* vals) {
+    for (int i = threadIdx.x; i < kHash; i += kBwdBlock) keys[i] = -1;
+    for (int i = threadIdx.x; i < 3 * kHash; i += kBwdBlock) vals[i] = 0.0;
+}
+
+// Adds the table to grad_verts: one atomic per (vertex, coordinate), lanes
+// running over the words of the table's rows, so that the atomics of a wave
+// fall into few lines (three adds per lane, a row apart each, cost 2.6 times
+// as much: 0.50 against 0.19 ms for 10 M adds to random rows).
+__device__ __forceinline__ void flush_table(float* grad, const int* keys, const double* vals) {
+    for (int i = threadIdx.x; i < 3 * kHash; i += kBwdBlock) {
+        const int h = (int)((uint32_t)i / 3u);
+        const int v = keys[h];
+        if (v >= 0) atomicAdd(grad + 3 * (int64_t)v + (i - 3 * h), (float)vals[i]);
+    }
 }
 
 // A face's box is scanned by kFaceLanes lanes side by side (consecutive
@@ -293,11 +324,8 @@ static_assert(3 * kFaceGroups * kFaceMaxPer <= kHash, "a workgroup's vertices fi
 
 __global__ __launch_bounds__(kBwdBlock) void bwd_faces_kernel(BwdArgs a, int per) {
     __shared__ int keys[kHash];
-    __shared__ float vals[3 * kHash];
-    for (int i = threadIdx.x; i < kHash; i += kBwdBlock) {
-        keys[i] = -1;
-        vals[3 * i] = vals[3 * i + 1] = vals[3 * i + 2] = 0.0f;
-    }
+    __shared__ double vals[3 * kHash];
+    clear_table(keys, vals);
     __syncthreads();
     const int sub = threadIdx.x & (kFaceLanes - 1), grp = threadIdx.x / kFaceLanes;
     for (int it = 0; it < per; ++it) {
@@ -341,14 +369,7 @@ __global__ __launch_bounds__(kBwdBlock) void bwd_faces_kernel(BwdArgs a, int per
         }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < kHash; i += kBwdBlock) {
-        int v = keys[i];
-        if (v >= 0) {
-            atomicAdd(a.grad + 3 * (int64_t)v + 0, vals[3 * i + 0]);
-            atomicAdd(a.grad + 3 * (int64_t)v + 1, vals[3 * i + 1]);
-            atomicAdd(a.grad + 3 * (int64_t)v + 2, vals[3 * i + 2]);
-        }
-    }
+    flush_table(a.grad, keys, vals);
 }
 
 // Faces with large boxes: each workgroup takes the next listed face and its
@@ -401,100 +422,81 @@ __global__ __launch_bounds__(kBwdBlock) void bwd_big_faces_kernel(BwdArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Binned form.  Pass 1: one workgroup per bin reads the slots of the bin's
-// pixels once (coalesced reads of pix_to_face and the gradients), maps each
-// slot's face to a chunk index through an LDS hash table, and accumulates the
-// nine coordinate sums per face in LDS as 64-bit fixed-point integers: integer
-// LDS atomics cost next to nothing on this hardware and float LDS atomics a
-// great deal (measured at config 4: 2.3 ms for the pass with float LDS
-// atomics, 0.95 ms with integer ones), and the per-bin sums become exact and
-// independent of the order of the additions.  The grid is 2^-S with
-// S = 38 - 2 log2(bin size) (2^-32 at bin size 8); a term must lie below
-// 2^min(51 - S, 62 - 2 log2(bin size) - S) (2^19 at bin size 8), where the
-// conversion is exact and a face's at most bin_size^2 terms cannot overflow;
-// a larger term (a sliver's geometric factor times a large gradient) goes to
-// grad_verts directly with a float atomic.  Terms are rounded to the nearest
-// grid point.  The pass records the largest face sum of the call (at the
-// flush, off the hot loop); if it lies below 2^(18 - S) -- gradients so small
-// that the grid holds them to fewer than 18 bits -- a second launch of the
-// pass (the rescue) redoes the sums on a grid 2^30 times finer than that
-// largest sum, after the vertex gradients are cleared again.  Normally the
-// rescue launch only reads the recorded sum and exits.  A face's nine sums
-// from a bin go to its own row partial[f][i] for the i-th bin of its range (no
-// global atomic), and the row's byte in an (F, 4) mask is set.  Pass 2: one
-// thread per face adds the rows the mask names and merges per vertex in LDS;
-// one float atomic per (vertex, coordinate) per workgroup.  Faces spanning
-// more than four bins take global atomics directly.
+// Binned form.  Pass 1: one workgroup per cell of pixels reads the slots of
+// the cell's pixels (coalesced reads of pix_to_face and the gradients), maps
+// each slot's face to a chunk index through an LDS hash table, and accumulates
+// the nine coordinate sums per face in LDS in FP64.  LDS adds FP64 in
+// hardware (FP32 adds are a compare-and-swap loop: 2.3 ms for the pass at
+// 4 x 1024 x 1024 pixels, K = 16), and an FP64 sum of FP32 terms needs no scale
+// and no range: 64-bit fixed point cost three more instructions a term, a
+// range check a slot, a recorded maximum and a second launch for gradients too
+// small for the grid.  A face's nine sums from a cell go to its own row
+// partial[f][i] for the i-th cell of its range (no global atomic), and the
+// row's byte in an (F, 4) mask is set.  Pass 2: the rows that the mask names
+// are added per face and merged per vertex in LDS; one float atomic per
+// (vertex, coordinate) per workgroup.  Faces spanning more than four cells
+// go to grad_verts directly.
+//
+// Cells are 8, 16 or 32 pixels wide and high, independent of the bins but for
+// dividing them: the largest whose slots the workgroup holds at once (1,024).
+// Larger bins as cells had their slots scanned once per 160 listed faces, on
+// too few workgroups.
 // ---------------------------------------------------------------------------
 constexpr int kP1Threads = 256;
-constexpr int kP1Chunk = 160;    // faces staged in LDS per pass over a bin's slots
-static_assert(kP1Chunk <= kP1Threads, "a chunk's faces are gathered one per thread");
+constexpr int kP1Chunk = 160;    // faces staged in LDS per pass over a cell's slots
+constexpr int kP1Rows = 184;     // rows of sums in LDS (at least kP1Chunk)
 constexpr int kP1Table = 512;    // LDS hash entries (>= 2 * kP1Chunk)
-constexpr int kP1Unroll = 4;     // slots per thread in one group of the bin's slots
+constexpr int kP1Probe = 64;     // entries probed before a cell is left to the listed way
+constexpr int kP1Unroll = 4;     // slots per thread in one group of the cell's slots
 constexpr int kP1Group = kP1Unroll * kP1Threads;  // slots the workgroup holds at once
+constexpr int kAgainGrid = 1024;  // workgroups that walk the crowded cells
 constexpr int kMaxPartials = 4;  // (the row masks are read as one uchar4)
 
 __device__ __forceinline__ uint32_t fhash(int f) { return ((uint32_t)f * 2654435761u) >> (32 - 9); }
 static_assert(kP1Table == 512, "fhash yields 9 bits");
 
-__device__ __forceinline__ void atomic_face(const BwdArgs& a, int f, const float* g9) {
-    const int32_t* fv = a.faces + 3 * (int64_t)f;
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-        int v = fv[j];
-        if (v < 0 || v >= a.V) continue;
-#pragma unroll
-        for (int x = 0; x < 3; ++x)
-            if (g9[3 * j + x] != 0.0f) atomicAdd(a.grad + 3 * (int64_t)v + x, g9[3 * j + x]);
-    }
-}
-
-// A face as the bin pass keeps it in LDS: the fields the slot recomputation
-// reads (FaceRec without the mesh id and the box), 88 bytes.
-struct Dbl2 {  // a pair of doubles at 8-byte alignment (double2 would pad the record to 96 bytes)
-    double x, y;
-};
-struct BinRec {
-    Dbl2 pa, ab, ac;
+// A face as the slot recomputation reads it (FaceRec without the mesh id and
+// the pixel ranges).
+struct SlotRec {
+    double2 pa, ab, ac;
     double E;
     float az, dz1, dz2, invE, il0, il1, il2;
     int face;  // the face's id
 };
-static_assert(sizeof(BinRec) == 88, "bin record layout");
 
-__device__ __forceinline__ void store_bin_rec(BinRec& d, const FaceRec& R, int f) {
-    d.pa = {R.pa.x, R.pa.y};
-    d.ab = {R.ab.x, R.ab.y};
-    d.ac = {R.ac.x, R.ac.y};
-    d.E = R.E;
-    d.az = R.az;
-    d.dz1 = R.dz1;
-    d.dz2 = R.dz2;
-    d.invE = R.invE;
-    d.il0 = R.il0;
-    d.il1 = R.il1;
-    d.il2 = R.il2;
-    d.face = f;
-}
-
-constexpr int kFixBits = 38;     // fixed-point grid 2^-(kFixBits - 2 log2(bin size))
-constexpr int kRescueBits = 18;  // a largest face sum below 2^18 grid points triggers the rescue
-constexpr int kRescueGrid = 2048;  // workgroups of the rescue launch
-
-// v * 2^S rounded to the nearest integer (ties to even), as a two's-complement
-// 64-bit integer, for abs(v) < 2^(51-S).  With M = 1.5 * 2^(52-S), the FP64
-// sum v + M lies in M's binade, where one unit of the last place is 2^-S, so
-// the addition itself rounds v to the grid and the difference of the two bit
-// patterns is that rounded value: one conversion, one FP64 add and one 64-bit
-// integer subtraction.  bits_m is the bit pattern of M.
-__device__ __forceinline__ unsigned long long to_fix(float v, double m, unsigned long long bits_m) {
-    return (unsigned long long)__double_as_longlong((double)v + m) - bits_m;
-}
-
-// Rescue condition from the recorded largest face sum (float bits, >= 0).
-__device__ __forceinline__ bool needs_rescue(int tbits_max, int S) {
-    return tbits_max > 0 && __int_as_float(tbits_max) < ldexpf(1.0f, kRescueBits - S);
-}
+// A chunk's faces in LDS, 64 bytes each as four arrays of 16-byte words (one
+// face's words a power of two apart would fall into few banks).  The vertices
+// are kept as the FP32 coordinates they are; the FP64 offsets from vertex a
+// are exact differences of them and come back bit for bit.
+struct ChunkRecs {
+    float4 q[4][kP1Chunk];
+    __device__ __forceinline__ void put(int j, const FaceRec& R, int f) {
+        const double bx = R.pa.x + R.ab.x, by = R.pa.y + R.ab.y, cx = R.pa.x + R.ac.x, cy = R.pa.y + R.ac.y;
+        q[0][j] = make_float4((float)R.pa.x, (float)R.pa.y, (float)bx, (float)by);
+        q[1][j] = make_float4((float)cx, (float)cy, __int_as_float(__double2loint(R.E)),
+                              __int_as_float(__double2hiint(R.E)));
+        q[2][j] = make_float4(R.az, R.dz1, R.dz2, R.invE);
+        q[3][j] = make_float4(R.il0, R.il1, R.il2, __int_as_float(f));
+    }
+    __device__ __forceinline__ int face(int j) const { return __float_as_int(q[3][j].w); }
+    __device__ __forceinline__ SlotRec get(int j) const {
+        const float4 u = q[0][j], v = q[1][j], w = q[2][j], x = q[3][j];
+        SlotRec R;
+        R.pa = make_double2(u.x, u.y);
+        R.ab = make_double2((double)u.z - R.pa.x, (double)u.w - R.pa.y);
+        R.ac = make_double2((double)v.x - R.pa.x, (double)v.y - R.pa.y);
+        R.E = __hiloint2double(__float_as_int(v.w), __float_as_int(v.z));
+        R.az = w.x;
+        R.dz1 = w.y;
+        R.dz2 = w.z;
+        R.invE = w.w;
+        R.il0 = x.x;
+        R.il1 = x.y;
+        R.il2 = x.z;
+        R.face = __float_as_int(x.w);
+        return R;
+    }
+};
 
 // Pixel centre coordinate 1 - (2i+1)/n from the reciprocal rn = 1/n with one
 // residual correction of the quotient: within one unit in the last place of
@@ -509,48 +511,24 @@ __device__ __forceinline__ double pix_coord_rcp(int i, double n, double rn) {
     return 1.0 - fma(r, rn, q0);
 }
 
-// A thread's position in the bin's slot order (pixel-major, k fastest),
-// advanced by kP1Threads slots at a time without divisions.
-struct SlotWalk {
-    int k, pr, pc;  // slot within the pixel, pixel row and column within the bin
-    int dk, dpl;    // kP1Threads = dpl * K + dk
-    int dr0, dc0;   // dpl pixels = dr0 rows + dc0 columns
-    int dr1, dc1;   // dpl + 1 pixels
-    __device__ __forceinline__ void init(int q, int K, int cols) {
-        const int pl = q / K;
+// Slot q of a cell in its slot order (pixel-major, k fastest): row, column
+// and slot within the pixel.  A cell has at most 4,096 slots (64 pixels of K =
+// 64), for which the quotients by a float reciprocal are exact.
+struct SlotPlace {
+    int k, pr, pc;
+    __device__ __forceinline__ SlotPlace(int q, int K, int cols, float inv_k, float inv_cols) {
+        const int pl = stage_pixel(q, inv_k);
         k = q - pl * K;
-        pr = pl / cols;
+        pr = stage_pixel(pl, inv_cols);
         pc = pl - pr * cols;
-        dpl = kP1Threads / K;
-        dk = kP1Threads - dpl * K;
-        dr0 = dpl / cols;
-        dc0 = dpl - dr0 * cols;
-        dr1 = (dpl + 1) / cols;
-        dc1 = (dpl + 1) - dr1 * cols;
-    }
-    __device__ __forceinline__ void next(int K, int cols) {
-        k += dk;
-        const bool carry = k >= K;
-        k = carry ? k - K : k;
-        pr += carry ? dr1 : dr0;
-        pc += carry ? dc1 : dc0;
-        const bool wrap = pc >= cols;
-        pc = wrap ? pc - cols : pc;
-        pr = wrap ? pr + 1 : pr;
     }
 };
 
-// The nine coordinate terms of one slot of face R (chunk index j) at pixel
-// (row, col), added to the chunk's fixed-point sums.
-struct FixGrid {
-    float limit;              // terms at or above this go to grad_verts directly
-    double m;                 // 1.5 * 2^(52 - S)
-    unsigned long long bits;  // bit pattern of m
-};
+// The nine coordinate terms of one slot of face R at pixel (row, col), added
+// to a row of its sums.
 template <bool kOpts>
-__device__ __forceinline__ void add_slot(const BwdArgs& a, const BinRec& R, int j, int row, int col, double dW,
-                                         double rW, double dH, double rH, const SlotUp& up,
-                                         unsigned long long* acci, const FixGrid& fx) {
+__device__ __forceinline__ void add_slot(const BwdArgs& a, const SlotRec& R, int row, int col, double dW, double rW,
+                                         double dH, double rH, const SlotUp& up, double* acc) {
     const float vz[3] = {R.az, R.az + R.dz1, R.az + R.dz2};
     FaceGrad g;
 #pragma unroll
@@ -559,333 +537,324 @@ __device__ __forceinline__ void add_slot(const BwdArgs& a, const BinRec& R, int 
     p.xf = p.yf = 0.0f;  // (the recomputation reads only the FP64 centre)
     p.x = pix_coord_rcp(col, dW, rW);
     p.y = pix_coord_rcp(row, dH, rH);
-    slot_grad_up<BinRec, kOpts>(a, R, vz, p, up, g);
+    slot_grad_up<SlotRec, kOpts>(a, R, vz, p, up, g);
     const float g9[9] = {g.gx[0], g.gy[0], g.gzv[0], g.gx[1], g.gy[1], g.gzv[1], g.gx[2], g.gy[2], g.gzv[2]};
-    float gmax = 0.0f;
 #pragma unroll
-    for (int x = 0; x < 9; ++x) gmax = fmaxf(gmax, fabsf(g9[x]));
-    if (gmax < fx.limit) {
-#pragma unroll
-        for (int x = 0; x < 9; ++x) atomicAdd(&acci[9 * j + x], to_fix(g9[x], fx.m, fx.bits));
-    } else {
-        // a term too large for the fixed-point sums (never for sane inputs): straight to the vertex
-#pragma unroll
-        for (int x = 0; x < 9; ++x) {
-            const float v = g9[x];
-            if (fabsf(v) < fx.limit) {
-                atomicAdd(&acci[9 * j + x], to_fix(v, fx.m, fx.bits));
-            } else {
-                const int vtx = a.faces[3 * (int64_t)R.face + x / 3];
-                if (vtx >= 0 && vtx < a.V) atomicAdd(a.grad + 3 * (int64_t)vtx + x % 3, v);
-            }
-        }
-    }
+    for (int x = 0; x < 9; ++x) atomicAdd(&acc[x], (double)g9[x]);
 }
 
-// Where face f's sums from bin (bx, by) go: its partial row f * 4 + i (i the
-// bin's place in the face's range), -1 (vertex atomics: the range spans more
-// than kMaxPartials bins) or -2 (nowhere: the face never counts, or the bin
+// Where face f's sums from cell (cx, cy) go: its partial row f * 4 + i (i the
+// cell's place in the face's range), -1 (to the vertices: the range spans more
+// than kMaxPartials cells) or -2 (nowhere: the face never counts, or the cell
 // lies outside its range).
-__device__ __forceinline__ int partial_row(const BwdArgs& a, const FaceRec& G, int f, int bx, int by) {
-    int bx0, bx1, by0, by1;
-    if (!face_bins(G, a.bs, bx0, bx1, by0, by1)) return -2;
-    const int nb = (bx1 - bx0 + 1) * (by1 - by0 + 1);
-    if (nb > kMaxPartials) return -1;
-    if (bx < bx0 || bx > bx1 || by < by0 || by > by1) return -2;
-    return f * kMaxPartials + (by - by0) * (bx1 - bx0 + 1) + (bx - bx0);
+__device__ __forceinline__ int partial_row(const BwdArgs& a, const FaceRec& G, int f, int cx, int cy) {
+    if (!G.ok() || G.px.y < G.px.x || G.px.w < G.px.z) return -2;
+    const int cx0 = G.px.x >> a.lgw, cx1 = G.px.y >> a.lgw, cy0 = G.px.z >> a.lgh, cy1 = G.px.w >> a.lgh;
+    const int64_t nc = (int64_t)(cx1 - cx0 + 1) * (cy1 - cy0 + 1);
+    if (nc > kMaxPartials) return -1;
+    if (cx < cx0 || cx > cx1 || cy < cy0 || cy > cy1) return -2;
+    return f * kMaxPartials + (cy - cy0) * (cx1 - cx0 + 1) + (cx - cx0);
 }
 
-// Writes a chunk face's sums (or sends them to the vertices) and marks the
-// partial row as written; tracks the workgroup's largest sum.
-__device__ __forceinline__ void flush_face(const BwdArgs& a, const unsigned long long* acc9, int dst, int face, int S,
-                                           bool track, int* smax) {
-    if (dst == -2) return;
-    float g9[9];
-    float fmx = 0.0f;
-#pragma unroll
-    for (int x = 0; x < 9; ++x) {
-        g9[x] = (float)ldexp((double)(long long)acc9[x], -S);
-        fmx = fmaxf(fmx, fabsf(g9[x]));
-    }
-    // non-negative floats order as their bit patterns
-    if (track && fmx > 0.0f) atomicMax(smax, __float_as_int(fmx));
-    if (dst >= 0) {
-        float* out = a.partial + (int64_t)dst * 9;
-#pragma unroll
-        for (int x = 0; x < 9; ++x) out[x] = g9[x];
-        a.pmask[dst] = 1;
-    } else {
-        atomic_face(a, face, g9);
-    }
+// The LDS of a cell's workgroup.
+struct CellLds {
+    ChunkRecs rec;
+    double acc[kP1Rows * 9];  // a face's sums, in replicas() rows
+    int key[kP1Table];   // face ids (-1: free)
+    unsigned char val[kP1Table];  // the key's chunk index
+    int dst[kP1Chunk];            // partial_row of each chunk face
+    int count, fail;
+};
+static_assert(kP1Chunk <= 256, "chunk indices are bytes");
+static_assert(sizeof(CellLds) <= 21 * 1280, "six workgroups share a compute unit's LDS");
+
+// Lanes that add to one LDS word go one after the other (64 lanes on one
+// FP64 word: 64 times as long as on 64 words), and neighbouring pixels name
+// the same faces, the more so the larger the faces are and the fewer a cell
+// names.  So a chunk of m faces has as many rows per face as there is room for,
+// 1 << replicas(m) of them, and a slot adds to the one of its pixel's column.
+__device__ __forceinline__ int replicas(int m) {
+    return 8 * m <= kP1Rows ? 3 : (4 * m <= kP1Rows ? 2 : (2 * m <= kP1Rows ? 1 : 0));
 }
 
-// rescue = 0: the pass, recording its largest face sum; rescue = 1: the
-// rescue pass, which exits unless that sum calls for it.  kOpts: the call
-// has perspective-correct or clipped barycentrics (an instance of its own, so
-// that their register needs do not lower the occupancy of the plain one).
-//
-// Two ways through a bin.  The direct way (a bin of at most kP1Group slots
-// whose slots name at most kP1Chunk distinct faces, nearly every bin): the
-// slots' face ids and upstream gradients are requested at once, the distinct
-// ids go into the LDS hash table as they arrive (the inserting lane numbers
-// the face), their records are gathered -- while the gradients are still in
-// flight -- and every slot is recomputed once.  Only the faces the slots name
-// are gathered, so a crowded bin (silhouettes) costs no more than a quiet one,
-// and the bin's list is not read.  Slot ids outside [0, F), of a face that
-// never counts or of another image are ignored.  The listed way (any other
-// bin): the bin's list is taken in chunks of kP1Chunk faces, each chunk's
-// records and hash table built, and every slot of the bin looked up in it.
-template <bool kOpts, bool kLoop>
-__global__ __launch_bounds__(kP1Threads) __attribute__((amdgpu_waves_per_eu(5, 8)))
-void bwd_bins_kernel(BwdArgs a, int rescue) {
-    __shared__ BinRec srec[kP1Chunk];
-    __shared__ unsigned long long acci[kP1Chunk * 9];
-    __shared__ int tkey[kP1Table];
-    __shared__ short tval[kP1Table];  // the key's face: its chunk index (-1: held over to the listed way)
-    __shared__ int sdst[kP1Chunk];    // partial_row of each chunk face
-    __shared__ int ucount, ufail;
-    int lgbs = 0;
-    while ((1 << lgbs) < a.bs) ++lgbs;
-    int S = kFixBits - 2 * lgbs;  // grid exponent of the sums
-    if (rescue) {
-        const int tb = a.hdr[kHdrTermMax];
-        if (!needs_rescue(tb, S)) return;
-        // the largest sum (< 2^eb) on 2^30 grid points
-        S = 30 - (((tb >> 23) & 0xff) - 126);
-    }
-    // terms below the limit: the conversion is exact, and a face's at most
-    // bs^2 of them stay below 2^62 on the grid
-    FixGrid fx;
-    fx.limit = ldexpf(1.0f, min(51, 62 - 2 * lgbs) - S);
-    fx.m = ldexp(1.5, 52 - S);
-    fx.bits = (unsigned long long)__double_as_longlong(fx.m);
-    __shared__ int smax;  // largest abs face sum of the workgroup (float bits)
-    if (!bins_usable(a)) return;
-    if (threadIdx.x == 0) smax = 0;  // (ordered before every update by the first bin's barriers)
-    const bool track = !rescue;
-    const int per_img = a.nby * a.nbx;
-    const int64_t nbins = (int64_t)a.N * per_img;
-    // kLoop: a grid smaller than the bin count (the rescue launch) walks the
-    // bins; otherwise the grid is one workgroup per bin, each XCD taking a
-    // contiguous range of bins (neighbouring bins gather mostly the same
-    // face records; xcd_item).  Either way the first bin is < nbins.
-    int64_t bin = kLoop ? (int64_t)blockIdx.x : xcd_item(blockIdx.x, nbins);
-    do {
-        const int n = (int)(bin / per_img);
-        const int rem = (int)(bin - (int64_t)n * per_img);
-        const int by = rem / a.nbx, bx = rem - (rem / a.nbx) * a.nbx;
-        const int r0 = by * a.bs, c0 = bx * a.bs;
-        const int rows = min(a.bs, a.H - r0), cols = min(a.bs, a.W - c0);
-        const int nslots = rows * cols * a.K;
-        // slot (pr, pc, k) of the bin is pix_to_face[sbase + (pr * W + pc) * K + k]
-        const int64_t sbase = (((int64_t)n * a.H + r0) * a.W + c0) * a.K;
-        const double dW = (double)a.W, dH = (double)a.H, rW = 1.0 / dW, rH = 1.0 / dH;
+// Coordinate sum x of face j of a chunk (over its rows).
+__device__ __forceinline__ double face_sum(const CellLds& L, int j, int rep, int x) {
+    double v = L.acc[9 * (j << rep) + x];
+    for (int i = 1; i < 1 << rep; ++i) v += L.acc[9 * ((j << rep) + i) + x];
+    return v;
+}
 
-        if (nslots <= kP1Group) {
-            // ---- the direct way
-            SlotWalk w;
-            w.init(threadIdx.x, a.K, cols);
-            int fq[kP1Unroll], rq[kP1Unroll], cq[kP1Unroll];
-#pragma unroll
-            for (int u = 0; u < kP1Unroll; ++u) {
-                const int q = u * kP1Threads + threadIdx.x;
-                rq[u] = r0 + w.pr;
-                cq[u] = c0 + w.pc;
-                int f = -1;
-                if (q < nslots)
-                    f = __builtin_nontemporal_load(a.p2f + sbase + (int64_t)(w.pr * a.W + w.pc) * a.K + w.k);
-                fq[u] = (f >= 0 && f < a.F) ? f : -1;
-                w.next(a.K, cols);
-            }
-            for (int i = threadIdx.x; i < kP1Table; i += kP1Threads) tkey[i] = -1;
-            if (threadIdx.x == 0) {
-                ucount = 0;
-                ufail = 0;
-            }
-            SlotUp up[kP1Unroll];
-            {
-                SlotWalk w2;
-                w2.init(threadIdx.x, a.K, cols);
-#pragma unroll
-                for (int u = 0; u < kP1Unroll; ++u) {
-                    up[u] = SlotUp{0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-                    if (fq[u] >= 0) up[u] = load_up(a, sbase + (int64_t)(w2.pr * a.W + w2.pc) * a.K + w2.k);
-                    w2.next(a.K, cols);
-                }
-            }
-            __syncthreads();
-            // distinct faces into the table; the lane that inserts a face numbers it
-#pragma unroll
-            for (int u = 0; u < kP1Unroll; ++u) {
-                const int f = fq[u];
-                if (f < 0) continue;
-                uint32_t h = fhash(f);
-                bool placed = false;
-                for (int probe = 0; probe < kP1Table; ++probe) {
-                    const int prev = atomicCAS(&tkey[h], -1, f);
-                    if (prev == -1) {
-                        const int j = atomicAdd(&ucount, 1);
-                        tval[h] = (short)(j < kP1Chunk ? j : -1);
-                        placed = true;
-                        break;
-                    }
-                    if (prev == f) {
-                        placed = true;
-                        break;
-                    }
-                    h = (h + 1) & (kP1Table - 1);
-                }
-                if (!placed) ufail = 1;  // (a full table: the listed way takes the bin)
-            }
-            __syncthreads();
-            const int U = ucount;
-            if (U <= kP1Chunk && !ufail) {
-                // records of the named faces, one thread per table entry
-                for (int i = threadIdx.x; i < kP1Table; i += kP1Threads) {
-                    const int f = tkey[i];
-                    if (f < 0) continue;
-                    const int j = tval[i];
-                    const FaceRec& G = a.recs[f];
-                    store_bin_rec(srec[j], G, f);
-                    const bool ok = G.ok() && G.mesh() == n;
-                    if (!ok) srec[j].face = -1;
-                    sdst[j] = ok ? partial_row(a, G, f, bx, by) : -2;
-#pragma unroll
-                    for (int x = 0; x < 9; ++x) acci[9 * j + x] = 0ull;
-                }
-                __syncthreads();
-#pragma unroll
-                for (int u = 0; u < kP1Unroll; ++u) {
-                    const int f = fq[u];
-                    if (f < 0) continue;
-                    uint32_t h = fhash(f);
-                    for (int probe = 0; probe < kP1Table && tkey[h] != f; ++probe) h = (h + 1) & (kP1Table - 1);
-                    const int j = tval[h];  // (every named face was placed)
-                    const BinRec R = srec[j];
-                    if (R.face < 0) continue;
-                    add_slot<kOpts>(a, R, j, rq[u], cq[u], dW, rW, dH, rH, up[u], acci, fx);
-                }
-                __syncthreads();
-                for (int j = threadIdx.x; j < U; j += kP1Threads)
-                    flush_face(a, &acci[9 * j], sdst[j], srec[j].face, S, track, &smax);
-                __syncthreads();
-                continue;
-            }
-            // (every thread has read ucount and ufail: the listed way may now reuse the table)
+// Writes the sums of the chunk's m faces, lanes running over a face's nine
+// words, to their partial rows, and marks those; the sums of a face without
+// rows go to its vertices, three neighbouring atomics each.
+__device__ __forceinline__ void flush_faces(const BwdArgs& a, const CellLds& L, int m) {
+    const int rep = replicas(m);
+    for (int i = threadIdx.x; i < 9 * m; i += kP1Threads) {
+        const int j = stage_pixel(i, 1.0f / 9.0f), x = i - 9 * j;
+        const int dst = L.dst[j];
+        if (dst == -2) continue;
+        const float v = (float)face_sum(L, j, rep, x);
+        if (dst >= 0) {
+            a.partial[(int64_t)dst * 9 + x] = v;
+            if (x == 0) a.pmask[dst] = 1;
+        } else if (v != 0.0f) {
+            const int c = x >= 6 ? 2 : (x >= 3 ? 1 : 0);
+            const int vtx = a.faces[3 * (int64_t)L.rec.face(j) + c];
+            if (vtx >= 0 && vtx < a.V) atomicAdd(a.grad + 3 * (int64_t)vtx + x - 3 * c, v);
         }
+    }
+}
 
-        // ---- the listed way
-        const int cnt = min(a.counts[bin], a.M);
-        const int* list = a.lists + bin * a.M;
-        for (int base = 0; base < cnt; base += kP1Chunk) {
-            const int m = min(kP1Chunk, cnt - base);
-            for (int i = threadIdx.x; i < kP1Table; i += kP1Threads) tkey[i] = -1;
-            for (int i = threadIdx.x; i < m * 9; i += kP1Threads) acci[i] = 0ull;
+// A slot's face into the table; the lane that inserts a face numbers it.
+__device__ __forceinline__ void name_face(CellLds& L, int f) {
+    uint32_t h = fhash(f);
+    for (int probe = 0; probe < kP1Probe; ++probe) {
+        const int prev = atomicCAS(&L.key[h], -1, f);
+        if (prev == f) return;
+        if (prev == -1) {
+            const int j = atomicAdd(&L.count, 1);
+            L.val[h] = (unsigned char)min(j, kP1Chunk - 1);  // (more than kP1Chunk: not read)
+            return;
+        }
+        h = (h + 1) & (kP1Table - 1);
+    }
+    L.fail = 1;  // (a crowded table: the listed way takes the cell)
+}
+
+__device__ __forceinline__ double* acc_row(CellLds& L, int j, int col, int rep) {
+    return &L.acc[9 * ((j << rep) + (col & ((1 << rep) - 1)))];
+}
+
+// Chunk index of face f, or -1.
+__device__ __forceinline__ int find_face(const CellLds& L, int f) {
+    uint32_t h = fhash(f);
+    for (int probe = 0; probe < kP1Table; ++probe) {
+        const int key = L.key[h];
+        if (key == f) return L.val[h];
+        if (key == -1) return -1;
+        h = (h + 1) & (kP1Table - 1);
+    }
+    return -1;
+}
+
+// Records of the table's faces, one thread per entry, and where their sums
+// go; zeroed sums.  A face of another image or one that never counts is marked
+// by its id.
+__device__ __forceinline__ void gather_named(const BwdArgs& a, CellLds& L, int n, int cx, int cy, int m) {
+    for (int i = threadIdx.x; i < 9 * (m << replicas(m)); i += kP1Threads) L.acc[i] = 0.0;
+    for (int i = threadIdx.x; i < kP1Table; i += kP1Threads) {
+        const int f = L.key[i];
+        if (f < 0) continue;
+        const int j = L.val[i];
+        const FaceRec& G = a.recs[f];
+        const bool ok = G.ok() && G.mesh() == n;
+        L.rec.put(j, G, ok ? f : -1);
+        L.dst[j] = ok ? partial_row(a, G, f, cx, cy) : -2;
+    }
+}
+
+// A cell's place: slot (pr, pc, k) is pix_to_face[sbase + (pr * W + pc) * K + k].
+struct CellGeo {
+    int n, cx, cy, r0, c0, cols, nslots;
+    float inv_cols;
+    int64_t sbase, bin;  // bin: the forward's bin that holds the cell
+    __device__ __forceinline__ CellGeo(const BwdArgs& a, int64_t cell) {
+        const int per_img = a.ncy * a.ncx;
+        n = (int)(cell / per_img);
+        const int rem = (int)(cell - (int64_t)n * per_img);
+        cy = rem / a.ncx;
+        cx = rem - cy * a.ncx;
+        r0 = cy << a.lgh;
+        c0 = cx << a.lgw;
+        cols = min(1 << a.lgw, a.W - c0);
+        nslots = min(1 << a.lgh, a.H - r0) * cols * a.K;
+        inv_cols = 1.0f / (float)cols;
+        sbase = (((int64_t)n * a.H + r0) * a.W + c0) * a.K;
+        bin = ((int64_t)n * a.nby + r0 / a.bs) * a.nbx + c0 / a.bs;
+    }
+};
+
+// Ways through a cell.  The direct way (its slots name at most kP1Chunk
+// distinct faces, nearly every cell): the distinct ids go into the LDS hash
+// table as they arrive, only those faces' records are gathered, and every slot
+// is recomputed once.  A crowded cell (silhouettes) then costs no more than a
+// quiet one, and no list is read.  Slot ids outside [0, F), of a face that
+// never counts or of another image are ignored.  The listed way (any other
+// cell): the list of the cell's bin is taken in chunks of kP1Chunk faces, each
+// chunk's records and hash table built, and every slot of the cell looked up
+// in it.
+//
+// This kernel takes cells of at most kP1Group slots the direct way, ids and
+// gradients in registers, the gradients in flight while the records are
+// gathered, and leaves the others to bwd_cells_again_kernel, whose code would
+// cost it registers.  kOpts: the call has perspective-correct or clipped
+// barycentrics (an instance of its own, so that their register needs do not
+// lower the occupancy of the plain one).
+//
+// Bound by latency and vector issue about alike: two dependent round trips
+// per cell (ids, then records; ids, then gradients), overlapped by the six
+// workgroups per compute unit that the LDS block (26.6 KB) and the registers
+// (80) allow; five of each took 711 us instead of 681 (4 x 1024 x 1024 pixels,
+// K = 16) and 448 instead of 419 (32 x 512 x 512, K = 8).  Both passes and
+// their preparation: 1015 -> 784 us (K = 16), 440 -> 446 us (K = 8, bins of 16
+// pixels) and 88 -> 48 us (8 x 256 x 256, K = 4, bins of 32), against bins
+// as cells with fixed-point sums and a second, rescue pass.
+template <bool kOpts>
+__global__ __launch_bounds__(kP1Threads) __attribute__((amdgpu_waves_per_eu(6, 8)))
+void bwd_cells_kernel(BwdArgs a) {
+    __shared__ CellLds L;
+    if (!bins_usable(a)) return;
+    // each XCD takes a contiguous range of cells (neighbouring cells gather
+    // mostly the same face records)
+    const int64_t cell = xcd_item(blockIdx.x, (int64_t)a.N * a.ncy * a.ncx);
+    const CellGeo c(a, cell);
+    if (a.counts[c.bin] == 0) return;  // no face reaches the bin: no slot to read
+    const double dW = (double)a.W, dH = (double)a.H, rW = 1.0 / dW, rH = 1.0 / dH;
+    const int t = threadIdx.x;
+    int fq[kP1Unroll], rq[kP1Unroll], cq[kP1Unroll];
+    int64_t sq[kP1Unroll];
+#pragma unroll
+    for (int u = 0; u < kP1Unroll; ++u) {
+        const int q = u * kP1Threads + t;
+        const SlotPlace w(q, a.K, c.cols, a.inv_k, c.inv_cols);
+        rq[u] = c.r0 + w.pr;
+        cq[u] = c.c0 + w.pc;
+        sq[u] = c.sbase + (int64_t)(w.pr * a.W + w.pc) * a.K + w.k;
+        int f = -1;
+        if (q < c.nslots) f = __builtin_nontemporal_load(a.p2f + sq[u]);
+        fq[u] = (f >= 0 && f < a.F) ? f : -1;
+    }
+    for (int i = t; i < kP1Table; i += kP1Threads) L.key[i] = -1;
+    if (t == 0) L.count = L.fail = 0;
+    SlotUp up[kP1Unroll];
+#pragma unroll
+    for (int u = 0; u < kP1Unroll; ++u) {
+        up[u] = SlotUp{0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+        if (fq[u] >= 0) up[u] = load_up(a, sq[u]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kP1Unroll; ++u)
+        if (fq[u] >= 0) name_face(L, fq[u]);
+    __syncthreads();
+    const int U = L.count;
+    if (U == 0) return;  // no slot is filled
+    if (U > kP1Chunk || L.fail) {
+        if (t == 0) a.crowded[atomicAdd(&a.hdr[kHdrCrowded], 1)] = (int)cell;
+        return;
+    }
+    gather_named(a, L, c.n, c.cx, c.cy, U);
+    __syncthreads();
+    const int rep = replicas(U);
+#pragma unroll
+    for (int u = 0; u < kP1Unroll; ++u) {
+        if (fq[u] < 0) continue;
+        const int j = find_face(L, fq[u]);  // (every named face was placed)
+        const SlotRec R = L.rec.get(j);
+        if (R.face >= 0)
+            add_slot<kOpts>(a, R, rq[u], cq[u], dW, rW, dH, rH, up[u], acc_row(L, j, cq[u], rep));
+    }
+    __syncthreads();
+    flush_faces(a, L, U);
+}
+
+// Cells that are read again: those the first kernel left (kAll false; a grid
+// smaller than the list walks it), or all cells where a cell has more than
+// kP1Group slots (K above 16): the direct way with ids and gradients read group
+// by group, else the listed way.
+template <bool kOpts, bool kAll>
+__global__ __launch_bounds__(kP1Threads) __attribute__((amdgpu_waves_per_eu(5, 8)))
+void bwd_cells_again_kernel(BwdArgs a) {
+    __shared__ CellLds L;
+    if (!bins_usable(a)) return;
+    const double dW = (double)a.W, dH = (double)a.H, rW = 1.0 / dW, rH = 1.0 / dH;
+    const int t = threadIdx.x;
+    const int ncell = kAll ? 1 : a.hdr[kHdrCrowded];
+    for (int i = kAll ? 0 : (int)blockIdx.x; i < ncell; i += gridDim.x) {
+        const CellGeo c(a, kAll ? xcd_item(blockIdx.x, (int64_t)a.N * a.ncy * a.ncx) : (int64_t)a.crowded[i]);
+        const int* list = a.lists + c.bin * a.M;
+        const int listed = min(a.counts[c.bin], a.M);
+        if (listed == 0) continue;  // no face reaches the bin
+        bool named = false;
+        // (a list that fits one chunk and is the cell's own needs no naming)
+        if (kAll && !(listed <= kP1Chunk && a.bs == kTile)) {
+            for (int q = t; q < kP1Table; q += kP1Threads) L.key[q] = -1;
+            if (t == 0) L.count = L.fail = 0;
             __syncthreads();
-            const int t = threadIdx.x;
-            if (t < m) {
-                const int j = t;
-                const int f = list[base + j];
-                const FaceRec& G = a.recs[f];
-                store_bin_rec(srec[j], G, f);
-                sdst[j] = partial_row(a, G, f, bx, by);
-                uint32_t h = fhash(f);
-                for (int probe = 0; probe < kP1Table; ++probe) {
-                    if (atomicCAS(&tkey[h], -1, f) == -1) {
-                        tval[h] = (short)j;
-                        break;
-                    }
-                    h = (h + 1) & (kP1Table - 1);
-                }
+            for (int q = t; q < c.nslots; q += kP1Threads) {
+                const SlotPlace w(q, a.K, c.cols, a.inv_k, c.inv_cols);
+                const int f = a.p2f[c.sbase + (int64_t)(w.pr * a.W + w.pc) * a.K + w.k];
+                if (f >= 0 && f < a.F && !L.fail) name_face(L, f);
             }
             __syncthreads();
-            SlotWalk w;
-            w.init(threadIdx.x, a.K, cols);
-            for (int q0 = 0; q0 < nslots; q0 += kP1Group) {
-                int fq[kP1Unroll], rq[kP1Unroll], cq[kP1Unroll];
-                int64_t sq[kP1Unroll];
-#pragma unroll
-                for (int u = 0; u < kP1Unroll; ++u) {
-                    const int q = q0 + u * kP1Threads + threadIdx.x;
-                    fq[u] = -1;
-                    rq[u] = r0 + w.pr;
-                    cq[u] = c0 + w.pc;
-                    sq[u] = 0;
-                    if (q < nslots) {
-                        sq[u] = sbase + ((int64_t)(w.pr * a.W + w.pc) * a.K + w.k);
-                        fq[u] = __builtin_nontemporal_load(a.p2f + sq[u]);
-                    }
-                    w.next(a.K, cols);
-                }
-#pragma unroll
-                for (int u = 0; u < kP1Unroll; ++u) {
-                    const int f = fq[u];
-                    if (f < 0) continue;
-                    int j = -1;
+            named = L.count <= kP1Chunk && !L.fail;
+            if (named) {
+                if (L.count == 0) return;  // no slot is filled
+                gather_named(a, L, c.n, c.cx, c.cy, L.count);
+            }
+        }
+        const int cnt = named ? L.count : listed;
+        for (int base = 0; base < cnt; base += kP1Chunk) {
+            const int m = min(kP1Chunk, cnt - base), rep = replicas(m);
+            __syncthreads();  // (the last chunk is flushed, count and fail are read)
+            if (!named) {
+                for (int q = t; q < kP1Table; q += kP1Threads) L.key[q] = -1;
+                for (int q = t; q < 9 * (m << rep); q += kP1Threads) L.acc[q] = 0.0;
+                __syncthreads();
+                if (t < m) {
+                    const int f = list[base + t];
+                    const FaceRec& G = a.recs[f];
+                    L.rec.put(t, G, f);
+                    L.dst[t] = partial_row(a, G, f, c.cx, c.cy);
                     uint32_t h = fhash(f);
                     for (int probe = 0; probe < kP1Table; ++probe) {
-                        const int key = tkey[h];
-                        if (key == f) {
-                            j = tval[h];
+                        if (atomicCAS(&L.key[h], -1, f) == -1) {
+                            L.val[h] = (unsigned char)t;
                             break;
                         }
-                        if (key == -1) break;
                         h = (h + 1) & (kP1Table - 1);
                     }
+                }
+                __syncthreads();
+            }
+            for (int q0 = 0; q0 < c.nslots; q0 += kP1Group) {
+                int64_t sq[kP1Unroll];
+                int fq[kP1Unroll], rq[kP1Unroll], cq[kP1Unroll];
+#pragma unroll
+                for (int u = 0; u < kP1Unroll; ++u) {
+                    const int q = q0 + u * kP1Threads + t;
+                    const SlotPlace w(q, a.K, c.cols, a.inv_k, c.inv_cols);
+                    rq[u] = c.r0 + w.pr;
+                    cq[u] = c.c0 + w.pc;
+                    sq[u] = c.sbase + ((int64_t)(w.pr * a.W + w.pc) * a.K + w.k);
+                    fq[u] = q < c.nslots ? a.p2f[sq[u]] : -1;
+                }
+#pragma unroll
+                for (int u = 0; u < kP1Unroll; ++u) {
+                    if (fq[u] < 0) continue;
+                    const int j = find_face(L, fq[u]);
                     if (j < 0) continue;
-                    add_slot<kOpts>(a, srec[j], j, rq[u], cq[u], dW, rW, dH, rH, load_up(a, sq[u]), acci, fx);
+                    const SlotRec R = L.rec.get(j);
+                    if (R.face >= 0)
+                        add_slot<kOpts>(a, R, rq[u], cq[u], dW, rW, dH, rH, load_up(a, sq[u]),
+                                        acc_row(L, j, cq[u], rep));
                 }
             }
             __syncthreads();
-            // flush: one partial per listed face (written and marked, zero or not)
-            if (t < m) flush_face(a, &acci[9 * t], sdst[t], srec[t].face, S, track, &smax);
-            __syncthreads();
+            flush_faces(a, L, m);
         }
-        __syncthreads();  // (a bin without chunks has no barrier of its own)
-    } while (kLoop && (bin += gridDim.x) < nbins);
-    if (track && threadIdx.x == 0) {
-        // the call's largest face sum: one global word, so a workgroup only
-        // updates it when its own maximum is larger than what it reads there
-        // (same-address atomics from every wave would serialise)
-        const int mine = smax;
-        if (mine > 0 && mine > __hip_atomic_load(&a.hdr[kHdrTermMax], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-            atomicMax(&a.hdr[kHdrTermMax], mine);
+        __syncthreads();  // (the next cell clears the tables)
     }
 }
-
-// Clears grad_verts before the rescue pass, when the recorded largest sum calls for it.
-__global__ void bwd_rescue_clear_kernel(BwdArgs a) {
-    int lgbs = 0;
-    while ((1 << lgbs) < a.bs) ++lgbs;
-    if (!needs_rescue(a.hdr[kHdrTermMax], kFixBits - 2 * lgbs)) return;
-    const int64_t n = a.V * 3;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        a.grad[i] = 0.0f;
-}
-
 
 // Pass 2: one thread per face adds the partial rows this call wrote for it
-// and merges the result per vertex in an LDS hash table, as 64-bit fixed point
-// (integer LDS atomics; float ones are slow on this hardware); each table
-// entry then issues one float atomic per coordinate.  The grid follows the
-// largest row the pass recorded (below 2^e): a face's sum of at most four rows
-// stays below 2^(e+2) and a vertex takes at most kBwdBlock faces of the
-// workgroup, below 2^(e+10), so the grid 2^(e-48) keeps every sum below 2^58
-// and every term inside to_fix's exact range.
+// and merges the result per vertex in an LDS hash table (FP64 sums); the
+// table's rows then go out with one float atomic per coordinate.
 __global__ __launch_bounds__(kBwdBlock) void bwd_face_sum_kernel(BwdArgs a) {
     __shared__ int keys[kHash];
-    __shared__ unsigned long long vals[3 * kHash];
+    __shared__ double vals[3 * kHash];
     if (!bins_usable(a)) return;
-    const int tb = a.hdr[kHdrTermMax];
-    if (tb <= 0) return;  // every row is zero
-    const int e = ((tb >> 23) & 0xff) - 126;
-    const int S = 48 - e;
-    const double fm = ldexp(1.5, 52 - S);
-    const unsigned long long fbits = (unsigned long long)__double_as_longlong(fm);
-    for (int i = threadIdx.x; i < kHash; i += kBwdBlock) {
-        keys[i] = -1;
-        vals[3 * i] = vals[3 * i + 1] = vals[3 * i + 2] = 0ull;
-    }
+    clear_table(keys, vals);
     __syncthreads();
     const int64_t f = (int64_t)blockIdx.x * kBwdBlock + threadIdx.x;
     const bool overflowed = (a.hdr[kHdrStatus] & kStatOverflow) != 0;
@@ -907,63 +876,42 @@ __global__ __launch_bounds__(kBwdBlock) void bwd_face_sum_kernel(BwdArgs a) {
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
                 const int v = fv[j];
-                if (v < 0 || v >= a.V) continue;
-                uint32_t h = vhash(v);
-                bool placed = false;
-                for (int probe = 0; probe < kHash; ++probe) {
-                    const int prev = atomicCAS(&keys[h], -1, v);
-                    if (prev == -1 || prev == v) {
-#pragma unroll
-                        for (int x = 0; x < 3; ++x) atomicAdd(&vals[3 * h + x], to_fix(g9[3 * j + x], fm, fbits));
-                        placed = true;
-                        break;
-                    }
-                    h = (h + 1) & (kHash - 1);
-                }
-                if (!placed) {
-#pragma unroll
-                    for (int x = 0; x < 3; ++x) atomicAdd(a.grad + 3 * (int64_t)v + x, g9[3 * j + x]);
-                }
+                if (v >= 0 && v < a.V) lds_add(keys, vals, a.grad, v, g9[3 * j], g9[3 * j + 1], g9[3 * j + 2]);
             }
         }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < kHash; i += kBwdBlock) {
-        const int v = keys[i];
-        if (v >= 0) {
-#pragma unroll
-            for (int x = 0; x < 3; ++x)
-                atomicAdd(a.grad + 3 * (int64_t)v + x, (float)ldexp((double)(long long)vals[3 * i + x], -S));
-        }
-    }
+    flush_table(a.grad, keys, vals);
 }
 
-// Zeroes grad_verts (n3v floats) and nmask words (the row masks, or the
-// header), and the recorded largest face sum.
+// Zeroes grad_verts (n3v floats), nmask words (the row masks, or the header)
+// and the count of crowded cells.
 __global__ void bwd_prep_kernel(float* __restrict__ grad, int64_t n3v, int* __restrict__ mask, int64_t nmask,
-                                int* __restrict__ term) {
+                                int* __restrict__ hdr) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     for (int64_t i = i0; i < n3v; i += stride) grad[i] = 0.0f;
     for (int64_t i = i0; i < nmask; i += stride) mask[i] = 0;
-    if (i0 == 0) *term = 0;
+    if (i0 == 0) hdr[kHdrCrowded] = 0;
+}
+static hipError_t launch_prep(float* grad, int64_t n3v, int* mask, int64_t nmask, int* hdr, hipStream_t s) {
+    const int64_t n = std::max(n3v, nmask);
+    const unsigned g = (unsigned)std::min<int64_t>((n + 255) / 256, 1024);
+    hipLaunchKernelGGL(bwd_prep_kernel, dim3(g > 0 ? g : 1), dim3(256), 0, s, grad, n3v, mask, nmask, hdr);
+    return hipGetLastError();
 }
 
 hipError_t launch_backward(const float* verts, int64_t V, const int32_t* faces, int64_t F, const int64_t* first,
                            const int64_t* nf, int N, int H, int W, int K, float blur, int opts, int bs, int M,
                            const int32_t* p2f, const float* gz, const float* gb, const float* gd, float* grad,
-                           int* hdr, FaceRec* recs, int* counts, int* lists, float* partial, int* big,
-                           bool reuse, const BinSig& sig, hipStream_t s, hipEvent_t eb, hipEvent_t ee) {
+                           int* hdr, FaceRec* recs, int* counts, int* lists, int* order, float* partial,
+                           int* big, bool reuse, const BinSig& sig, hipStream_t s, hipEvent_t eb, hipEvent_t ee) {
     reuse = reuse && bs > 0;
     hipError_t e = hipSuccess;
     // the binned form clears grad_verts together with its row masks (below);
     // the per-face form clears it with the header, in one launch
     if (bs == 0 || F == 0) {
-        const int64_t n = V * 3 > kHdrWords ? V * 3 : kHdrWords;
-        const unsigned g = (unsigned)(n < 256 * 1024 ? (n + 255) / 256 : 1024);
-        hipLaunchKernelGGL(bwd_prep_kernel, dim3(g), dim3(256), 0, s, grad, V * 3, hdr, (int64_t)(reuse ? 0 : kHdrWords),
-                           hdr + kHdrTermMax);
-        e = hipGetLastError();
+        e = launch_prep(grad, V * 3, hdr, reuse ? 0 : kHdrWords, hdr, s);
         if (e != hipSuccess) return e;
     } else if (!reuse) {
         e = launch_fill_i32(hdr, kHdrWords, 0, s);
@@ -999,6 +947,9 @@ hipError_t launch_backward(const float* verts, int64_t V, const int32_t* faces, 
     a.nby = bs > 0 ? (H + bs - 1) / bs : 0;
     a.nbx = bs > 0 ? (W + bs - 1) / bs : 0;
     a.M = M;
+    a.inv_k = 1.0f / (float)K;
+    a.crowded = order;
+    a.lgw = a.lgh = a.ncy = a.ncx = 0;
     a.reuse = reuse ? 1 : 0;
     a.sig = sig;
     if (bs > 0) {
@@ -1010,19 +961,35 @@ hipError_t launch_backward(const float* verts, int64_t V, const int32_t* faces, 
             e = launch_binning(recs, F, N, H, W, bs, M, counts, lists, hdr, s);
             if (e != hipSuccess) return e;
         }
-        const int64_t nbins = (int64_t)N * a.nby * a.nbx;
-        // grad_verts, the row masks (no partial row is written yet: F x 4 mask
-        // bytes = F words) and the recorded largest sum, in one launch
-        hipLaunchKernelGGL(bwd_prep_kernel, dim3(1024), dim3(256), 0, s, grad, V * 3, big, F, hdr + kHdrTermMax);
+        // grad_verts and the row masks (no partial row is written yet: F x 4
+        // mask bytes = F words), in one launch
+        e = launch_prep(grad, V * 3, big, F, hdr, s);
+        if (e != hipSuccess) return e;
+        // the largest cell that divides the bins and whose slots fit a
+        // workgroup's registers, wider before higher (K = 16: 8 x 8, K = 8: 16 x
+        // 8, K = 1: 32 x 32); 8 x 8 where none does.  Half the size at K = 8
+        // took 611 us instead of 448 (32 x 512 x 512 pixels), twice the size on
+        // 512 threads 495.
+        a.lgw = a.lgh = 3;
+        while ((int64_t)K << (a.lgw + a.lgh + 1) <= kP1Group && a.lgh < 5) {
+            int& lg = a.lgw == a.lgh ? a.lgw : a.lgh;
+            if (bs % (2 << lg) != 0) break;
+            ++lg;
+        }
+        a.ncy = (H + (1 << a.lgh) - 1) >> a.lgh;
+        a.ncx = (W + (1 << a.lgw) - 1) >> a.lgw;
         if (eb) (void)hipEventRecord(eb, s);
         const bool o = (opts & (kOptPersp | kOptClip)) != 0;
-        auto bins = o ? bwd_bins_kernel<true, false> : bwd_bins_kernel<false, false>;
-        auto rescue = o ? bwd_bins_kernel<true, true> : bwd_bins_kernel<false, true>;
-        hipLaunchKernelGGL(bins, dim3((unsigned)nbins), dim3(kP1Threads), 0, s, a, 0);
-        hipLaunchKernelGGL(bwd_rescue_clear_kernel, dim3(256), dim3(256), 0, s, a);
-        // the rescue launch normally exits at once: a small grid that walks the bins when it does not
-        hipLaunchKernelGGL(rescue, dim3((unsigned)(nbins < kRescueGrid ? nbins : kRescueGrid)), dim3(kP1Threads), 0,
-                           s, a, 1);
+        const int64_t ncells = (int64_t)N * a.ncy * a.ncx;
+        if ((int64_t)K << (a.lgw + a.lgh) <= kP1Group) {
+            auto cells = o ? bwd_cells_kernel<true> : bwd_cells_kernel<false>;
+            auto again = o ? bwd_cells_again_kernel<true, false> : bwd_cells_again_kernel<false, false>;
+            hipLaunchKernelGGL(cells, dim3((unsigned)ncells), dim3(kP1Threads), 0, s, a);
+            hipLaunchKernelGGL(again, dim3((unsigned)std::min<int64_t>(ncells, kAgainGrid)), dim3(kP1Threads), 0, s, a);
+        } else {
+            auto again = o ? bwd_cells_again_kernel<true, true> : bwd_cells_again_kernel<false, true>;
+            hipLaunchKernelGGL(again, dim3((unsigned)ncells), dim3(kP1Threads), 0, s, a);
+        }
         hipLaunchKernelGGL(bwd_face_sum_kernel, dim3((unsigned)((F + kBwdBlock - 1) / kBwdBlock)), dim3(kBwdBlock), 0,
                            s, a);
         if (ee) (void)hipEventRecord(ee, s);

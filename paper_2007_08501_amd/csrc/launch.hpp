@@ -30,8 +30,8 @@ hipError_t launch_fine(const FaceRec* recs, const int64_t* first, const int64_t*
 hipError_t launch_backward(const float* verts, int64_t V, const int32_t* faces, int64_t F, const int64_t* first,
                            const int64_t* nf, int N, int H, int W, int K, float blur, int opts, int bs, int M,
                            const int32_t* p2f, const float* gz, const float* gb, const float* gd, float* grad,
-                           int* hdr, FaceRec* recs, int* counts, int* lists, float* partial, int* big,
-                           bool reuse, const BinSig& sig, hipStream_t s, hipEvent_t ev_begin, hipEvent_t ev_end);
+                           int* hdr, FaceRec* recs, int* counts, int* lists, int* order, float* partial,
+                           int* big, bool reuse, const BinSig& sig, hipStream_t s, hipEvent_t ev_begin, hipEvent_t ev_end);
 
 hipError_t launch_blend_fwd(const int32_t* p2f, const float* d, int64_t P, int K, float sigma, float* alpha,
                             hipStream_t s);

@@ -66,3 +66,41 @@ def test_per_face_backward_splits(level, n, image, K):
     ref = oracle.backward(b.verts, b.faces, b.image_size, o["p2f"], *g)
     got = run_bwd(b, _t(o["p2f"].astype(np.int32)), *g, bs=0)
     compare_grad(got.cpu().numpy(), ref, f"level {level}")
+
+
+# The binned backward's cells: 8, 16 or 32 pixels a side by the slots they
+# hold and the bins they divide (24-pixel bins only by 8), cut by the image's
+# edges; K above 16 reads its ids again; faces over more than four cells go to
+# the vertices.  Coarse meshes for the latter, finer ones for partial rows.
+@pytest.mark.parametrize("bs,K,level,image", [(8, 1, 2, (45, 61)), (8, 16, 3, (45, 61)), (8, 20, 3, (29, 43)),
+                                              (16, 3, 1, (77, 50)), (16, 8, 3, (50, 77)), (24, 5, 2, (61, 45)),
+                                              (32, 1, 2, (70, 100)), (32, 2, 3, (100, 70)), (32, 4, 1, (66, 65)),
+                                              (64, 4, 3, (66, 65)), (16, 33, 2, (33, 50)), (32, 64, 3, (40, 33))])
+def test_binned_backward_cells(bs, K, level, image):
+    from _util import compare_grad, run_bwd, threads, tie_masked_grads
+    from paper_2007_08501_amd import meshgen
+    b = meshgen.make_config(2, n_override=3, level_override=level)
+    b.image_size, b.faces_per_pixel = image, K
+    o = oracle.rasterize(b.verts, b.faces, b.first_idx, b.num_faces, b.image_size, b.blur_radius, K,
+                         nthreads=threads())
+    g = tie_masked_grads(b, o["p2f"], *meshgen.upstream_grads(b))
+    ref = oracle.backward(b.verts, b.faces, b.image_size, o["p2f"], *g)
+    got = run_bwd(b, _t(o["p2f"].astype(np.int32)), *g, bs=bs)
+    compare_grad(got.cpu().numpy(), ref, f"bins {bs} K {K}")
+
+
+# Upstream gradients over 40 orders of magnitude (sums in FP64 have no grid and
+# no range): the gradient is linear in them.
+@pytest.mark.parametrize("scale", [1e-30, 1e-12, 1e12, 1e20])
+def test_binned_backward_any_scale(scale):
+    from _util import run_bwd, run_fwd, to_dev
+    from paper_2007_08501_amd import meshgen
+    b = meshgen.make_config(2, n_override=2, level_override=3, image_override=48)
+    d = to_dev(b)
+    out, _ = run_fwd(b, 8, dev_inputs=d)
+    g = [_t(x) for x in meshgen.upstream_grads(b)]
+    one = run_bwd(b, out.pix_to_face, *g, dev_inputs=d, bs=8)
+    s = float(np.float32(scale))
+    got = run_bwd(b, out.pix_to_face, *(x * s for x in g), dev_inputs=d, bs=8)
+    # each side within a few ulps per added term: a few hundred terms a vertex
+    assert ((got.double() / s - one.double()).abs().max() <= 1e-4 * one.abs().max()).item()
