@@ -498,19 +498,6 @@ struct ChunkRecs {
     }
 };
 
-// Pixel centre coordinate 1 - (2i+1)/n from the reciprocal rn = 1/n with one
-// residual correction of the quotient: within one unit in the last place of
-// the forward's correctly rounded division, at five FP64 operations instead
-// of a division.  The backward only recomputes values of a face the forward
-// already chose, so the last place of the pixel centre cannot change a
-// decision that matters: it moves an edge function by about 1e-19.
-__device__ __forceinline__ double pix_coord_rcp(int i, double n, double rn) {
-    const double num = (double)(2 * i + 1);
-    const double q0 = num * rn;
-    const double r = fma(-q0, n, num);
-    return 1.0 - fma(r, rn, q0);
-}
-
 // Slot q of a cell in its slot order (pixel-major, k fastest): row, column
 // and slot within the pixel.  A cell has at most 4,096 slots (64 pixels of K =
 // 64), for which the quotients by a float reciprocal are exact.

@@ -25,6 +25,8 @@
 // scheme (tiles first, then pixels, register top-K per pixel); the coarse
 // pass is a counting sort of the points by home tile instead of per-bin
 // lists, so it has no capacity limit.
+#include <algorithm>
+
 #include "device.hpp"
 #include "launch.hpp"
 
@@ -654,7 +656,8 @@ struct PtBwdArgs {
     float r;
     double r2;
     int tiles_x, tiles_y, span_x, span_y;
-    int Kp;  // slots per pixel in LDS (K rounded up to a multiple of 4)
+    int Kp;      // slots per pixel in LDS (K rounded up to a multiple of 4)
+    int lg_cap;  // slot-major form: log2 of the points per chunk
     int reuse;
     BinSig sig;
 };
@@ -829,16 +832,23 @@ __global__ __launch_bounds__(kBwdTileThreads) void pt_bwd_tile_kernel(PtBwdArgs 
 // the pixel's offset within the point's pixel range; a point is listed at
 // most once per pixel, so every cell has one writer and no atomics are
 // needed.  Each point then sums its cells in row-major pixel order in FP64,
-// as the point-major form does.  Points beyond kSlotCap per tile are taken in
-// chunks, each rescanning the box.
-constexpr int kSlotCap = 1024;          // points per chunk
-constexpr int kSlotHash = 2 * kSlotCap; // hash entries (power of two)
-constexpr int kSlotMaxCells = 25;       // (span_x + 1) * (span_y + 1) at most
-constexpr int kSlotLoads = 16;          // slots loaded per thread before any is used
+// as the point-major form does.  Points beyond the chunk's capacity are taken
+// in further chunks, each rescanning the box.  Bound by the latency of the id
+// rows and the hash probes, so by the workgroups that fit a compute unit's
+// LDS: the capacity (128 to 1,024 points) is the smallest that holds about
+// twice the points of a covered tile's mean (half of the tiles taken as
+// covered).  At 4 x 270 x 401 pixels, 7 x 5 cells, the box-staged form took
+// 181 us; this one 140 with half that capacity, 77 with it (92 before the
+// cells' gradients were requested together), 110 with twice.
+constexpr int kSlotCapMin = 7, kSlotCapMax = 10;  // log2
+constexpr int kSlotLoads = 16;                    // slots loaded per thread before any is used
+constexpr int kCellLoads = 8;                     // cells whose gradients are requested together
 constexpr uint8_t kNoSlot = 0xff;
+constexpr size_t kSlotLdsMax = 64 * 1024;
 
-static_assert(kSlotHash == 1 << 11, "slot_hash yields 11 bits");
-__device__ __forceinline__ int slot_hash(int id) { return (int)(((uint32_t)id * 2654435761u) >> 21); }
+__device__ __forceinline__ int slot_hash(int id, int lg_hash) {
+    return (int)(((uint32_t)id * 2654435761u) >> (32 - lg_hash));
+}
 
 __device__ __forceinline__ void pt_bwd_slots_tile(const PtBwdArgs& b, int t, int2* htab, int* prc, uint8_t* cell) {
     const int lo = b.start[t], hi = b.start[t + 1];
@@ -854,9 +864,11 @@ __device__ __forceinline__ void pt_bwd_slots_tile(const PtBwdArgs& b, int t, int
     const int ex = b.span_x + 1, ey = b.span_y + 1, ncell = ex * ey;
     const int rowl = bw * K, nbox = bh * rowl;
     const float inv_rowl = 1.0f / (float)rowl, inv_k = 1.0f / (float)K;
-    for (int c_lo = lo; c_lo < hi; c_lo += kSlotCap) {
-        const int nloc = min(kSlotCap, hi - c_lo);
-        for (int i = threadIdx.x; i < kSlotHash; i += kBwdTileThreads) htab[i] = make_int2(-1, 0);
+    const double dW = (double)b.W, dH = (double)b.H, rW = 1.0 / dW, rH = 1.0 / dH;
+    const int cap = 1 << b.lg_cap, lg_hash = b.lg_cap + 1, nhash = 1 << lg_hash;
+    for (int c_lo = lo; c_lo < hi; c_lo += cap) {
+        const int nloc = min(cap, hi - c_lo);
+        for (int i = threadIdx.x; i < nhash; i += kBwdTileThreads) htab[i] = make_int2(-1, 0);
         uint32_t* cw = reinterpret_cast<uint32_t*>(cell);
         for (int i = threadIdx.x; i < (nloc * ncell + 3) / 4; i += kBwdTileThreads) cw[i] = 0xffffffffu;
         __syncthreads();
@@ -867,7 +879,7 @@ __device__ __forceinline__ void pt_bwd_slots_tile(const PtBwdArgs& b, int t, int
             disc_pixels(rec.x, rec.y, b.r, b.H, b.W, c0, c1, r0, r1);
             prc[i] = max(r0, y0) | (max(c0, x0) << 16);
             // ids are distinct, and the table is at least half empty
-            for (int h = slot_hash(id);; h = (h + 1) & (kSlotHash - 1)) {
+            for (int h = slot_hash(id, lg_hash);; h = (h + 1) & (nhash - 1)) {
                 if (atomicCAS(&htab[h].x, -1, id) == -1) {
                     htab[h].y = i;
                     break;
@@ -893,7 +905,7 @@ __device__ __forceinline__ void pt_bwd_slots_tile(const PtBwdArgs& b, int t, int
                 const int id = vi[j];
                 if (id < 0) continue;
                 int local = -1;
-                for (int h = slot_hash(id);; h = (h + 1) & (kSlotHash - 1)) {
+                for (int h = slot_hash(id, lg_hash);; h = (h + 1) & (nhash - 1)) {
                     const int2 en = htab[h];
                     if (en.x == id) {
                         local = en.y;
@@ -922,21 +934,36 @@ __device__ __forceinline__ void pt_bwd_slots_tile(const PtBwdArgs& b, int t, int
             const double x = rec.x, y = rec.y;
             double gx = 0.0, gy = 0.0, gzs = 0.0;
             const uint8_t* mine = cell + i * ncell;
-            for (int dr = 0; dr < ey; ++dr) {
-                const int r = pr0 + dr;
-                const double py = 1.0 - (double)(2 * r + 1) / (double)b.H;
-                for (int dc = 0; dc < ex; ++dc) {
-                    const int k = mine[dr * ex + dc];
-                    if (k == kNoSlot) continue;
-                    const int c = pc0 + dc;
-                    const double px = 1.0 - (double)(2 * c + 1) / (double)b.W;
-                    const int64_t g = (((int64_t)n * b.H + r) * b.W + c) * K + k;
-                    if (b.gz) gzs += (double)b.gz[g];
-                    if (b.gd) {
-                        const double gg = 2.0 * (double)b.gd[g];
-                        gx += gg * (x - px);
-                        gy += gg * (y - py);
+            // the cells in row-major order, eight at a time, their gradients
+            // all requested before the first is used
+            int dr = 0, dc = 0;
+            for (int c0 = 0; c0 < ncell; c0 += kCellLoads) {
+                float vz[kCellLoads], vd[kCellLoads];
+                int at[kCellLoads];  // row << 16 | column within the range, or -1
+#pragma unroll
+                for (int j = 0; j < kCellLoads; ++j) {
+                    const int k = c0 + j < ncell ? (int)mine[c0 + j] : (int)kNoSlot;
+                    at[j] = k == kNoSlot ? -1 : (dr << 16) | dc;
+                    vz[j] = vd[j] = 0.0f;
+                    if (k != kNoSlot) {
+                        const int64_t g = (((int64_t)n * b.H + pr0 + dr) * b.W + pc0 + dc) * K + k;
+                        if (b.gz) vz[j] = b.gz[g];
+                        if (b.gd) vd[j] = b.gd[g];
                     }
+                    if (++dc == ex) {
+                        dc = 0;
+                        ++dr;
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < kCellLoads; ++j) {
+                    if (at[j] < 0) continue;
+                    const double px = pix_coord_rcp(pc0 + (at[j] & 0xffff), dW, rW);
+                    const double py = pix_coord_rcp(pr0 + (at[j] >> 16), dH, rH);
+                    gzs += (double)vz[j];
+                    const double gg = 2.0 * (double)vd[j];
+                    gx += gg * (x - px);
+                    gy += gg * (y - py);
                 }
             }
             pt_write_grad(b, id, gx, gy, gzs);
@@ -948,18 +975,25 @@ __device__ __forceinline__ void pt_bwd_slots_tile(const PtBwdArgs& b, int t, int
 __global__ __launch_bounds__(kBwdTileThreads) void pt_bwd_slots_kernel(PtBwdArgs b) {
     if (!pt_bwd_usable(b)) return;
     int2* htab = reinterpret_cast<int2*>(bwd_lds);
-    int* prc = reinterpret_cast<int*>(htab + kSlotHash);
-    uint8_t* cell = reinterpret_cast<uint8_t*>(prc + kSlotCap);
+    int* prc = reinterpret_cast<int*>(htab + (2 << b.lg_cap));
+    uint8_t* cell = reinterpret_cast<uint8_t*>(prc + (1 << b.lg_cap));
     const int ntile = b.ohist[kPtOrderBuckets - 2];
     for (int j = blockIdx.x; j < ntile; j += gridDim.x) pt_bwd_slots_tile(b, b.order[j], htab, prc, cell);
 }
 
-// LDS bytes of the slot-major backward, or 0 when its cells do not fit.
-static size_t pt_bwd_slots_lds_bytes(int span_x, int span_y, int K) {
-    const int64_t ncell = (int64_t)(span_x + 1) * (span_y + 1);
-    if (ncell > kSlotMaxCells || K >= kNoSlot) return 0;
-    return (size_t)kSlotHash * sizeof(int2) + (size_t)kSlotCap * sizeof(int) +
-           (((size_t)kSlotCap * ncell + 3) & ~(size_t)3);
+// LDS bytes of the slot-major backward and its chunks' capacity, or 0 when
+// the cells of the smallest chunk do not fit.
+static size_t pt_bwd_slots_lds_bytes(const PtArgs& a, int& lg_cap) {
+    const int64_t ncell = (int64_t)(a.span_x + 1) * (a.span_y + 1);
+    if (a.K >= kNoSlot) return 0;
+    lg_cap = kSlotCapMin;
+    while (lg_cap < kSlotCapMax && 4 * a.P > a.T << lg_cap) ++lg_cap;
+    for (; lg_cap >= kSlotCapMin; --lg_cap) {
+        const size_t cap = (size_t)1 << lg_cap;
+        const size_t bytes = cap * (2 * sizeof(int2) + sizeof(int)) + ((cap * ncell + 3) & ~(size_t)3);
+        if (bytes <= kSlotLdsMax) return bytes;
+    }
+    return 0;
 }
 
 // LDS bytes of the box-staged backward, or 0 when it does not fit.
@@ -1015,7 +1049,7 @@ hipError_t launch_points_bwd(const float* pts, int64_t P, const int64_t* first, 
     b.Kp = (K + 3) & ~3;
     b.reuse = reuse ? 1 : 0;
     b.sig = sig;
-    const size_t slds = pt_bwd_slots_lds_bytes(a.span_x, a.span_y, K);
+    const size_t slds = pt_bwd_slots_lds_bytes(a, b.lg_cap);
     const size_t lds = pt_bwd_lds_bytes(a, a.span_x, a.span_y, gz != nullptr, gd != nullptr);
     if (eb) (void)hipEventRecord(eb, s);
     if (slds > 0) {
@@ -1171,109 +1205,173 @@ __global__ __launch_bounds__(256) void composite_fwd_kernel(CompArgs a, float* _
     }
 }
 
+// Opacity gradients of the lane's slots of pixel p (stored), and what the
+// feature gradients are made of: the slots' ids, their weights wf and the
+// pixel's upstream gradient g (dL/df of slot i's point collects wf[i] g).
+template <int L, int CB>
+__device__ __forceinline__ void composite_bwd_pixel(const CompArgs& a, const float* __restrict__ gimg,
+                                                    float* __restrict__ gw, int64_t p, int sub, int (&id)[kCompQ],
+                                                    float (&wf)[kCompQ], float (&g)[CB]) {
+    const float chain = a.from_d ? -a.inv_r2 : 1.0f;
+    float al[kCompQ];
+    comp_slots(a, p, sub, id, al);
+#pragma unroll
+    for (int c = 0; c < CB; ++c) g[c] = (p < a.npix && c < a.D) ? gimg[p * a.D + c] : 0.0f;
+    float gk[kCompQ];
+#pragma unroll
+    for (int i = 0; i < kCompQ; ++i) {
+        gk[i] = 0.0f;
+        if (id[i] >= 0) {
+            if (a.f) {
+                const float* fr = a.f + (int64_t)id[i] * a.D;
+#pragma unroll
+                for (int c = 0; c < CB; ++c)
+                    if (c < a.D) gk[i] = fmaf(g[c], fr[c], gk[i]);
+            } else {
+#pragma unroll
+                for (int c = 0; c < CB; ++c) gk[i] += g[c];  // features all ones
+            }
+        }
+    }
+    float dal[kCompQ];
+    if (!a.norm) {
+        float t = 1.0f;
+#pragma unroll
+        for (int i = 0; i < kCompQ; ++i) t *= 1.0f - al[i];
+        float T = seg_exclusive_prod<L>(t, sub);
+        // the lane's four maps composed (slot 4 sub outermost), then the
+        // composition of every later lane's maps: a suffix scan
+        float A = 1.0f, B = 0.0f;
+#pragma unroll
+        for (int i = kCompQ - 1; i >= 0; --i) {
+            B = fmaf(1.0f - al[i], B, al[i] * gk[i]);
+            A *= 1.0f - al[i];
+        }
+#pragma unroll
+        for (int d = 1; d < L; d <<= 1) {
+            const float A2 = __shfl_down(A, d, L), B2 = __shfl_down(B, d, L);
+            if (sub + d < L) {
+                B = fmaf(A, B2, B);
+                A *= A2;
+            }
+        }
+        const float Bn = __shfl_down(B, 1, L);
+        float V = sub == L - 1 ? 0.0f : Bn;  // R after the lane's last slot
+        float R[kCompQ];
+#pragma unroll
+        for (int i = kCompQ - 1; i >= 0; --i) {
+            R[i] = V;
+            V = fmaf(1.0f - al[i], V, al[i] * gk[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < kCompQ; ++i) {
+            dal[i] = T * (gk[i] - R[i]);
+            wf[i] = al[i] * T;
+            T *= 1.0f - al[i];
+        }
+    } else {
+        float S = 0.0f, Ag = 0.0f;
+#pragma unroll
+        for (int i = 0; i < kCompQ; ++i) {
+            S += al[i];
+            Ag = fmaf(al[i], gk[i], Ag);
+        }
+        S = seg_sum<L>(S);
+        Ag = seg_sum<L>(Ag);
+        const float invS = S > 0.0f ? 1.0f / S : 0.0f;
+#pragma unroll
+        for (int i = 0; i < kCompQ; ++i) {
+            dal[i] = (gk[i] - Ag * invS) * invS;
+            wf[i] = al[i] * invS;
+        }
+    }
+    const int64_t o = p * a.K + kCompQ * sub;
+    if (p < a.npix && kCompQ * (sub + 1) <= a.K) {
+        f32x4_a4 v;
+#pragma unroll
+        for (int i = 0; i < kCompQ; ++i) v[i] = id[i] >= 0 ? dal[i] * chain : 0.0f;
+        *reinterpret_cast<f32x4_a4*>(gw + o) = v;  // one 16-byte store
+    } else {
+#pragma unroll
+        for (int i = 0; i < kCompQ; ++i)
+            if (p < a.npix && kCompQ * sub + i < a.K) gw[o + i] = id[i] >= 0 ? dal[i] * chain : 0.0f;
+    }
+}
+
 template <int L, int CB>
 __global__ __launch_bounds__(256) void composite_bwd_kernel(CompArgs a, const float* __restrict__ gimg,
-                                                            float* __restrict__ gw, float* __restrict__ gf) {
+                                                            float* __restrict__ gw) {
     constexpr int PPW = 64 / L;
     const int lane = threadIdx.x & 63, sub = lane & (L - 1), grp = lane / L;
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    const float chain = a.from_d ? -a.inv_r2 : 1.0f;
     for (int64_t p0 = wave * PPW; p0 < a.npix; p0 += nwaves * PPW) {
-        const int64_t p = p0 + grp;
         int id[kCompQ];
-        float al[kCompQ];
-        comp_slots(a, p, sub, id, al);
-        float g[CB];
+        float wf[kCompQ], g[CB];
+        composite_bwd_pixel<L, CB>(a, gimg, gw, p0 + grp, sub, id, wf, g);
+    }
+}
+
+// The same with feature gradients.  A point is named by many neighbouring
+// pixels, so a workgroup takes a span of consecutive pixels (about 2,048
+// slots), adds the span's terms per point in an LDS hash table, in FP64 (LDS
+// adds FP64 in hardware, FP32 in a compare-and-swap loop), and sends each
+// point's row out once, lanes running over the words of the rows.  A point
+// that finds no place within kFeatProbe entries adds to its row directly.
+// Bound by the rate of global float atomics before (one per slot and channel,
+// each on a line of its own: 465 us at 4 x 270 x 401 pixels, K = 16, 3
+// channels); now 70 us there, by the tables' LDS atomics.
+constexpr int kFeatSlots = 2048;
+constexpr int kFeatProbe = 16;
+extern __shared__ double feat_lds[];
+
+template <int L, int CB>
+__global__ __launch_bounds__(256) void composite_bwd_feat_kernel(CompArgs a, const float* __restrict__ gimg,
+                                                                 float* __restrict__ gw, float* __restrict__ gf,
+                                                                 int span, int lg_table) {
+    constexpr int PPW = 64 / L;
+    const int lane = threadIdx.x & 63, sub = lane & (L - 1), grp = lane / L, wave = threadIdx.x >> 6;
+    const int table = 1 << lg_table;
+    double* vals = feat_lds;                              // table rows of D
+    int* keys = reinterpret_cast<int*>(vals + table * a.D);  // point ids (-1: free)
+    const float inv_d = 1.0f / (float)a.D;
+    for (int64_t s0 = (int64_t)blockIdx.x * span; s0 < a.npix; s0 += (int64_t)gridDim.x * span) {
+        for (int i = threadIdx.x; i < table; i += 256) keys[i] = -1;
+        for (int i = threadIdx.x; i < table * a.D; i += 256) vals[i] = 0.0;
+        __syncthreads();
+        for (int q = wave * PPW; q < span; q += 4 * PPW) {
+            int id[kCompQ];
+            float wf[kCompQ], g[CB];
+            // (span is a multiple of the pixels of four waves)
+            composite_bwd_pixel<L, CB>(a, gimg, gw, s0 + q + grp, sub, id, wf, g);
 #pragma unroll
-        for (int c = 0; c < CB; ++c) g[c] = (p < a.npix && c < a.D) ? gimg[p * a.D + c] : 0.0f;
-        float gk[kCompQ];
+            for (int i = 0; i < kCompQ; ++i) {
+                if (id[i] < 0 || wf[i] == 0.0f) continue;
+                uint32_t h = ((uint32_t)id[i] * 2654435761u) >> (32 - lg_table);
+                bool placed = false;
+                for (int probe = 0; probe < kFeatProbe && !placed; ++probe) {
+                    const int prev = atomicCAS(&keys[h], -1, id[i]);
+                    placed = prev == -1 || prev == id[i];
+                    if (!placed) h = (h + 1) & (uint32_t)(table - 1);
+                }
 #pragma unroll
-        for (int i = 0; i < kCompQ; ++i) {
-            gk[i] = 0.0f;
-            if (id[i] >= 0) {
-                if (a.f) {
-                    const float* fr = a.f + (int64_t)id[i] * a.D;
-#pragma unroll
-                    for (int c = 0; c < CB; ++c)
-                        if (c < a.D) gk[i] = fmaf(g[c], fr[c], gk[i]);
-                } else {
-#pragma unroll
-                    for (int c = 0; c < CB; ++c) gk[i] += g[c];  // features all ones
+                for (int c = 0; c < CB; ++c) {
+                    if (c >= a.D) continue;
+                    const float v = wf[i] * g[c];
+                    if (placed)
+                        atomicAdd(&vals[h * a.D + c], (double)v);
+                    else
+                        atomicAdd(gf + (int64_t)id[i] * a.D + c, v);
                 }
             }
         }
-        float dal[kCompQ], wf[kCompQ];
-        if (!a.norm) {
-            float t = 1.0f;
-#pragma unroll
-            for (int i = 0; i < kCompQ; ++i) t *= 1.0f - al[i];
-            float T = seg_exclusive_prod<L>(t, sub);
-            // the lane's four maps composed (slot 4 sub outermost), then the
-            // composition of every later lane's maps: a suffix scan
-            float A = 1.0f, B = 0.0f;
-#pragma unroll
-            for (int i = kCompQ - 1; i >= 0; --i) {
-                B = fmaf(1.0f - al[i], B, al[i] * gk[i]);
-                A *= 1.0f - al[i];
-            }
-#pragma unroll
-            for (int d = 1; d < L; d <<= 1) {
-                const float A2 = __shfl_down(A, d, L), B2 = __shfl_down(B, d, L);
-                if (sub + d < L) {
-                    B = fmaf(A, B2, B);
-                    A *= A2;
-                }
-            }
-            const float Bn = __shfl_down(B, 1, L);
-            float V = sub == L - 1 ? 0.0f : Bn;  // R after the lane's last slot
-            float R[kCompQ];
-#pragma unroll
-            for (int i = kCompQ - 1; i >= 0; --i) {
-                R[i] = V;
-                V = fmaf(1.0f - al[i], V, al[i] * gk[i]);
-            }
-#pragma unroll
-            for (int i = 0; i < kCompQ; ++i) {
-                dal[i] = T * (gk[i] - R[i]);
-                wf[i] = al[i] * T;
-                T *= 1.0f - al[i];
-            }
-        } else {
-            float S = 0.0f, Ag = 0.0f;
-#pragma unroll
-            for (int i = 0; i < kCompQ; ++i) {
-                S += al[i];
-                Ag = fmaf(al[i], gk[i], Ag);
-            }
-            S = seg_sum<L>(S);
-            Ag = seg_sum<L>(Ag);
-            const float invS = S > 0.0f ? 1.0f / S : 0.0f;
-#pragma unroll
-            for (int i = 0; i < kCompQ; ++i) {
-                dal[i] = (gk[i] - Ag * invS) * invS;
-                wf[i] = al[i] * invS;
-            }
+        __syncthreads();
+        for (int i = threadIdx.x; i < table * a.D; i += 256) {
+            const int h = (int)(((float)i + 0.5f) * inv_d);  // i / D (i < 2^13: exact)
+            const int point = keys[h];
+            if (point >= 0) atomicAdd(gf + (int64_t)point * a.D + (i - h * a.D), (float)vals[i]);
         }
-        const int64_t o = p * a.K + kCompQ * sub;
-        if (p < a.npix && kCompQ * (sub + 1) <= a.K) {
-            f32x4_a4 v;
-#pragma unroll
-            for (int i = 0; i < kCompQ; ++i) v[i] = id[i] >= 0 ? dal[i] * chain : 0.0f;
-            *reinterpret_cast<f32x4_a4*>(gw + o) = v;  // one 16-byte store
-        } else {
-#pragma unroll
-            for (int i = 0; i < kCompQ; ++i)
-                if (p < a.npix && kCompQ * sub + i < a.K) gw[o + i] = id[i] >= 0 ? dal[i] * chain : 0.0f;
-        }
-#pragma unroll
-        for (int i = 0; i < kCompQ; ++i) {
-            if (gf && id[i] >= 0 && wf[i] != 0.0f) {
-#pragma unroll
-                for (int c = 0; c < CB; ++c)
-                    if (c < a.D) atomicAdd(gf + (int64_t)id[i] * a.D + c, wf[i] * g[c]);
-            }
-        }
+        __syncthreads();  // (the next span clears the table)
     }
 }
 
@@ -1307,8 +1405,19 @@ static hipError_t comp_launch(const CompArgs& a, bool bwd, const float* gimg, fl
 #define COMP_L(L)                                                                                      \
     if (a.K <= kCompQ * L) {                                                                           \
         const dim3 grid(comp_blocks(a.npix, L));                                                       \
-        if (bwd)                                                                                       \
-            hipLaunchKernelGGL((composite_bwd_kernel<L, CB>), grid, dim3(256), 0, s, a, gimg, gw, gf); \
+        if (bwd && gf) {                                                                               \
+            /* a span of whole rounds of the workgroup; 34 to 36 KB of table */                        \
+            constexpr int round = 4 * (64 / L);                                                        \
+            const int64_t most = std::max<int64_t>(1, a.npix / (512 * round)); /* spans for the chip */ \
+            const int span = (int)std::min<int64_t>(most, std::max(1, kFeatSlots / (a.K * round))) * round; \
+            const int lg = CB <= 4 ? 10 : 9;                                                           \
+            const size_t lds = ((size_t)a.D * sizeof(double) + sizeof(int)) << lg;                     \
+            const int64_t spans = (a.npix + span - 1) / span;                                          \
+            hipLaunchKernelGGL((composite_bwd_feat_kernel<L, CB>),                                     \
+                               dim3((unsigned)std::min<int64_t>(spans, 16384)), dim3(256), lds, s, a, gimg, gw, gf, \
+                               span, lg);                                                              \
+        } else if (bwd)                                                                                \
+            hipLaunchKernelGGL((composite_bwd_kernel<L, CB>), grid, dim3(256), 0, s, a, gimg, gw);     \
         else                                                                                           \
             hipLaunchKernelGGL((composite_fwd_kernel<L, CB>), grid, dim3(256), 0, s, a, img);          \
         return hipGetLastError();                                                                      \

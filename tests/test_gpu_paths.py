@@ -104,3 +104,55 @@ def test_binned_backward_any_scale(scale):
     got = run_bwd(b, out.pix_to_face, *(x * s for x in g), dev_inputs=d, bs=8)
     # each side within a few ulps per added term: a few hundred terms a vertex
     assert ((got.double() / s - one.double()).abs().max() <= 1e-4 * one.abs().max()).item()
+
+
+# Feature gradients: a span of pixels per workgroup, its points in an LDS table
+# (1,024 entries for up to four channels, 512 above), points without a place
+# added directly.  Few points (every span names the same ones), about as many as
+# a span names, and many more than the table holds; K and pixel counts that
+# leave part spans.  A term is a product of at most 64 factors and one add:
+# 130 roundings of 2^-24 of the sum of the terms' sizes.
+@pytest.mark.parametrize("norm", [False, True])
+@pytest.mark.parametrize("K,D,P,npix", [(1, 1, 3, 5), (1, 3, 5000, 4099), (5, 8, 40, 700), (8, 5, 3000, 1025),
+                                        (16, 3, 100000, 2050), (17, 4, 9, 130), (50, 2, 2000, 97),
+                                        (64, 8, 100000, 200)])
+def test_feature_gradient_table(K, D, P, npix, norm):
+    from paper_2007_08501_amd.points import alpha_composite, norm_composite
+    rng = np.random.default_rng(K * 100 + D)
+    idx = rng.integers(0, P, (npix, K)).astype(np.int32)
+    idx[rng.uniform(size=idx.shape) < 0.2] = -1
+    al = rng.uniform(0, 1, (npix, K)).astype(np.float32)
+    f = rng.uniform(-1, 1, (P, D)).astype(np.float32)
+    g = rng.standard_normal((npix, D)).astype(np.float32)
+    back = oracle.norm_composite_backward if norm else oracle.alpha_composite_backward
+    _, ref = back(idx, al.astype(np.float64), f.astype(np.float64), g)
+    _, size = back(idx, al.astype(np.float64), f.astype(np.float64), np.abs(g))
+    ft = _t(f).requires_grad_(True)
+    img = (norm_composite if norm else alpha_composite)(_t(idx), _t(al), ft)
+    got, = torch.autograd.grad(img, (ft,), _t(g))
+    assert (np.abs(got.cpu().numpy() - ref) <= 8e-6 * np.abs(size) + 1e-30).all()
+
+
+# The slot-major point backward for pixel ranges of one pixel to 21 a side and
+# the forms behind it, on an image whose sides differ, with chunks (all points
+# homed in few tiles) and without.  The sums are FP64, rounded once.
+@pytest.mark.parametrize("radius,n_pts,spread", [(0.005, 300, 0.9), (0.04, 2000, 0.9), (0.09, 3000, 0.05),
+                                                 (0.16, 500, 0.9), (0.3, 300, 0.9), (0.44, 200, 0.5),
+                                                 (0.6, 100, 0.9)])
+def test_point_backward_ranges(radius, n_pts, spread):
+    from test_gpu_points import oracle_pfwd, run_pbwd, run_pfwd
+    from _util import threads
+    from paper_2007_08501_amd import _lib
+    rng = np.random.default_rng(int(1000 * radius))
+    H, W, K = 43, 70, 6
+    pts = np.c_[rng.uniform(-spread, spread, (n_pts, 2)), rng.uniform(0.5, 3, n_pts)].astype(np.float32)
+    radius = float(np.float32(radius))
+    p, f = _t(pts), torch.zeros(1, dtype=torch.int64, device="cuda")
+    n = torch.full((1,), n_pts, dtype=torch.int64, device="cuda")
+    idx, _, _, ws = run_pfwd(p, f, n, H, W, radius, K)
+    gz, gd = (rng.standard_normal((1, H, W, K)).astype(np.float32) for _ in range(2))
+    got = run_pbwd(p, f, n, H, W, radius, K, idx, _t(gz), _t(gd), ws, _lib.RAST_BWD_REUSE_FORWARD)
+    o = oracle_pfwd(pts, [0], [n_pts], H, W, radius, K)
+    np.testing.assert_array_equal(idx.cpu().numpy(), o["idx"])
+    ref = oracle.points_backward(pts, (H, W), o["idx"], gz, gd, nthreads=threads())
+    assert np.abs(got.cpu().numpy() - ref).max() <= 1e-6 * np.abs(ref).max()
