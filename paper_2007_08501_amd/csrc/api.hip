@@ -450,11 +450,11 @@ int rasterize_points_fwd(const float* points, int64_t P, const int64_t* cloud_to
     hipStream_t s = (hipStream_t)stream;
     char* ws = (char*)workspace;
     int* hdr = (int*)(ws + L.hdr);
-    if (rast::launch_header_init(hdr, pt_signature(P, N, H, W, radius), s) != hipSuccess) return RAST_EHIP;
     return hip_rc(rast::launch_points_fwd(points, P, cloud_to_first_idx, num_points_per_cloud, N, H, W, radius,
                                           points_per_pixel, hdr, (int*)(ws + L.start), (int*)(ws + L.bsum),
                                           (int*)(ws + L.home), (int*)(ws + L.rank), (float4*)(ws + L.sorted),
-                                          (int*)(ws + L.order), (int*)(ws + L.ohist), idx, zbuf, dists, s,
+                                          (int*)(ws + L.order), (int*)(ws + L.ohist), idx, zbuf, dists,
+                                          pt_signature(P, N, H, W, radius), s,
                                           tl_events.begin[RAST_KERNEL_POINTS_FINE],
                                           tl_events.end[RAST_KERNEL_POINTS_FINE]));
 }

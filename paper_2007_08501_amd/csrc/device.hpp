@@ -371,7 +371,38 @@ __device__ __forceinline__ void sort8(uint64_t (&b)[8]) {
     cex(b[1], b[2]); cex(b[3], b[4]); cex(b[5], b[6]);
 }
 
+// Sorts sixteen keys ascending with Green's 60-comparator network.
+__device__ __forceinline__ void sort16(uint64_t (&b)[16]) {
+#pragma unroll
+    for (int d = 1; d <= 8; d *= 2)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if (!(i & d)) cex(b[i], b[i + d]);
+    cex(b[5], b[10]); cex(b[6], b[9]); cex(b[3], b[12]); cex(b[13], b[14]);
+    cex(b[4], b[8]); cex(b[7], b[11]); cex(b[1], b[2]);
+    cex(b[1], b[4]); cex(b[7], b[13]); cex(b[2], b[8]); cex(b[11], b[14]);
+    cex(b[2], b[4]); cex(b[5], b[6]); cex(b[9], b[10]); cex(b[11], b[13]); cex(b[3], b[8]); cex(b[7], b[12]);
+    cex(b[6], b[8]); cex(b[10], b[12]); cex(b[3], b[5]); cex(b[7], b[9]);
+    cex(b[3], b[4]); cex(b[5], b[6]); cex(b[7], b[8]); cex(b[9], b[10]); cex(b[11], b[12]);
+    cex(b[6], b[7]); cex(b[8], b[9]);
+}
+template <int NB>
+__device__ __forceinline__ void sort_batch(uint64_t (&b)[NB]) {
+    static_assert(NB == 8 || NB == 16, "batch size");
+    if constexpr (NB == 8)
+        sort8(b);
+    else
+        sort16(b);
+}
+
 constexpr bool is_pow2(int x) { return x > 0 && (x & (x - 1)) == 0; }
+
+// New keys merged at once into a queue of kb: the merge's log2(kb) stages of
+// kb / 2 compare-exchanges are the price of a batch whatever its size, so the
+// long queues take sixteen at a time (K = 64: 16 compare-exchanges a key
+// instead of 26; the point pass at 8 x 200,000 points, K = 50: 266 -> 237 us),
+// the others eight, which hold fewer registers (K = 16: 6 against 7).
+constexpr int queue_batch(int kb) { return kb >= 32 ? 16 : 8; }
 
 // Register-resident sorted list of the KB smallest keys, only ever indexed
 // with compile-time constants.
@@ -382,39 +413,24 @@ struct TopK {
 #pragma unroll
         for (int i = 0; i < KB; ++i) q[i] = kEmptyKey;
     }
-    // Keeps the KB smallest of the queue and eight new keys (absent keys are
-    // kEmptyKey).  The batch is sorted, then one half-cleaner step
-    // q[i] = min(q[i], b[KB-1-i]) leaves the KB smallest of both as a bitonic
+    // Keeps the KB smallest of the queue and NB new keys (absent keys are
+    // kEmptyKey), merging within the first S slots, for a lane whose queue
+    // holds c keys and gets n new ones with c + n <= S (S = KB: any number).
+    // The batch is sorted, then one half-cleaner step
+    // q[i] = min(q[i], b[S-1-i]) leaves the S smallest of both as a bitonic
     // sequence, and a bitonic merge sorts it: about four compare-exchanges
-    // per key for KB = 16, against KB for one insertion at a time.
-    __device__ __forceinline__ void merge8(uint64_t (&b)[8]) {
-        sort8(b);
-        constexpr int M = KB < 8 ? KB : 8;
+    // per key for KB = 16, against KB for one insertion at a time.  With S < KB
+    // the slots from S on stay empty and the keys the half-cleaner drops are
+    // empty ones.
+    template <int S, int NB>
+    __device__ __forceinline__ void merge(uint64_t (&b)[NB]) {
+        static_assert(S <= KB && is_pow2(S), "prefix size");
+        sort_batch(b);
+        constexpr int M = S < NB ? S : NB;
 #pragma unroll
         for (int i = 0; i < M; ++i) {
-            const int qi = KB - M + i;
+            const int qi = S - M + i;
             q[qi] = key_min(b[M - 1 - i], q[qi]);
-        }
-#pragma unroll
-        for (int d = KB / 2; d >= 1; d /= 2) {
-#pragma unroll
-            for (int i = 0; i < KB; ++i)
-                if (!(i & d)) cex(q[i], q[i + d]);
-        }
-    }
-    // merge8 confined to the first S slots, for a lane whose queue holds c
-    // keys and gets n new ones with c + n <= S: the slots from S on stay
-    // empty, the eight keys the half-cleaner drops are empty ones, and the
-    // merge costs log2(S) stages of S / 2 compare-exchanges instead of
-    // log2(KB) stages of KB / 2.
-    template <int S>
-    __device__ __forceinline__ void merge8_prefix(uint64_t (&b)[8]) {
-        static_assert(S >= 8 && S <= KB && is_pow2(S), "prefix size");
-        sort8(b);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int qi = S - 8 + i;
-            q[qi] = key_min(b[7 - i], q[qi]);
         }
 #pragma unroll
         for (int d = S / 2; d >= 1; d /= 2) {
@@ -423,13 +439,14 @@ struct TopK {
                 if (!(i & d)) cex(q[i], q[i + d]);
         }
     }
-    // Adds eight keys: batched merge for power-of-two queues, else one at a time.
-    __device__ __forceinline__ void push8(uint64_t (&b)[8]) {
+    // Adds NB keys: batched merge for power-of-two queues, else one at a time.
+    template <int NB>
+    __device__ __forceinline__ void push(uint64_t (&b)[NB]) {
         if constexpr (is_pow2(KB)) {
-            merge8(b);
+            merge<KB>(b);
         } else {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) insert(b[u]);
+            for (int u = 0; u < NB; ++u) insert(b[u]);
         }
     }
     // Branch-free insertion: every slot is a compare-exchange with the

@@ -621,13 +621,14 @@ __device__ __forceinline__ void test_kept(const FineArgs& a, const TileLds& L, c
     const int lane = threadIdx.x & 63;
     __syncthreads();
     uint64_t mine = T(lane < m ? L.rec[lane].mask : 0ull);
-    // eight candidates per round; the round count is the wave's longest
+    constexpr int NB = queue_batch(KB);
+    // NB candidates per round; the round count is the wave's longest
     // list, so the loop is uniform and the queue stays in place across rounds
     const int nmax = wave_max(__popcll(mine));
-    for (int i0 = 0; i0 < nmax; i0 += 8) {
-        uint64_t b[8];
+    for (int i0 = 0; i0 < nmax; i0 += NB) {
+        uint64_t b[NB];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < NB; ++u) {
             uint64_t key = kEmptyKey;
             if (mine != 0ull) {
                 const int j = __ffsll((unsigned long long)mine) - 1;
@@ -637,7 +638,7 @@ __device__ __forceinline__ void test_kept(const FineArgs& a, const TileLds& L, c
             }
             b[u] = key;
         }
-        top.push8(b);
+        top.push(b);
     }
     __syncthreads();
 }

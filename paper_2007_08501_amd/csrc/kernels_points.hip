@@ -32,6 +32,8 @@
 
 namespace rast {
 
+constexpr int kPtOrderBuckets = 64;  // work buckets of the tile order
+
 // Home tile of a point: the tile holding the first pixel (lowest row, lowest
 // column) of the pixel ranges its disc may cover.  A disc then reaches at
 // most rx tiles to the right of and ry tiles below its home tile, so a tile
@@ -68,10 +70,9 @@ struct PtArgs {
     float* dists;
 };
 
-// Home tile of point p, or -1 when it takes no part (outside every cloud,
+// Home tile of point p of cloud n, or -1 when it takes no part (n < 0: outside every cloud,
 // behind the camera, or covering no pixel).
-__device__ __forceinline__ int pt_home(const PtArgs& a, int64_t p) {
-    const int n = find_mesh(a.first, a.np, a.N, p);
+__device__ __forceinline__ int pt_home(const PtArgs& a, int64_t p, int n) {
     const float x = a.pts[3 * p], y = a.pts[3 * p + 1], z = a.pts[3 * p + 2];
     int c0, c1, r0, r1;
     if (n < 0 || !(z >= 0.0f) || !disc_pixels(x, y, a.r, a.H, a.W, c0, c1, r0, r1)) return -1;
@@ -86,13 +87,22 @@ __device__ __forceinline__ void pt_check_cloud(const PtArgs& a, int64_t i) {
     if (bad) atomicOr(&a.hdr[kHdrStatus], kStatMesh);
 }
 
+// Clears the header (and stamps it), the tile counts and the order's buckets.
+__global__ __launch_bounds__(256) void pt_init_kernel(PtArgs a, BinSig sig) {
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+    if (i0 < kHdrWords)
+        a.hdr[i0] = (i0 >= kHdrSig && i0 < kHdrSig + kSigWords) ? sig.w[i0 - kHdrSig] : 0;
+    if (i0 < kPtOrderBuckets) a.ohist[i0] = 0;
+    for (int64_t i = i0; i <= a.T; i += stride) a.start[i] = 0;
+}
+
 // Counting, one thread per point: the rank of a point within its home tile is
 // the count before its own increment.
 __global__ __launch_bounds__(256) void pt_count_kernel(PtArgs a) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p < a.N) pt_check_cloud(a, p);
     if (p >= a.P) return;
-    const int h = pt_home(a, p);
+    const int h = pt_home(a, p, find_mesh(a.first, a.np, a.N, p));
     a.home[p] = h;
     a.rank[p] = h >= 0 ? atomicAdd(&a.start[h], 1) : 0;
 }
@@ -100,28 +110,62 @@ __global__ __launch_bounds__(256) void pt_count_kernel(PtArgs a) {
 // The same with the counts of a block's points first gathered in an LDS
 // histogram of every tile of the batch (when they fit): one global atomic per
 // tile a block touches instead of one per point.  A point's rank is the
-// block's base for its tile plus its rank within the block.
+// block's base for its tile plus its rank within the block.  A block's points
+// are consecutive, so it clears and adds only the tiles of the images they
+// span (a point of another image, which only inconsistent cloud ranges give,
+// counts globally).
 constexpr int kCountThreads = 1024;
 constexpr int kCountPer = 8;                  // points per thread
 constexpr int kCountLdsTiles = 16384;         // tiles the LDS histogram holds
 
+// The last image whose cloud starts at or before point p (0 if none).
+__device__ __forceinline__ int pt_image_of(const PtArgs& a, int64_t p) {
+    int lo = 0, hi = a.N - 1, ans = 0;
+    while (lo <= hi) {
+        const int mid = (lo + hi) >> 1;
+        if (a.first[mid] <= p) {
+            ans = mid;
+            lo = mid + 1;
+        } else {
+            hi = mid - 1;
+        }
+    }
+    return ans;
+}
+
 __global__ __launch_bounds__(kCountThreads) void pt_count_lds_kernel(PtArgs a) {
     __shared__ int hist[kCountLdsTiles];
-    const int T = (int)a.T;
+    const int per_img = a.tiles_x * a.tiles_y;
     if (blockIdx.x == 0)
         for (int i = threadIdx.x; i < a.N; i += kCountThreads) pt_check_cloud(a, i);
-    for (int i = threadIdx.x; i < T; i += kCountThreads) hist[i] = 0;
+    const int64_t p0 = (int64_t)blockIdx.x * kCountThreads * kCountPer;
+    const int n0 = pt_image_of(a, p0), n1 = max(n0, pt_image_of(a, p0 + kCountThreads * kCountPer - 1));
+    const int t0 = n0 * per_img, t1 = (n1 + 1) * per_img;  // (within [0, T])
+    for (int i = t0 + threadIdx.x; i < t1; i += kCountThreads) hist[i] = 0;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kCountThreads * kCountPer + threadIdx.x;
+    const int64_t base = p0 + threadIdx.x;
     int h[kCountPer], lr[kCountPer];
 #pragma unroll
     for (int j = 0; j < kCountPer; ++j) {
         const int64_t p = base + (int64_t)j * kCountThreads;
-        h[j] = p < a.P ? pt_home(a, p) : -1;
-        lr[j] = h[j] >= 0 ? atomicAdd(&hist[h[j]], 1) : 0;
+        h[j] = -1;
+        if (p < a.P) {
+            // mostly one cloud a block, found once (the same answer as the search per point)
+            int n = n0;
+            if (n0 != n1)
+                n = find_mesh(a.first, a.np, a.N, p);
+            else if (p < a.first[n0] || p >= a.first[n0] + a.np[n0])
+                n = -1;
+            h[j] = pt_home(a, p, n);
+        }
+        lr[j] = 0;
+        if (h[j] >= t0 && h[j] < t1)
+            lr[j] = atomicAdd(&hist[h[j]], 1);
+        else if (h[j] >= 0)
+            lr[j] = atomicAdd(&a.start[h[j]], 1);
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < T; i += kCountThreads) {
+    for (int i = t0 + threadIdx.x; i < t1; i += kCountThreads) {
         const int c = hist[i];
         if (c > 0) hist[i] = atomicAdd(&a.start[i], c);
     }
@@ -131,7 +175,7 @@ __global__ __launch_bounds__(kCountThreads) void pt_count_lds_kernel(PtArgs a) {
         const int64_t p = base + (int64_t)j * kCountThreads;
         if (p < a.P) {
             a.home[p] = h[j];
-            a.rank[p] = h[j] >= 0 ? hist[h[j]] + lr[j] : 0;
+            a.rank[p] = h[j] < 0 ? 0 : (h[j] >= t0 && h[j] < t1 ? hist[h[j]] : 0) + lr[j];
         }
     }
 }
@@ -230,9 +274,7 @@ __global__ __launch_bounds__(256) void pt_scatter_kernel(PtArgs a) {
 // bucketed on a log scale (two buckets per octave), and a counting sort over
 // the 64 buckets lists the tiles.  Within a bucket the order is arbitrary;
 // the fragments do not depend on it.
-constexpr int kPtOrderBuckets = 64;
-
-__device__ __forceinline__ int pt_tile_bucket(const PtArgs& a, int t) {
+__device__ __forceinline__ int pt_tile_bucket(const PtArgs& a, const int* start, int t) {
     const int per_img = a.tiles_x * a.tiles_y;
     const int n = t / per_img;
     const int tt = t - n * per_img;
@@ -240,7 +282,7 @@ __device__ __forceinline__ int pt_tile_bucket(const PtArgs& a, int t) {
     int w = 0;
     for (int yy = max(ty - a.ry, 0); yy <= ty; ++yy) {
         const int64_t row = ((int64_t)n * a.tiles_y + yy) * a.tiles_x;
-        w += a.start[row + tx + 1] - a.start[row + max(tx - a.rx, 0)];
+        w += start[row + tx + 1] - start[row + max(tx - a.rx, 0)];
     }
     const unsigned v = (unsigned)w + 1u;
     const int lg = 31 - __clz(v);
@@ -250,7 +292,7 @@ __device__ __forceinline__ int pt_tile_bucket(const PtArgs& a, int t) {
 
 __global__ __launch_bounds__(256) void pt_order_hist_kernel(PtArgs a) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    (void)wave_bucket_slot(a.ohist, t < a.T ? pt_tile_bucket(a, (int)t) : -1);
+    (void)wave_bucket_slot(a.ohist, t < a.T ? pt_tile_bucket(a, a.start, (int)t) : -1);
 }
 
 __global__ void pt_order_scan_kernel(int* __restrict__ ohist) {
@@ -266,18 +308,74 @@ __global__ void pt_order_scan_kernel(int* __restrict__ ohist) {
 
 __global__ __launch_bounds__(256) void pt_order_scatter_kernel(PtArgs a) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int pos = wave_bucket_slot(a.ohist, t < a.T ? pt_tile_bucket(a, (int)t) : -1);
+    const int pos = wave_bucket_slot(a.ohist, t < a.T ? pt_tile_bucket(a, a.start, (int)t) : -1);
     if (t < a.T) a.order[pos] = (int)t;
 }
 
 static hipError_t pt_order(const PtArgs& a, hipStream_t s) {
-    hipError_t e = launch_fill_i32(a.ohist, kPtOrderBuckets, 0, s);
-    if (e != hipSuccess) return e;
     const unsigned g = (unsigned)((a.T + 255) / 256);
     hipLaunchKernelGGL(pt_order_hist_kernel, dim3(g), dim3(256), 0, s, a);
     hipLaunchKernelGGL(pt_order_scan_kernel, dim3(1), dim3(64), 0, s, a.ohist);
     hipLaunchKernelGGL(pt_order_scatter_kernel, dim3(g), dim3(256), 0, s, a);
     return hipGetLastError();
+}
+
+// Scan and tile order of up to kOneBlockTiles tiles in one workgroup, the
+// starts in LDS: six launches of a few microseconds each, most of it their
+// own latency, in one (8 x 1,024 tiles: 42 us with the clear, now 15).
+constexpr int kOneBlockPer = 15;
+constexpr int kOneBlockTiles = kOneBlockPer * kScanThreads;
+__global__ __launch_bounds__(kScanThreads) void pt_scan_order_kernel(PtArgs a) {
+    __shared__ int st[kOneBlockTiles + 1];
+    __shared__ int hist[kPtOrderBuckets];
+    __shared__ int sm[kScanThreads / 64];
+    const int T = (int)a.T, tid = threadIdx.x;
+    for (int i = tid; i < T; i += kScanThreads) st[i] = a.start[i];
+    if (tid < kPtOrderBuckets) hist[tid] = 0;
+    __syncthreads();
+    const int per = (T + kScanThreads - 1) / kScanThreads;  // consecutive tiles of a thread
+    const int i0 = min(tid * per, T), i1 = min(i0 + per, T);
+    int sum = 0;
+    for (int i = i0; i < i1; ++i) sum += st[i];
+    int total;
+    int ex = block_exclusive(sum, sm, total);
+    for (int i = i0; i < i1; ++i) {
+        const int c = st[i];
+        st[i] = ex;
+        ex += c;
+    }
+    if (tid == 0) st[T] = total;
+    __syncthreads();
+    for (int i = tid; i <= T; i += kScanThreads) a.start[i] = st[i];
+    // a tile's bucket and its rank there (the lanes of a bucket go one after
+    // the other: 128 tiles a microsecond, less than ballots per bucket cost)
+    int bucket[kOneBlockPer], rank[kOneBlockPer];
+#pragma unroll
+    for (int j = 0; j < kOneBlockPer; ++j) {
+        const int t = j * kScanThreads + tid;
+        if (t < T) {
+            bucket[j] = pt_tile_bucket(a, st, t);
+            rank[j] = atomicAdd(&hist[bucket[j]], 1);
+        }
+    }
+    __syncthreads();
+    if (tid < 64) {
+        static_assert(kPtOrderBuckets == 64, "one bucket a lane");
+        int incl = hist[tid];
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int u = __shfl_up(incl, o);
+            if (tid >= o) incl += u;
+        }
+        a.ohist[tid] = incl;  // the buckets' ends, as the scatter of pt_order leaves them
+        hist[tid] = incl - hist[tid];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kOneBlockPer; ++j) {
+        const int t = j * kScanThreads + tid;
+        if (t < T) a.order[hist[bucket[j]] + rank[j]] = t;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -322,18 +420,19 @@ __device__ __forceinline__ double pt_d2(double x, double y, double px, double py
     return dx * dx + dy * dy;
 }
 
-// Pushes a lane's listed hits into its queue, eight at a time, merging
-// within the first S slots (S = KB: the whole queue).
+// Pushes a lane's listed hits into its queue, NB at a time, merging within
+// the first S slots (S = KB: the whole queue).
 template <int S, int KB, class BL>
 __device__ __forceinline__ void pt_push_hits(TopK<KB>& top, const BL& L, const unsigned char* my, int nl, int nmax) {
-    for (int i0 = 0; i0 < nmax; i0 += 8) {
-        uint64_t b[8];
+    constexpr int NB = queue_batch(KB);
+    for (int i0 = 0; i0 < nmax; i0 += NB) {
+        uint64_t b[NB];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) b[u] = (i0 + u < nl) ? L.key[my[64 * (i0 + u)]] : kEmptyKey;
+        for (int u = 0; u < NB; ++u) b[u] = (i0 + u < nl) ? L.key[my[64 * (i0 + u)]] : kEmptyKey;
         if constexpr (S == KB)
-            top.push8(b);
+            top.push(b);
         else
-            top.template merge8_prefix<S>(b);
+            top.template merge<S>(b);
     }
 }
 
@@ -370,9 +469,7 @@ __device__ __forceinline__ void pt_batch(const PtArgs& a, BL& L, TopK<KB>& top, 
         // every push of this batch fits the smallest prefix that holds the
         // wave's largest queue after it (the choice is uniform over the wave)
         const int need = wave_max(held + nl);
-        if (need <= 8)
-            pt_push_hits<8, KB>(top, L, my, nl, nmax);
-        else if (need <= 16)
+        if (need <= 16)
             pt_push_hits<16, KB>(top, L, my, nl, nmax);
         else if (need <= 32 && KB > 32)
             pt_push_hits<(KB > 32 ? 32 : KB), KB>(top, L, my, nl, nmax);
@@ -563,8 +660,11 @@ static PtArgs pt_args(const float* pts, int64_t P, const int64_t* first, const i
 
 int64_t pt_scan_blocks(int64_t T) { return (T + kScanTile - 1) / kScanTile; }
 
-static hipError_t pt_sort(const PtArgs& a, hipStream_t s) {
-    hipError_t e = launch_fill_i32(a.start, a.T + 1, 0, s);
+// Header, sorted points and tile order.
+static hipError_t pt_sort(const PtArgs& a, const BinSig& sig, hipStream_t s) {
+    hipLaunchKernelGGL(pt_init_kernel, dim3((unsigned)std::min<int64_t>((a.T + 256) / 256, 1024)), dim3(256), 0, s, a,
+                       sig);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (a.T <= kCountLdsTiles) {
         const int64_t per_block = (int64_t)kCountThreads * kCountPer;
@@ -575,10 +675,17 @@ static hipError_t pt_sort(const PtArgs& a, hipStream_t s) {
         const unsigned g = (unsigned)((nthreads + 255) / 256);
         hipLaunchKernelGGL(pt_count_kernel, dim3(g), dim3(256), 0, s, a);
     }
-    const int64_t nb = pt_scan_blocks(a.T);
-    hipLaunchKernelGGL(pt_scan_sums_kernel, dim3((unsigned)nb), dim3(kScanThreads), 0, s, a.start, a.T, a.bsum);
-    hipLaunchKernelGGL(pt_scan_top_kernel, dim3(1), dim3(kScanThreads), 0, s, a.bsum, nb);
-    hipLaunchKernelGGL(pt_scan_apply_kernel, dim3((unsigned)nb), dim3(kScanThreads), 0, s, a.start, a.T, a.bsum, nb);
+    if (a.T <= kOneBlockTiles) {
+        hipLaunchKernelGGL(pt_scan_order_kernel, dim3(1), dim3(kScanThreads), 0, s, a);
+    } else {
+        const int64_t nb = pt_scan_blocks(a.T);
+        hipLaunchKernelGGL(pt_scan_sums_kernel, dim3((unsigned)nb), dim3(kScanThreads), 0, s, a.start, a.T, a.bsum);
+        hipLaunchKernelGGL(pt_scan_top_kernel, dim3(1), dim3(kScanThreads), 0, s, a.bsum, nb);
+        hipLaunchKernelGGL(pt_scan_apply_kernel, dim3((unsigned)nb), dim3(kScanThreads), 0, s, a.start, a.T, a.bsum,
+                           nb);
+        e = pt_order(a, s);
+        if (e != hipSuccess) return e;
+    }
     if (a.P > 0) hipLaunchKernelGGL(pt_scatter_kernel, dim3((unsigned)((a.P + 255) / 256)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
@@ -595,16 +702,14 @@ static hipError_t pt_fine_k(const PtArgs& a, bool aligned, hipStream_t s, hipEve
 hipError_t launch_points_fwd(const float* pts, int64_t P, const int64_t* first, const int64_t* np, int N, int H,
                              int W, float radius, int K, int* hdr, int* start, int* bsum, int* home, int* rank,
                              float4* sorted, int* order, int* ohist, int32_t* idx, float* zbuf, float* dists,
-                             hipStream_t s, hipEvent_t eb, hipEvent_t ee) {
+                             const BinSig& sig, hipStream_t s, hipEvent_t eb, hipEvent_t ee) {
     PtArgs a = pt_args(pts, P, first, np, N, H, W, radius, K, hdr, start, bsum, home, rank, sorted);
     a.order = order;
     a.ohist = ohist;
     a.idx = idx;
     a.zbuf = zbuf;
     a.dists = dists;
-    hipError_t e = pt_sort(a, s);
-    if (e != hipSuccess) return e;
-    e = pt_order(a, s);
+    hipError_t e = pt_sort(a, sig, s);
     if (e != hipSuccess) return e;
     const bool aligned = (((uintptr_t)idx | (uintptr_t)zbuf | (uintptr_t)dists) & 15) == 0;
 #define PT_FINE_BUCKET(KB)                                                     \
@@ -1015,11 +1120,7 @@ hipError_t launch_points_bwd(const float* pts, int64_t P, const int64_t* first, 
     hipError_t e = launch_fill_f32(grad, 3 * P, 0.0f, s);
     if (e != hipSuccess) return e;
     if (!reuse) {
-        e = launch_header_init(hdr, sig, s);
-        if (e != hipSuccess) return e;
-        e = pt_sort(a, s);
-        if (e != hipSuccess) return e;
-        e = pt_order(a, s);
+        e = pt_sort(a, sig, s);
         if (e != hipSuccess) return e;
     }
     if (P == 0) return hipSuccess;

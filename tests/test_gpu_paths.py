@@ -156,3 +156,19 @@ def test_point_backward_ranges(radius, n_pts, spread):
     np.testing.assert_array_equal(idx.cpu().numpy(), o["idx"])
     ref = oracle.points_backward(pts, (H, W), o["idx"], gz, gd, nthreads=threads())
     assert np.abs(got.cpu().numpy() - ref).max() <= 1e-6 * np.abs(ref).max()
+
+
+# Scan and tile order in one workgroup up to 15,360 tiles, in six launches
+# above; several clouds, so that a counting block spans images (or, with an
+# empty one between, skips them).  Fragments are exact.
+@pytest.mark.parametrize("H,W,sizes", [(8, 8, [3]), (960, 1024, [150, 0, 90]), (968, 1024, [150]),
+                                       (70, 41, [20000, 0, 1, 9000, 500])])
+def test_point_sort_sizes(H, W, sizes):
+    from test_gpu_points import check_case
+    if H > 900:
+        H, W, sizes = H, W, [sum(sizes)] if len(sizes) == 1 else [sizes[0]]
+    rng = np.random.default_rng(H)
+    n = sum(sizes)
+    pts = np.c_[rng.uniform(-0.95, 0.95, (n, 2)), rng.uniform(0.5, 3, n)].astype(np.float32)
+    first = np.concatenate([[0], np.cumsum(sizes)[:-1]]).astype(np.int64)
+    check_case(pts, first, np.array(sizes, dtype=np.int64), H, W, 0.02, 2, f"{H}x{W}")
