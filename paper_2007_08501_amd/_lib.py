@@ -120,15 +120,23 @@ def _check(fn: str, rc: int):
 
 
 def _p(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    """Device address as the int that a c_void_p argument takes (None: NULL)."""
+    return None if t is None else t.data_ptr()
 
 
-def _stream(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+# The current stream's handle as an int; building a torch.cuda.Stream object
+# for it costs several microseconds a call.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream(device) -> int:
+    if _raw_stream is not None and device.index is not None:
+        return _raw_stream(device.index)
+    return torch.cuda.current_stream(device).cuda_stream
 
 
 def _require(t, name, dtype, device=None):
-    if t is None:
+    if t is None or (t.is_cuda and t.dtype == dtype and t.is_contiguous() and (device is None or t.device == device)):
         return
     if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
@@ -136,8 +144,7 @@ def _require(t, name, dtype, device=None):
         raise ValueError(f"{name} must be {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if device is not None and t.device != device:
-        raise ValueError(f"{name} is on {t.device}, expected {device}")
+    raise ValueError(f"{name} is on {t.device}, expected {device}")
 
 
 def rast_workspace_size(N, H, W, F, bin_size, max_faces_per_bin) -> int:
@@ -261,9 +268,10 @@ def rast_query_status(workspace):
 
 
 def _same_shape(ref, shape, *named):
-    """Raise unless every given tensor has exactly `shape` (checked before any launch)."""
+    """Raise unless every given tensor has exactly `shape`, a tuple or torch.Size
+    (checked before any launch)."""
     for t, n in named:
-        if t is not None and tuple(t.shape) != tuple(shape):
+        if t is not None and t.shape != shape:
             raise ValueError(f"{n} has shape {tuple(t.shape)}, expected {tuple(shape)} (from {ref})")
 
 

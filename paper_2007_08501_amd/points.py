@@ -65,6 +65,7 @@ class _RasterizePoints(torch.autograd.Function):
         ctx.ws = ws
         ctx.args = (H, W, radius, K)
         ctx.mark_non_differentiable(idx)
+        ctx.set_materialize_grads(False)  # (None for an output without a gradient, taken as zero)
         return idx, zbuf, dists
 
     @staticmethod

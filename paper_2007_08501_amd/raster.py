@@ -124,6 +124,9 @@ class _RasterizeMeshes(torch.autograd.Function):
                 raise _lib.RastError("rasterize_meshes_fwd", st, _lib.status_string(st))
         ctx.save_for_backward(vd, faces, first_idx, num_faces, out.pix_to_face)
         ctx.mark_non_differentiable(out.pix_to_face)
+        # an output without a gradient gives None, which the kernels take as
+        # zero without reading it, instead of a tensor of zeros
+        ctx.set_materialize_grads(False)
         ctx.dims = (N, H, W, K)
         ctx.blur = blur
         ctx.bins = (bs, M)
@@ -137,7 +140,7 @@ class _RasterizeMeshes(torch.autograd.Function):
         N, H, W, K = ctx.dims
 
         def prep(g):
-            return None if g is None else g.contiguous().to(torch.float32)
+            return None if g is None else g.to(torch.float32).contiguous()
 
         grad_verts = torch.empty_like(verts)
         bs, M = ctx.bins

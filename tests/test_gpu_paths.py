@@ -172,3 +172,41 @@ def test_point_sort_sizes(H, W, sizes):
     pts = np.c_[rng.uniform(-0.95, 0.95, (n, 2)), rng.uniform(0.5, 3, n)].astype(np.float32)
     first = np.concatenate([[0], np.cumsum(sizes)[:-1]]).astype(np.int64)
     check_case(pts, first, np.array(sizes, dtype=np.int64), H, W, 0.02, 2, f"{H}x{W}")
+
+
+# An output without a gradient reaches the backward as None: the same gradient
+# as with zeros (up to the order of the float atomics, a few ulps of the sums).
+@pytest.mark.parametrize("bs", [0, 8])
+@pytest.mark.parametrize("which", [0, 1, 2])
+def test_missing_upstream_gradients_are_zeros(which, bs):
+    from _util import run_bwd, to_dev
+    from paper_2007_08501_amd import meshgen
+    from paper_2007_08501_amd.raster import RasterSettings, rasterize_meshes
+    b = meshgen.make_config(2, n_override=2, level_override=3, image_override=40)
+    v, f, fi, nf = to_dev(b)
+    v.requires_grad_(True)
+    fr = rasterize_meshes(v, f, fi, nf, RasterSettings(image_size=40, blur_radius=b.blur_radius, faces_per_pixel=4,
+                                                       bin_size=bs))
+    g = [_t(x) for x in meshgen.upstream_grads(b)]
+    got, = torch.autograd.grad((fr.zbuf, fr.bary, fr.dists)[which], (v,), g[which])
+    full = [x if i == which else torch.zeros_like(x) for i, x in enumerate(g)]
+    ref = run_bwd(b, fr.pix_to_face, *full, dev_inputs=(v.detach(), f, fi, nf), bs=bs)
+    assert (got - ref).abs().max() <= 1e-5 * ref.abs().max()
+
+
+def test_missing_point_gradients_are_zeros():
+    from test_gpu_points import dev_cloud, run_pbwd, run_pfwd
+    from paper_2007_08501_amd import meshgen
+    from paper_2007_08501_amd.points import PointsRasterSettings, rasterize_points
+    b = meshgen.make_points_config(1)
+    H, W = b.image_size
+    p, f, n = dev_cloud(b)
+    idx, _, _, ws = run_pfwd(p, f, n, H, W, b.radius, 4)
+    g = torch.randn((1, H, W, 4), device="cuda")
+    p.requires_grad_(True)
+    fr = rasterize_points(p, f, n, PointsRasterSettings(image_size=(H, W), radius=b.radius, points_per_pixel=4))
+    for which in (1, 2):
+        got, = torch.autograd.grad(fr[which], (p,), g, retain_graph=True)
+        gz, gd = (g, torch.zeros_like(g)) if which == 1 else (torch.zeros_like(g), g)
+        ref = run_pbwd(p.detach(), f, n, H, W, b.radius, 4, idx, gz, gd, ws)
+        assert torch.equal(got, ref)
