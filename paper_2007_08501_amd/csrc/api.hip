@@ -171,21 +171,17 @@ static int fwd_impl(const float* verts_packed, int64_t V, const int32_t* faces_p
     rast::FaceRec* recs = (rast::FaceRec*)(ws + L.recs);
     int n_workers = (sched == RAST_SCHED_PERSISTENT) ? n_workers_for_current_device() : 0;
 
+    int* counts = bin_size > 0 ? (int*)(ws + L.counts) : nullptr;
+    int* lists = bin_size > 0 ? (int*)(ws + L.lists) : nullptr;
     // the header carries this call's binning signature for a backward that reuses the bins
     hipError_t e = rast::launch_header_init(
-        hdr, bin_signature(F, N, H, W, bin_size, bin_size > 0 ? max_faces_per_bin : 0, blur_radius, options), s);
+        hdr, bin_signature(F, N, H, W, bin_size, bin_size > 0 ? max_faces_per_bin : 0, blur_radius, options), counts,
+        L.nbins, s);
     if (e != hipSuccess) return RAST_EHIP;
     e = rast::launch_face_setup(verts_packed, V, faces_packed, F, mesh_to_face_first_idx, num_faces_per_mesh, N, H,
-                                W, sqrtf(blur_radius), options, recs, hdr, s);
+                                W, sqrtf(blur_radius), options, recs, hdr, bin_size, max_faces_per_bin, counts, lists,
+                                s);
     if (e != hipSuccess) return RAST_EHIP;
-    int* counts = nullptr;
-    int* lists = nullptr;
-    if (bin_size > 0) {
-        counts = (int*)(ws + L.counts);
-        lists = (int*)(ws + L.lists);
-        e = rast::launch_binning(recs, F, N, H, W, bin_size, max_faces_per_bin, counts, lists, hdr, s);
-        if (e != hipSuccess) return RAST_EHIP;
-    }
     e = rast::launch_fine(recs, mesh_to_face_first_idx, num_faces_per_mesh, counts, lists, F, N, H, W,
                           faces_per_pixel, blur_radius, options, bin_size, max_faces_per_bin, sched,
                           (int*)(ws + L.order),
@@ -287,13 +283,12 @@ int rast_bin_count(const float* verts_packed, int64_t V, const int32_t* faces_pa
     char* ws = (char*)workspace;
     int* hdr = (int*)(ws + L.hdr);
     rast::FaceRec* recs = (rast::FaceRec*)(ws + L.recs);
-    hipError_t e = rast::launch_fill_i32(hdr, rast::kHdrWords, 0, s);
-    if (e != hipSuccess) return RAST_EHIP;
-    e = rast::launch_face_setup(verts_packed, V, faces_packed, F, mesh_to_face_first_idx, num_faces_per_mesh, N, H,
-                                W, sqrtf(blur_radius), 0, recs, hdr, s);
+    int* counts = (int*)(ws + L.counts);
+    hipError_t e = rast::launch_header_init(hdr, rast::BinSig{}, counts, L.nbins, s);
     if (e != hipSuccess) return RAST_EHIP;
     // M = 0: count only, no list writes
-    return hip_rc(rast::launch_binning(recs, F, N, H, W, bin_size, 0, (int*)(ws + L.counts), nullptr, hdr, s));
+    return hip_rc(rast::launch_face_setup(verts_packed, V, faces_packed, F, mesh_to_face_first_idx, num_faces_per_mesh,
+                                          N, H, W, sqrtf(blur_radius), 0, recs, hdr, bin_size, 0, counts, nullptr, s));
 }
 
 int rast_query_status(const void* workspace, int* status, int* max_bin_count, void* stream) {

@@ -900,9 +900,6 @@ hipError_t launch_backward(const float* verts, int64_t V, const int32_t* faces, 
     if (bs == 0 || F == 0) {
         e = launch_prep(grad, V * 3, hdr, reuse ? 0 : kHdrWords, hdr, s);
         if (e != hipSuccess) return e;
-    } else if (!reuse) {
-        e = launch_fill_i32(hdr, kHdrWords, 0, s);
-        if (e != hipSuccess) return e;
     }
     if (F == 0) return hipSuccess;
     BwdArgs a;
@@ -943,9 +940,10 @@ hipError_t launch_backward(const float* verts, int64_t V, const int32_t* faces, 
         // the same face setup and binning as the forward (unless the forward's
         // are reused), then the two passes
         if (!reuse) {
-            e = launch_face_setup(verts, V, faces, F, first, nf, N, H, W, a.rb, opts, recs, hdr, s);
+            e = launch_header_init(hdr, BinSig{}, counts, (int64_t)N * a.nby * a.nbx, s);
             if (e != hipSuccess) return e;
-            e = launch_binning(recs, F, N, H, W, bs, M, counts, lists, hdr, s);
+            e = launch_face_setup(verts, V, faces, F, first, nf, N, H, W, a.rb, opts, recs, hdr, bs, M, counts, lists,
+                                  s);
             if (e != hipSuccess) return e;
         }
         // grad_verts and the row masks (no partial row is written yet: F x 4

@@ -1,9 +1,9 @@
 // kernels_fwd.hip -- forward rasterization kernels for gfx950.
 //
-//   face_setup      one thread per face: mesh id, 112-byte record, padded bbox
-//   bin_faces       one thread per face: append the face to every bin its bbox
-//                   touches (counting only when lists == nullptr); largest bin
-//                   count -> workspace header, overflow flag
+//   face_setup      one thread per face: mesh id, 112-byte record, pixel
+//                   ranges; with bins, the face appended to every bin that its
+//                   ranges touch (counting only when lists == nullptr) and the
+//                   largest bin count -> workspace header, overflow flag
 //   raster_tiles    one wave per 8x8 pixel tile: loop over candidate faces
 //                   (all faces of the tile's mesh, or the tile's bin list),
 //                   cull per tile, test per pixel, keep the K nearest in
@@ -44,14 +44,16 @@ hipError_t launch_fill_i32(int* p, int64_t n, int v, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Clears the workspace header and stamps the binning signature.
-__global__ void header_init_kernel(int* __restrict__ hdr, BinSig sig) {
-    for (int i = threadIdx.x; i < kHdrWords; i += blockDim.x)
-        hdr[i] = (i >= kHdrSig && i < kHdrSig + kSigWords) ? sig.w[i - kHdrSig] : 0;
+// Clears the workspace header, stamps the binning signature and clears the
+// nbins bin counts, in one launch.
+__global__ void header_init_kernel(int* __restrict__ hdr, BinSig sig, int* __restrict__ counts, int64_t nbins) {
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+    if (i0 < kHdrWords) hdr[i0] = (i0 >= kHdrSig && i0 < kHdrSig + kSigWords) ? sig.w[i0 - kHdrSig] : 0;
+    for (int64_t i = i0; i < nbins; i += stride) counts[i] = 0;
 }
 
-hipError_t launch_header_init(int* hdr, const BinSig& sig, hipStream_t s) {
-    hipLaunchKernelGGL(header_init_kernel, dim3(1), dim3(64), 0, s, hdr, sig);
+hipError_t launch_header_init(int* hdr, const BinSig& sig, int* counts, int64_t nbins, hipStream_t s) {
+    hipLaunchKernelGGL(header_init_kernel, dim3(grid_for(nbins / 4, 256)), dim3(256), 0, s, hdr, sig, counts, nbins);
     return hipGetLastError();
 }
 
@@ -76,79 +78,20 @@ hipError_t launch_fill_f32(float* p, int64_t n, float v, hipStream_t s) {
     return hipGetLastError();
 }
 
-// One thread per face builds the face's record (make_rec: mesh id, exact FP64
-// edge vectors, grown box); the workgroup's 256 records are staged in LDS and
-// stored with coalesced 16-byte writes (a lane storing its own 112 bytes
-// leaves each store instruction scattered over 64 lines).  The threads below
-// N also check the mesh ranges.
-__global__ __launch_bounds__(256) void face_setup_kernel(const float* __restrict__ verts, int64_t V,
-                                                         const int32_t* __restrict__ faces, int64_t F,
-                                                         const int64_t* __restrict__ first,
-                                                         const int64_t* __restrict__ nf, int N, int H, int W, float rb,
-                                                         int opts, FaceRec* __restrict__ recs, int* __restrict__ hdr) {
-    __shared__ FaceRec srec[256];
-    const int64_t f0 = (int64_t)blockIdx.x * blockDim.x;
-    int64_t f = f0 + threadIdx.x;
-    if (first != nullptr && f < N) {
-        // mesh range check: inside [0, F] and ascending without overlap
-        int64_t a = first[f], c = nf[f];
-        bool bad = a < 0 || c < 0 || a + c > F;
-        if (f > 0) bad = bad || a < first[f - 1] + nf[f - 1];
-        if (bad) atomicOr(&hdr[kHdrStatus], kStatMesh);
-    }
-    if (f0 >= F) return;  // (uniform over the workgroup)
-    if (f < F) {
-        int mesh = first != nullptr ? find_mesh(first, nf, N, f) : 0;
-        int i0 = faces[3 * f + 0], i1 = faces[3 * f + 1], i2 = faces[3 * f + 2];
-        bool idx_ok = i0 >= 0 && i0 < V && i1 >= 0 && i1 < V && i2 >= 0 && i2 < V;
-        if (!idx_ok) {
-            atomicOr(&hdr[kHdrStatus], kStatMesh);
-            mesh = -1;
-            i0 = i1 = i2 = 0;
-        }
-        if (V == 0) {
-            srec[threadIdx.x] = make_rec(0, 0, 0, 0, 0, 0, 0, 0, 0, rb, H, W, -1);
-        } else {
-            const float* a = verts + 3 * (int64_t)i0;
-            const float* b = verts + 3 * (int64_t)i1;
-            const float* c = verts + 3 * (int64_t)i2;
-            srec[threadIdx.x] =
-                make_rec(a[0], a[1], a[2], b[0], b[1], b[2], c[0], c[1], c[2], rb, H, W, mesh, opts);
-        }
-    }
-    __syncthreads();
-    // the workgroup's records are contiguous: coalesced 16-byte stores
-    const int n = (int)min((int64_t)blockDim.x, F - f0);
-    const float4* src = reinterpret_cast<const float4*>(srec);
-    float4* dst = reinterpret_cast<float4*>(recs + f0);
-    constexpr int W4 = sizeof(FaceRec) / sizeof(float4);
-    for (int i = threadIdx.x; i < n * W4; i += blockDim.x) dst[i] = src[i];
-}
-
-hipError_t launch_face_setup(const float* verts, int64_t V, const int32_t* faces, int64_t F, const int64_t* first,
-                             const int64_t* nf, int N, int H, int W, float rb, int opts, FaceRec* recs, int* hdr,
-                             hipStream_t s) {
-    int64_t n = F > N ? F : N;
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(face_setup_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, verts, V, faces, F,
-                       first, nf, N, H, W, rb, opts, recs, hdr);
-    return hipGetLastError();
-}
-
-// One thread per face appends the face to every bin of its range.  The
-// workgroup's 256 consecutive faces (usually neighbours on the mesh, sharing
-// bins) first count their appends per distinct bin in an LDS hash table; one
-// global atomic per distinct bin then reserves room for all of the
-// workgroup's appends to it, and a second walk over the ranges hands out the
-// positions.  An append whose bin finds the table full reserves its own
-// position with a global atomic, and so does one whose bin is not within
-// kBinProbe slots of its hash position (both walks probe the same slots, so
-// they agree on which bins the table holds): a workgroup of large faces,
-// touching thousands of bins, then costs at most kBinProbe probes per
-// append.  The workgroup also records the largest
-// count it leaves in any of its bins (the last reservation in a bin ends at
-// its final count, so the maximum over workgroups is the largest bin count)
-// and flags a count above the capacity M.
+// Binning of a workgroup's faces.  The workgroup's 256 consecutive faces
+// (usually neighbours on the mesh, sharing bins) first count their appends per
+// distinct bin in an LDS hash table; one global atomic per distinct bin then
+// reserves room for all of the workgroup's appends to it, and a second walk
+// over the ranges hands out the positions.  An append whose bin finds the
+// table full reserves its own position with a global atomic, and so does one
+// whose bin is not within kBinProbe slots of its hash position (both walks
+// probe the same slots, so they agree on which bins the table holds): a
+// workgroup of large faces, touching thousands of bins, then costs at most
+// kBinProbe probes per append.  The workgroup also records the largest count
+// it leaves in any of its bins (the last reservation in a bin ends at its
+// final count, so the maximum over workgroups is the largest bin count) and
+// flags a count above the capacity M.
+constexpr int kSetupBlock = 256;
 constexpr int kBinHash = 1024;  // LDS hash entries of the binning workgroup
 constexpr int kBinProbe = 32;   // slots probed per append
 __device__ __forceinline__ uint32_t bin_hash(int64_t b) {
@@ -156,34 +99,37 @@ __device__ __forceinline__ uint32_t bin_hash(int64_t b) {
 }
 static_assert(kBinHash == 1024, "bin_hash yields 10 bits");
 
-__global__ __launch_bounds__(256) void bin_faces_kernel(const FaceRec* __restrict__ recs, int64_t F, int bs,
-                                                        int nby, int nbx, int M, int* __restrict__ counts,
-                                                        int* __restrict__ lists, int* __restrict__ hdr) {
-    __shared__ unsigned long long hkey[kBinHash];  // bin + 1 (0: empty)
-    __shared__ int wmax[4];
-    __shared__ int hcnt[kBinHash];   // appends per bin, then the next rank to hand out
-    __shared__ int hbase[kBinHash];  // the workgroup's reserved start in the bin
-    for (int i = threadIdx.x; i < kBinHash; i += blockDim.x) {
-        hkey[i] = 0ull;
-        hcnt[i] = 0;
+struct BinArgs {
+    int bs, nby, nbx, M;
+    int* counts;
+    int* lists;  // nullptr: count only
+};
+
+struct BinTable {
+    unsigned long long key[kBinHash];  // bin + 1 (0: empty)
+    int cnt[kBinHash];                 // appends per bin, then the next rank to hand out
+    int base[kBinHash];                // the workgroup's reserved start in the bin
+    int wmax[kSetupBlock / 64];
+};
+
+// Appends face f of image n, if it has any pixels (px), to its bins.
+__device__ __forceinline__ void bin_face(const BinArgs& a, BinTable& T, bool ok, int n, const int4 px, int f,
+                                         int* __restrict__ hdr) {
+    for (int i = threadIdx.x; i < kBinHash; i += kSetupBlock) {
+        T.key[i] = 0ull;
+        T.cnt[i] = 0;
     }
-    const int64_t f = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int n = 0, bx0 = 0, by0 = 0, nbw = 1, nb = 0;
-    if (f < F) {
-        const FaceRec& R = recs[f];
-        int bx1, by1;
-        if (face_bins(R, bs, bx0, bx1, by0, by1)) {
-            n = R.mesh();
-            nbw = bx1 - bx0 + 1;
-            nb = nbw * (by1 - by0 + 1);
-        }
+    int bx0 = 0, by0 = 0, bx1, by1, nbw = 1, nb = 0;
+    if (ok && face_bins_of_px(px, a.bs, bx0, bx1, by0, by1)) {
+        nbw = bx1 - bx0 + 1;
+        nb = nbw * (by1 - by0 + 1);
     }
     __syncthreads();
     // 1. count per distinct bin
     {
         int ri = 0, rj = 0;
         for (int i = 0; i < nb; ++i) {
-            const long long bin = ((int64_t)n * nby + by0 + ri) * nbx + bx0 + rj;
+            const long long bin = ((int64_t)n * a.nby + by0 + ri) * a.nbx + bx0 + rj;
             if (++rj == nbw) {
                 rj = 0;
                 ++ri;
@@ -191,9 +137,9 @@ __global__ __launch_bounds__(256) void bin_faces_kernel(const FaceRec* __restric
             const unsigned long long key = (unsigned long long)bin + 1ull;
             uint32_t h = bin_hash(bin);
             for (int probe = 0; probe < kBinProbe; ++probe) {
-                const unsigned long long prev = atomicCAS(&hkey[h], 0ull, key);
+                const unsigned long long prev = atomicCAS(&T.key[h], 0ull, key);
                 if (prev == 0ull || prev == key) {
-                    atomicAdd(&hcnt[h], 1);
+                    atomicAdd(&T.cnt[h], 1);
                     break;
                 }
                 h = (h + 1) & (kBinHash - 1);
@@ -203,12 +149,12 @@ __global__ __launch_bounds__(256) void bin_faces_kernel(const FaceRec* __restric
     __syncthreads();
     // 2. one reservation per distinct bin
     int top = 0;  // largest count this thread leaves in a bin
-    for (int i = threadIdx.x; i < kBinHash; i += blockDim.x) {
-        const unsigned long long key = hkey[i];
+    for (int i = threadIdx.x; i < kBinHash; i += kSetupBlock) {
+        const unsigned long long key = T.key[i];
         if (key != 0ull) {
-            hbase[i] = atomicAdd(&counts[key - 1], hcnt[i]);
-            top = max(top, hbase[i] + hcnt[i]);
-            hcnt[i] = 0;
+            T.base[i] = atomicAdd(&a.counts[key - 1], T.cnt[i]);
+            top = max(top, T.base[i] + T.cnt[i]);
+            T.cnt[i] = 0;
         }
     }
     __syncthreads();
@@ -216,7 +162,7 @@ __global__ __launch_bounds__(256) void bin_faces_kernel(const FaceRec* __restric
     {
         int ri = 0, rj = 0;
         for (int i = 0; i < nb; ++i) {
-            const long long bin = ((int64_t)n * nby + by0 + ri) * nbx + bx0 + rj;
+            const long long bin = ((int64_t)n * a.nby + by0 + ri) * a.nbx + bx0 + rj;
             if (++rj == nbw) {
                 rj = 0;
                 ++ri;
@@ -225,44 +171,110 @@ __global__ __launch_bounds__(256) void bin_faces_kernel(const FaceRec* __restric
             uint32_t h = bin_hash(bin);
             int pos = -1;
             for (int probe = 0; probe < kBinProbe; ++probe) {
-                const unsigned long long key = hkey[h];
+                const unsigned long long key = T.key[h];
                 if (key == want) {
-                    pos = hbase[h] + atomicAdd(&hcnt[h], 1);
+                    pos = T.base[h] + atomicAdd(&T.cnt[h], 1);
                     break;
                 }
                 if (key == 0ull) break;
                 h = (h + 1) & (kBinHash - 1);
             }
             if (pos < 0) {
-                pos = atomicAdd(&counts[bin], 1);  // (not in the table)
+                pos = atomicAdd(&a.counts[bin], 1);  // (not in the table)
                 top = max(top, pos + 1);
             }
-            if (lists != nullptr && pos < M) lists[bin * M + pos] = (int)f;
+            if (a.lists != nullptr && pos < a.M) a.lists[bin * a.M + pos] = f;
         }
     }
     // the workgroup's largest count: one word per wave, then one read and, only
     // if larger, one atomic per workgroup (same-address atomics serialise)
-    for (int o = 32; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o));
-    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = top;
+    top = wave_max(top);
+    if ((threadIdx.x & 63) == 0) T.wmax[threadIdx.x >> 6] = top;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < (int)(blockDim.x >> 6); ++w) top = max(top, wmax[w]);
+        for (int w = 1; w < kSetupBlock / 64; ++w) top = max(top, T.wmax[w]);
         if (top > __hip_atomic_load(&hdr[kHdrMaxCount], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
             atomicMax(&hdr[kHdrMaxCount], top);
-        if (M > 0 && top > M) atomicOr(&hdr[kHdrStatus], kStatOverflow);
+        if (a.M > 0 && top > a.M) atomicOr(&hdr[kHdrStatus], kStatOverflow);
     }
 }
 
-hipError_t launch_binning(const FaceRec* recs, int64_t F, int N, int H, int W, int bs, int M, int* counts, int* lists,
-                          int* hdr, hipStream_t s) {
-    int nby = (H + bs - 1) / bs, nbx = (W + bs - 1) / bs;
-    int64_t nbins = (int64_t)N * nby * nbx;
-    hipError_t e = launch_fill_i32(counts, nbins, 0, s);
-    if (e != hipSuccess) return e;
-    if (F > 0) {
-        hipLaunchKernelGGL(bin_faces_kernel, dim3((unsigned)((F + 255) / 256)), dim3(256), 0, s, recs, F, bs, nby, nbx,
-                           M, counts, lists, hdr);
+// One thread per face builds the face's record (make_rec: mesh id, exact FP64
+// edge vectors, pixel ranges); the workgroup's 256 records are staged in LDS
+// and stored with coalesced 16-byte writes (a lane storing its own 112 bytes
+// leaves each store instruction scattered over 64 lines).  The threads below
+// N also check the mesh ranges.  kBin: the faces are binned at once, over the
+// staging's LDS; as a kernel of its own the binning read every record's
+// ranges back, two lines a face: SETUP_NOW.
+template <bool kBin>
+__global__ __launch_bounds__(kSetupBlock) void face_setup_kernel(const float* __restrict__ verts, int64_t V,
+                                                                 const int32_t* __restrict__ faces, int64_t F,
+                                                                 const int64_t* __restrict__ first,
+                                                                 const int64_t* __restrict__ nf, int N, int H, int W,
+                                                                 float rb, int opts, FaceRec* __restrict__ recs,
+                                                                 int* __restrict__ hdr, BinArgs bin) {
+    __shared__ union {
+        FaceRec rec[kSetupBlock];
+        BinTable table;
+    } L;
+    const int64_t f0 = (int64_t)blockIdx.x * kSetupBlock;
+    int64_t f = f0 + threadIdx.x;
+    if (first != nullptr && f < N) {
+        // mesh range check: inside [0, F] and ascending without overlap
+        int64_t a = first[f], c = nf[f];
+        bool bad = a < 0 || c < 0 || a + c > F;
+        if (f > 0) bad = bad || a < first[f - 1] + nf[f - 1];
+        if (bad) atomicOr(&hdr[kHdrStatus], kStatMesh);
     }
+    if (f0 >= F) return;  // (uniform over the workgroup)
+    bool ok = false;
+    int image = 0;
+    int4 px = make_int4(0, -1, 0, -1);
+    if (f < F) {
+        int mesh = first != nullptr ? find_mesh(first, nf, N, f) : 0;
+        int i0 = faces[3 * f + 0], i1 = faces[3 * f + 1], i2 = faces[3 * f + 2];
+        bool idx_ok = i0 >= 0 && i0 < V && i1 >= 0 && i1 < V && i2 >= 0 && i2 < V;
+        if (!idx_ok) {
+            atomicOr(&hdr[kHdrStatus], kStatMesh);
+            mesh = -1;
+            i0 = i1 = i2 = 0;
+        }
+        FaceRec R;
+        if (V == 0) {
+            R = make_rec(0, 0, 0, 0, 0, 0, 0, 0, 0, rb, H, W, -1);
+        } else {
+            const float* a = verts + 3 * (int64_t)i0;
+            const float* b = verts + 3 * (int64_t)i1;
+            const float* c = verts + 3 * (int64_t)i2;
+            R = make_rec(a[0], a[1], a[2], b[0], b[1], b[2], c[0], c[1], c[2], rb, H, W, mesh, opts);
+        }
+        ok = R.ok();
+        image = R.mesh();
+        px = R.px;
+        L.rec[threadIdx.x] = R;
+    }
+    __syncthreads();
+    // the workgroup's records are contiguous: coalesced 16-byte stores
+    const int n = (int)min((int64_t)kSetupBlock, F - f0);
+    const float4* src = reinterpret_cast<const float4*>(L.rec);
+    float4* dst = reinterpret_cast<float4*>(recs + f0);
+    constexpr int W4 = sizeof(FaceRec) / sizeof(float4);
+    for (int i = threadIdx.x; i < n * W4; i += kSetupBlock) dst[i] = src[i];
+    if constexpr (kBin) {
+        __syncthreads();
+        bin_face(bin, L.table, ok, image, px, (int)f, hdr);
+    }
+}
+
+hipError_t launch_face_setup(const float* verts, int64_t V, const int32_t* faces, int64_t F, const int64_t* first,
+                             const int64_t* nf, int N, int H, int W, float rb, int opts, FaceRec* recs, int* hdr,
+                             int bs, int M, int* counts, int* lists, hipStream_t s) {
+    int64_t n = F > N ? F : N;
+    if (n <= 0) return hipSuccess;
+    const BinArgs b{bs, bs > 0 ? (H + bs - 1) / bs : 0, bs > 0 ? (W + bs - 1) / bs : 0, M, counts, lists};
+    auto setup = bs > 0 ? face_setup_kernel<true> : face_setup_kernel<false>;
+    hipLaunchKernelGGL(setup, dim3((unsigned)((n + kSetupBlock - 1) / kSetupBlock)), dim3(kSetupBlock), 0, s, verts, V,
+                       faces, F, first, nf, N, H, W, rb, opts, recs, hdr, b);
     return hipGetLastError();
 }
 

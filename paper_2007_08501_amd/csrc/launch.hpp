@@ -10,16 +10,16 @@ namespace rast {
 
 hipError_t launch_fill_i32(int* p, int64_t n, int v, hipStream_t s);
 hipError_t launch_fill_f32(float* p, int64_t n, float v, hipStream_t s);
-hipError_t launch_header_init(int* hdr, const BinSig& sig, hipStream_t s);
+// the header cleared and stamped, the nbins counts cleared
+hipError_t launch_header_init(int* hdr, const BinSig& sig, int* counts, int64_t nbins, hipStream_t s);
 // out[0] = the header's device status as a rast_status code, out[1] = its largest bin count
 hipError_t launch_status_out(const int* hdr, int32_t* out, hipStream_t s);
 
+// Face records; with bs > 0 also the bins (cleared counts expected): M 0 and
+// lists nullptr count only.
 hipError_t launch_face_setup(const float* verts, int64_t V, const int32_t* faces, int64_t F, const int64_t* first,
                              const int64_t* nf, int N, int H, int W, float rb, int opts, FaceRec* recs, int* hdr,
-                             hipStream_t s);
-
-hipError_t launch_binning(const FaceRec* recs, int64_t F, int N, int H, int W, int bs, int M, int* counts, int* lists,
-                          int* hdr, hipStream_t s);
+                             int bs, int M, int* counts, int* lists, hipStream_t s);
 
 hipError_t launch_fine(const FaceRec* recs, const int64_t* first, const int64_t* nf, const int* counts,
                        const int* lists, int64_t F, int N, int H, int W, int K, float blur, int opts, int bs, int M,
