@@ -13,11 +13,21 @@
 
 namespace rast {
 
+// sigmoid(x) and sigmoid(-x), 1 / (1 + e) and e / (1 + e) with e = exp(-|x|),
+// which does not overflow: one exponential and no branch for both signs.
+// Evaluated by a branch on the sign (two exponentials and two divisions
+// wherever a wave holds both signs, and again for -x) this bound the silhouette
+// blend, with its loads in branches that waited for each other: 20 x
+// 128 x 128 pixels, K = 50 took 43 us forward and 53 us backward, now 29 and 43
+// (bound by memory: 65 MB of ids read, and in the backward 65 MB written).
 __device__ __forceinline__ float sigmoidf(float x) {
-    // 1 / (1 + exp(-x)), evaluated on the side where exp does not overflow
-    if (x >= 0.0f) return 1.0f / (1.0f + expf(-x));
-    float e = expf(x);
-    return e / (1.0f + e);
+    const float e = expf(-fabsf(x));
+    return (x >= 0.0f ? 1.0f : e) / (1.0f + e);
+}
+__device__ __forceinline__ void sigmoid_pair(float x, float& pos, float& neg) {
+    const float e = expf(-fabsf(x)), den = 1.0f + e;
+    pos = (x >= 0.0f ? 1.0f : e) / den;
+    neg = (x <= 0.0f ? 1.0f : e) / den;
 }
 
 // A pixel's K slots are spread over L lanes of a wave, four consecutive slots
@@ -31,27 +41,67 @@ constexpr int kBlendQ = 4;  // consecutive slots per lane
 typedef int bi32x4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef float bf32x4 __attribute__((ext_vector_type(4), aligned(4)));
 
-// The lane's slots of pixel p: whether each holds a face, and d / sigma.
-__device__ __forceinline__ void blend_slots(const int32_t* __restrict__ p2f, const float* __restrict__ d, int64_t p,
-                                            int64_t P, int K, int sub, float inv_sigma, bool (&on)[kBlendQ],
-                                            float (&x)[kBlendQ]) {
-    const int64_t o = p * K + kBlendQ * sub;
-    if (p < P && kBlendQ * (sub + 1) <= K) {
-        const bi32x4 vi = *reinterpret_cast<const bi32x4*>(p2f + o);
-        const bf32x4 vd = *reinterpret_cast<const bf32x4*>(d + o);
+// A lane's slots of one pixel: whether each holds a face, and d / sigma.  The
+// distances are read only by lanes that hold a face.  TAIL: slots or pixels
+// may lie beyond the arrays' ends; without it a lane whose slots run past its
+// pixel's reads the next pixel's words and drops them, so that no load sits in
+// a branch and the loads of all groups are in flight together.
+struct BlendSlots {
+    bool on[kBlendQ];
+    float x[kBlendQ];
+    bool any;
+
+    template <bool TAIL>
+    __device__ __forceinline__ void load_ids(const int32_t* __restrict__ p2f, int64_t p, int64_t P, int K, int sub) {
+        const int64_t o = p * K + kBlendQ * sub;
+        if constexpr (TAIL) {
 #pragma unroll
-        for (int i = 0; i < kBlendQ; ++i) {
-            on[i] = vi[i] >= 0;
-            x[i] = vd[i] * inv_sigma;
-        }
-    } else {
+            for (int i = 0; i < kBlendQ; ++i) on[i] = p < P && kBlendQ * sub + i < K && p2f[o + i] >= 0;
+        } else {
+            const bi32x4 vi = *reinterpret_cast<const bi32x4*>(p2f + o);
 #pragma unroll
-        for (int i = 0; i < kBlendQ; ++i) {
-            const bool in = p < P && kBlendQ * sub + i < K;
-            on[i] = in && p2f[o + i] >= 0;
-            x[i] = in ? d[o + i] * inv_sigma : 0.0f;
+            for (int i = 0; i < kBlendQ; ++i) on[i] = kBlendQ * sub + i < K && vi[i] >= 0;
         }
+        any = false;
+#pragma unroll
+        for (int i = 0; i < kBlendQ; ++i) any = any || on[i];
     }
+
+    template <bool TAIL>
+    __device__ __forceinline__ void load_dists(const float* __restrict__ d, int64_t p, int K, int sub,
+                                               float inv_sigma) {
+        const int64_t o = p * K + kBlendQ * sub;
+        bf32x4 vd{0.0f, 0.0f, 0.0f, 0.0f};
+        if constexpr (TAIL) {
+#pragma unroll
+            for (int i = 0; i < kBlendQ; ++i)
+                if (on[i]) vd[i] = d[o + i];
+        } else {
+            if (any) vd = *reinterpret_cast<const bf32x4*>(d + o);
+        }
+#pragma unroll
+        for (int i = 0; i < kBlendQ; ++i) x[i] = vd[i] * inv_sigma;
+    }
+};
+
+// pixel groups that a wave has in flight (their loads are issued together):
+// 1 group 32 + 44 us at the size above, 2 groups 29 + 43, 4 groups 27 + 44
+constexpr int kBlendU = 2;
+
+// whether all words that a wave's groups at p0 touch without TAIL exist
+template <int L>
+__device__ __forceinline__ bool blend_inside(int64_t p0, int64_t P, int K) {
+    return (p0 + kBlendU * (64 / L) - 1) * K + kBlendQ * L <= P * K;
+}
+
+// A wave's groups: the ids of all, then the distances of all.
+template <int L, bool TAIL>
+__device__ __forceinline__ void blend_load(const int32_t* __restrict__ p2f, const float* __restrict__ d, int64_t p,
+                                           int64_t P, int K, int sub, float inv_sigma, BlendSlots (&sl)[kBlendU]) {
+#pragma unroll
+    for (int u = 0; u < kBlendU; ++u) sl[u].load_ids<TAIL>(p2f, p + u * (64 / L), P, K, sub);
+#pragma unroll
+    for (int u = 0; u < kBlendU; ++u) sl[u].load_dists<TAIL>(d, p + u * (64 / L), K, sub, inv_sigma);
 }
 
 template <int L>
@@ -90,17 +140,25 @@ __global__ __launch_bounds__(256) void blend_fwd_kernel(const int32_t* __restric
     const int lane = threadIdx.x & 63, sub = lane & (L - 1), grp = lane / L;
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    for (int64_t p0 = wave * PPW; p0 < P; p0 += nwaves * PPW) {
-        const int64_t p = p0 + grp;
-        bool on[kBlendQ];
-        float x[kBlendQ];
-        blend_slots(p2f, d, p, P, K, sub, inv_sigma, on, x);
-        float t = 1.0f;  // product of 1 - prob_k over the lane's slots
+    for (int64_t p0 = wave * (PPW * kBlendU); p0 < P; p0 += nwaves * (PPW * kBlendU)) {
+        BlendSlots sl[kBlendU];
+        if (blend_inside<L>(p0, P, K)) {
+            blend_load<L, false>(p2f, d, p0 + grp, P, K, sub, inv_sigma, sl);
+        } else {
+            blend_load<L, true>(p2f, d, p0 + grp, P, K, sub, inv_sigma, sl);
+        }
 #pragma unroll
-        for (int i = 0; i < kBlendQ; ++i)
-            if (on[i]) t *= sigmoidf(x[i]);
-        t = blend_seg_prod<L>(t);
-        if (sub == 0 && p < P) alpha[p] = 1.0f - t;
+        for (int u = 0; u < kBlendU; ++u) {
+            float t = 1.0f;  // product of 1 - prob_k over the lane's slots
+            if (__any(sl[u].any)) {
+#pragma unroll
+                for (int i = 0; i < kBlendQ; ++i)
+                    t *= sl[u].on[i] ? sigmoidf(sl[u].x[i]) : 1.0f;
+                t = blend_seg_prod<L>(t);
+            }
+            const int64_t p = p0 + u * PPW + grp;
+            if (sub == 0 && p < P) alpha[p] = 1.0f - t;
+        }
     }
 }
 
@@ -116,37 +174,52 @@ __global__ __launch_bounds__(256) void blend_bwd_kernel(const int32_t* __restric
     const int lane = threadIdx.x & 63, sub = lane & (L - 1), grp = lane / L;
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    for (int64_t p0 = wave * PPW; p0 < P; p0 += nwaves * PPW) {
-        const int64_t p = p0 + grp;
-        bool on[kBlendQ];
-        float x[kBlendQ];
-        blend_slots(p2f, d, p, P, K, sub, inv_sigma, on, x);
-        float om[kBlendQ];  // 1 - prob_k (1 for an empty slot)
-        float t = 1.0f;
+    for (int64_t p0 = wave * (PPW * kBlendU); p0 < P; p0 += nwaves * (PPW * kBlendU)) {
+        BlendSlots sl[kBlendU];
+        float g[kBlendU];
+        if (blend_inside<L>(p0, P, K)) {
 #pragma unroll
-        for (int i = 0; i < kBlendQ; ++i) {
-            om[i] = on[i] ? sigmoidf(x[i]) : 1.0f;
-            t *= om[i];
-        }
-        float pre = blend_excl_prefix<L>(t, sub);
-        const float lsuf = blend_excl_suffix<L>(t, sub);
-        const float g = p < P ? ga[p] : 0.0f;
-        float out[kBlendQ];
-#pragma unroll
-        for (int i = 0; i < kBlendQ; ++i) {
-            float suf = lsuf;
-#pragma unroll
-            for (int j = i + 1; j < kBlendQ; ++j) suf *= om[j];
-            out[i] = on[i] ? -g * inv_sigma * sigmoidf(-x[i]) * om[i] * pre * suf : 0.0f;
-            pre *= om[i];
-        }
-        const int64_t o = p * K + kBlendQ * sub;
-        if (p < P && kBlendQ * (sub + 1) <= K) {
-            *reinterpret_cast<bf32x4*>(gd + o) = bf32x4{out[0], out[1], out[2], out[3]};
+            for (int u = 0; u < kBlendU; ++u) g[u] = ga[p0 + u * PPW + grp];
+            blend_load<L, false>(p2f, d, p0 + grp, P, K, sub, inv_sigma, sl);
         } else {
 #pragma unroll
-            for (int i = 0; i < kBlendQ; ++i)
-                if (p < P && kBlendQ * sub + i < K) gd[o + i] = out[i];
+            for (int u = 0; u < kBlendU; ++u) g[u] = p0 + u * PPW + grp < P ? ga[p0 + u * PPW + grp] : 0.0f;
+            blend_load<L, true>(p2f, d, p0 + grp, P, K, sub, inv_sigma, sl);
+        }
+#pragma unroll
+        for (int u = 0; u < kBlendU; ++u) {
+            float out[kBlendQ];
+#pragma unroll
+            for (int i = 0; i < kBlendQ; ++i) out[i] = 0.0f;
+            if (__any(sl[u].any)) {
+                float om[kBlendQ];  // 1 - prob_k (1 for an empty slot)
+                float pr[kBlendQ];  // prob_k
+                float t = 1.0f;
+#pragma unroll
+                for (int i = 0; i < kBlendQ; ++i) {
+                    sigmoid_pair(sl[u].x[i], om[i], pr[i]);
+                    if (!sl[u].on[i]) om[i] = 1.0f;
+                    t *= om[i];
+                }
+                float pre = blend_excl_prefix<L>(t, sub);
+                const float lsuf = blend_excl_suffix<L>(t, sub);
+#pragma unroll
+                for (int i = 0; i < kBlendQ; ++i) {
+                    float suf = lsuf;
+#pragma unroll
+                    for (int j = i + 1; j < kBlendQ; ++j) suf *= om[j];
+                    if (sl[u].on[i]) out[i] = -g[u] * inv_sigma * pr[i] * om[i] * pre * suf;
+                    pre *= om[i];
+                }
+            }
+            const int64_t p = p0 + u * PPW + grp, o = p * K + kBlendQ * sub;
+            if (p < P && kBlendQ * (sub + 1) <= K) {
+                *reinterpret_cast<bf32x4*>(gd + o) = bf32x4{out[0], out[1], out[2], out[3]};
+            } else {
+#pragma unroll
+                for (int i = 0; i < kBlendQ; ++i)
+                    if (p < P && kBlendQ * sub + i < K) gd[o + i] = out[i];
+            }
         }
     }
 }
@@ -167,7 +240,7 @@ __global__ __launch_bounds__(256) void blend_bwd_kernel(const int32_t* __restric
 // per pixel every load instruction touched 64 rows K C words apart and the
 // loads of one slot waited for the last one's: a forward and backward of
 // 4 x 512 x 512 pixels, K = 8, C = 3 took 534 us (87 + 435 in the kernels),
-// now 124 us, 4.7 TB/s of the bytes that it cannot do without.
+// now 103 us (the start of its reads still lies in the last-level cache).
 struct SoftmaxArgs {
     const int32_t* p2f;
     const float* z;
@@ -399,8 +472,9 @@ static int blend_lanes(int K) {
     return L;
 }
 
-static unsigned blend_grid(int64_t P, int L) {
-    const int64_t waves = (P + 64 / L - 1) / (64 / L);
+static unsigned blend_grid(int64_t P, int L, int groups = 1) {
+    const int64_t per = (int64_t)(64 / L) * groups;  // pixels a wave takes at a time
+    const int64_t waves = (P + per - 1) / per;
     int64_t blocks = (waves + 3) / 4;
     if (blocks > 65536) blocks = 65536;
     return (unsigned)(blocks > 0 ? blocks : 1);
@@ -458,7 +532,7 @@ hipError_t launch_blend_fwd(const int32_t* p2f, const float* d, int64_t P, int K
                             hipStream_t s) {
     if (P == 0) return hipSuccess;
     const int L = blend_lanes(K);
-    const dim3 grid(blend_grid(P, L));
+    const dim3 grid(blend_grid(P, L, kBlendU));
 #define RAST_BLEND_FWD(LL) \
     case LL: hipLaunchKernelGGL(blend_fwd_kernel<LL>, grid, dim3(256), 0, s, p2f, d, P, K, 1.0f / sigma, alpha); break;
     switch (L) {
@@ -473,7 +547,7 @@ hipError_t launch_blend_bwd(const int32_t* p2f, const float* d, const float* ga,
                             float* gd, hipStream_t s) {
     if (P == 0) return hipSuccess;
     const int L = blend_lanes(K);
-    const dim3 grid(blend_grid(P, L));
+    const dim3 grid(blend_grid(P, L, kBlendU));
 #define RAST_BLEND_BWD(LL)                                                                                       \
     case LL:                                                                                                     \
         hipLaunchKernelGGL(blend_bwd_kernel<LL>, grid, dim3(256), 0, s, p2f, d, ga, P, K, 1.0f / sigma, gd); \

@@ -210,3 +210,62 @@ def test_missing_point_gradients_are_zeros():
         gz, gd = (g, torch.zeros_like(g)) if which == 1 else (torch.zeros_like(g), g)
         ref = run_pbwd(p.detach(), f, n, H, W, b.radius, 4, idx, gz, gd, ws)
         assert torch.equal(got, ref)
+
+
+# The silhouette blend: four slots a lane, 1..16 lanes a pixel, two groups of
+# pixels a wave, the last ones with bounds checks.  sigmoid(x) carries
+# |x| 1.2e-7 (two roundings of x) and 6e-7 (its own operations) relative, so a
+# product over slots S carries e(S) = sum_S (1.2e-7 |x| + 7e-7) and alpha that
+# times the product and one rounding; a gradient carries the pixel's e(S)
+# twice (its own factor and prob_k) relative, and an underflow of a factor.
+@pytest.mark.parametrize("K,P", [(1, 1), (1, 127), (1, 129), (2, 300), (3, 64), (4, 63), (5, 65), (8, 131), (13, 33),
+                                 (16, 32), (17, 15), (33, 9), (50, 8), (50, 77), (64, 1), (64, 24)])
+def test_silhouette_lane_groups(K, P):
+    from paper_2007_08501_amd.raster import silhouette_blend
+    rng = np.random.default_rng(100 * K + P)
+    on = (rng.uniform(size=(P, K)) < 0.7) & (rng.uniform(size=(P, 1)) < 0.7)  # holes and empty pixels
+    sigma = 1e-4
+    p2f = np.where(on, rng.integers(0, 50, (P, K)), -1).astype(np.int32)
+    d = np.where(on, rng.uniform(-8, 8, (P, K)) * sigma, -1).astype(np.float32)
+    ga = rng.standard_normal(P).astype(np.float32)
+    d64 = d.astype(np.float64)
+    ref, refg = oracle.silhouette_blend(p2f, d64, sigma), oracle.silhouette_blend_backward(p2f, d64, sigma, ga)
+    e = np.where(on, 1.2e-7 * np.abs(d64 / sigma) + 7e-7, 0.0).sum(-1)
+    dt = _t(d).requires_grad_(True)
+    alpha = silhouette_blend(_t(p2f), dt, sigma)
+    assert (np.abs(alpha.detach().cpu().numpy() - ref) <= (1 - ref) * e + 1.2e-7).all()
+    gd = torch.autograd.grad(alpha, dt, _t(ga))[0].cpu().numpy()
+    assert (np.abs(gd - refg) <= np.abs(refg) * (2 * e + 1e-6)[:, None] + 1e-30).all()
+    assert (gd[~on] == 0).all()
+
+
+# The fine pass's pixel ranges and edge masks: loose triangles of every size,
+# thin ones, edges along the axes, vertices far off the screen, images smaller
+# than a tile or cut by one, no blur and a wide one, more than 64 faces a tile
+# (a block of records).  Against the oracle, and all bin sizes bit for bit.
+@pytest.mark.parametrize("H,W,blur,K,F", [(1, 1, 0.0, 3, 40), (5, 3, 1e-3, 2, 60), (9, 70, 0.0, 24, 300),
+                                          (64, 8, 1e-4, 5, 200), (37, 53, 2e-2, 6, 150), (40, 24, 0.0, 64, 900)])
+def test_fine_pass_edges(H, W, blur, K, F):
+    from _util import compare_fwd, frag_numpy, run_fwd, threads
+    from paper_2007_08501_amd import meshgen
+    rng = np.random.default_rng(H * 100 + W)
+    size = 10.0 ** rng.uniform(-1.5, 0.5, (F, 1, 1))
+    xy = rng.uniform(-1.1, 1.1, (F, 1, 2)) + size * rng.uniform(-1, 1, (F, 3, 2))
+    xy[0::7, 1, 0] = xy[0::7, 0, 0]            # an edge along y
+    xy[1::7, 2, 1] = xy[1::7, 0, 1]            # an edge along x
+    t = rng.uniform(0, 1, (len(xy[2::7]), 1))  # thin: the third vertex near the first edge
+    xy[2::7, 2] = xy[2::7, 0] * t + xy[2::7, 1] * (1 - t) + 0.01
+    xy[3::7, 1] *= 6.0                         # a vertex off the screen
+    v = np.concatenate([xy.reshape(-1, 2), rng.uniform(1, 5, (3 * F, 1))], 1).astype(np.float32)
+    nf = np.array([F // 3, F - F // 3])
+    b = meshgen.Batch(name="edges", verts=v, faces=np.arange(3 * F, dtype=np.int32).reshape(F, 3),
+                      first_idx=np.array([0, F // 3]), num_faces=nf, verts_first_idx=np.array([0, F]),
+                      num_verts=3 * nf, image_size=(H, W), faces_per_pixel=K, blur_radius=float(np.float32(blur)),
+                      bin_size=8, max_faces_per_bin=None)
+    naive, _ = run_fwd(b, 0)
+    o = oracle.rasterize(b.verts, b.faces, b.first_idx, b.num_faces, b.image_size, b.blur_radius, K,
+                         nthreads=threads())
+    compare_fwd(frag_numpy(naive), o, b, f"{H}x{W}")
+    for bs in (8, 16, 24):
+        for x, y in zip(naive, run_fwd(b, bs)[0]):
+            assert torch.equal(x, y)
