@@ -264,7 +264,7 @@ __device__ __forceinline__ bool apply_opts(int opts, float az, float dz1, float 
     return true;
 }
 
-// Does face R count for pixel p, given that p lies in R's grown box?  On
+// Does face R count for pixel p, given that p lies in R's pixel ranges?  On
 // success z is its depth (under the options, if any).
 template <class Rec>
 __device__ __forceinline__ bool face_counts_in_box(const Rec& R, const Pix& p, float blur, float& z, int opts = 0) {

@@ -241,7 +241,7 @@ __device__ __forceinline__ void scan_pixel(const BwdArgs& a, const FaceRec& R, c
     }
 }
 
-// Face f's record (with the blur-grown box), its vertex ids and depths.
+// Face f's record (with its pixel ranges), its vertex ids and depths.
 __device__ __forceinline__ bool load_face(const BwdArgs& a, int64_t f, FaceRec& R, int (&vi)[3], float (&vz)[3],
                                           int& n) {
     vi[0] = a.faces[3 * f];

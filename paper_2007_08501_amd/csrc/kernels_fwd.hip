@@ -312,7 +312,7 @@ constexpr int kChunk = tile_layout::kChunk;
 
 // A face as the tile pass keeps it in LDS: the geometry the pixel tests read
 // (the fields of FaceRec that the evaluation uses), the face id, and the
-// tile's pixels that the face's grown box may cover, as a 64-bit mask
+// tile's pixels in the face's pixel ranges, as a 64-bit mask
 // (bit r*8 + c), which replaces the box.
 struct TileRec {
     double2 pa, ab, ac;

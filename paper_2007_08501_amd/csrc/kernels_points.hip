@@ -2,9 +2,10 @@
 //
 //   pt_count      cloud id, home tile and rank in that tile of every point
 //                 (counts gathered per block in LDS when the tiles fit)
-//   pt_scan_*     exclusive scan of the per-tile counts into tile starts
+//   pt_scan_order exclusive scan of the per-tile counts into tile starts and
+//                 the tile order for the fine pass, heaviest first, in one
+//                 workgroup; more tiles than it holds: pt_scan_*, pt_order_*
 //   pt_scatter    one thread per point: 16-byte record at its sorted slot
-//   pt_order_*    tile order for the fine pass, heaviest first
 //   pt_raster     one wave per 8x8 tile: candidates from the home lists of
 //                 the tiles that can reach it, cull, exact FP64 test over
 //                 each candidate's pixel range, K nearest along z in
@@ -15,7 +16,8 @@
 //                 atomics).  pt_bwd_tile / pt_bwd: the point-major forms
 //                 for large radii
 //   composite     a pixel's slots over the lanes of a wave segment, four per
-//                 lane: Alpha / Norm compositing and its backward
+//                 lane: Alpha / Norm compositing and its backward; feature
+//                 gradients through an LDS table of point rows
 //
 // Paper, Section 3.3: every point is splatted to a disc of radius r in screen
 // space; each pixel keeps the K points nearest along z whose discs cover it,
