@@ -10,8 +10,8 @@
 //                 the tiles that can reach it, cull, exact FP64 test over
 //                 each candidate's pixel range, K nearest along z in
 //                 registers, write the fragments
-//   pt_bwd_slots  one workgroup per home tile (device-sized grid): the ids of
-//                 the tile's pixel box, matched to the tile's own points
+//   pt_bwd_slots  one workgroup per chunk of a home tile's points (device-
+//                 sized grid): the ids of the tile's pixel box, matched to them
 //                 through an LDS hash; each point sums its own slots (no
 //                 atomics).  pt_bwd_tile / pt_bwd: the point-major forms
 //                 for large radii
@@ -29,8 +29,10 @@
 // lists, so it has no capacity limit.
 #include <algorithm>
 
+#include "../../include/rast.h"
 #include "device.hpp"
 #include "launch.hpp"
+#include "point_forms.hpp"
 
 namespace rast {
 
@@ -59,6 +61,8 @@ struct PtArgs {
     int tiles_x, tiles_y, rx, ry;
     int span_x, span_y;     // pixel columns / rows a disc reaches past its first
     int64_t T;              // tiles in the batch
+    PtSlots slots;          // the slot-major backward's chunk
+    int chunk;              // its points (the largest int: the backward takes another form)
     int* hdr;
     int* start;             // T+1: counts, then tile starts
     int* bsum;              // scan block sums
@@ -275,12 +279,15 @@ __global__ __launch_bounds__(256) void pt_scatter_kernel(PtArgs a) {
 // of candidates (the sorted points of the home tiles that can reach it),
 // bucketed on a log scale (two buckets per octave), and a counting sort over
 // the 64 buckets lists the tiles.  Within a bucket the order is arbitrary;
-// the fragments do not depend on it.
+// the fragments do not depend on it.  The first bucket, above every such
+// level, holds the tiles whose own points are more than a chunk of the
+// slot-major backward, which shares those out by chunks.
 __device__ __forceinline__ int pt_tile_bucket(const PtArgs& a, const int* start, int t) {
     const int per_img = a.tiles_x * a.tiles_y;
     const int n = t / per_img;
     const int tt = t - n * per_img;
     const int ty = tt / a.tiles_x, tx = tt - ty * a.tiles_x;
+    if (start[t + 1] - start[t] > a.chunk) return 0;
     int w = 0;
     for (int yy = max(ty - a.ry, 0); yy <= ty; ++yy) {
         const int64_t row = ((int64_t)n * a.tiles_y + yy) * a.tiles_x;
@@ -639,13 +646,13 @@ static PtArgs pt_args(const float* pts, int64_t P, const int64_t* first, const i
     a.r2 = (double)radius * (double)radius;
     a.tiles_x = (W + kTile - 1) / kTile;
     a.tiles_y = (H + kTile - 1) / kTile;
-    // pixel-range spans of a disc: at most floor(r W + 0.03) columns past its
-    // first (the ranges are widened by 0.01 pixel at each end)
-    a.span_x = (int)fmin(floor((double)radius * W + 0.05), (double)W);
-    a.span_y = (int)fmin(floor((double)radius * H + 0.05), (double)H);
+    a.span_x = pt_span(radius, W);
+    a.span_y = pt_span(radius, H);
     a.rx = min((kTile - 1 + a.span_x) / kTile, a.tiles_x - 1);
     a.ry = min((kTile - 1 + a.span_y) / kTile, a.tiles_y - 1);
     a.T = (int64_t)N * a.tiles_x * a.tiles_y;
+    a.slots = pt_slots(P, a.T, (int64_t)(a.span_x + 1) * (a.span_y + 1));
+    a.chunk = a.slots.lg_cap > 0 ? 1 << a.slots.lg_cap : INT32_MAX;
     a.hdr = hdr;
     a.start = start;
     a.bsum = bsum;
@@ -764,7 +771,7 @@ struct PtBwdArgs {
     double r2;
     int tiles_x, tiles_y, span_x, span_y;
     int Kp;      // slots per pixel in LDS (K rounded up to a multiple of 4)
-    int lg_cap;  // slot-major form: log2 of the points per chunk
+    int lg_cap, lg_table;  // slot-major form: log2 of the points per chunk and of the table's entries
     int reuse;
     BinSig sig;
 };
@@ -939,27 +946,23 @@ __global__ __launch_bounds__(kBwdTileThreads) void pt_bwd_tile_kernel(PtBwdArgs 
 // the pixel's offset within the point's pixel range; a point is listed at
 // most once per pixel, so every cell has one writer and no atomics are
 // needed.  Each point then sums its cells in row-major pixel order in FP64,
-// as the point-major form does.  Points beyond the chunk's capacity are taken
-// in further chunks, each rescanning the box.  Bound by the latency of the id
-// rows and the hash probes, so by the workgroups that fit a compute unit's
-// LDS: the capacity (128 to 1,024 points) is the smallest that holds about
-// twice the points of a covered tile's mean (half of the tiles taken as
-// covered).  At 4 x 270 x 401 pixels, 7 x 5 cells, the box-staged form took
-// 181 us; this one 140 with half that capacity, 77 with it (92 before the
-// cells' gradients were requested together), 110 with twice.
-constexpr int kSlotCapMin = 7, kSlotCapMax = 10;  // log2
-constexpr int kSlotLoads = 16;                    // slots loaded per thread before any is used
-constexpr int kCellLoads = 8;                     // cells whose gradients are requested together
+// as the point-major form does.  Points beyond the chunk's capacity (128 to
+// 1,024 points, pt_slots) are further chunks, each reading the box again.
+// Bound by the latency of the id rows and the hash probes, so by the workgroups
+// that a compute unit holds: six by the registers.
+constexpr int kSlotLoads = 16;  // slots loaded per thread before any is used
+constexpr int kCellLoads = 6;   // cells whose gradients are requested together
 constexpr uint8_t kNoSlot = 0xff;
-constexpr size_t kSlotLdsMax = 64 * 1024;
+static_assert(RAST_KMAX < kNoSlot, "a cell holds a slot number or kNoSlot");
+static_assert(kPtTile == kTile, "the rule's tiles are the kernels'");
 
 __device__ __forceinline__ int slot_hash(int id, int lg_hash) {
     return (int)(((uint32_t)id * 2654435761u) >> (32 - lg_hash));
 }
 
-__device__ __forceinline__ void pt_bwd_slots_tile(const PtBwdArgs& b, int t, int2* htab, int* prc, uint8_t* cell) {
-    const int lo = b.start[t], hi = b.start[t + 1];
-    if (lo == hi) return;  // uniform: no point has this home tile
+// One chunk: the points [c_lo, hi) of tile t, at most 1 << b.lg_cap of them taken.
+__device__ __forceinline__ void pt_bwd_slots_chunk(const PtBwdArgs& b, int t, int c_lo, int hi, int2* htab, int* prc,
+                                                   uint8_t* cell) {
     const int per_img = b.tiles_x * b.tiles_y;
     const int n = t / per_img;
     const int rem = t - n * per_img;
@@ -972,143 +975,173 @@ __device__ __forceinline__ void pt_bwd_slots_tile(const PtBwdArgs& b, int t, int
     const int rowl = bw * K, nbox = bh * rowl;
     const float inv_rowl = 1.0f / (float)rowl, inv_k = 1.0f / (float)K;
     const double dW = (double)b.W, dH = (double)b.H, rW = 1.0 / dW, rH = 1.0 / dH;
-    const int cap = 1 << b.lg_cap, lg_hash = b.lg_cap + 1, nhash = 1 << lg_hash;
-    for (int c_lo = lo; c_lo < hi; c_lo += cap) {
-        const int nloc = min(cap, hi - c_lo);
-        for (int i = threadIdx.x; i < nhash; i += kBwdTileThreads) htab[i] = make_int2(-1, 0);
-        uint32_t* cw = reinterpret_cast<uint32_t*>(cell);
-        for (int i = threadIdx.x; i < (nloc * ncell + 3) / 4; i += kBwdTileThreads) cw[i] = 0xffffffffu;
-        __syncthreads();
-        for (int i = threadIdx.x; i < nloc; i += kBwdTileThreads) {
-            const float4 rec = b.sorted[c_lo + i];
-            const int id = __float_as_int(rec.w);
-            int c0, c1, r0, r1;
-            disc_pixels(rec.x, rec.y, b.r, b.H, b.W, c0, c1, r0, r1);
-            prc[i] = max(r0, y0) | (max(c0, x0) << 16);
-            // ids are distinct, and the table is at least half empty
-            for (int h = slot_hash(id, lg_hash);; h = (h + 1) & (nhash - 1)) {
-                if (atomicCAS(&htab[h].x, -1, id) == -1) {
-                    htab[h].y = i;
-                    break;
-                }
+    const int nloc = min(1 << b.lg_cap, hi - c_lo);
+    // a table for these points: an eighth to a quarter full, if there is room
+    const int lg_hash = min(b.lg_table, max(8, 35 - __clz(nloc - 1))), nhash = 1 << lg_hash;
+    for (int i = threadIdx.x; i < nhash; i += kBwdTileThreads) htab[i] = make_int2(-1, 0);
+    uint32_t* cw = reinterpret_cast<uint32_t*>(cell);
+    for (int i = threadIdx.x; i < (nloc * ncell + 3) / 4; i += kBwdTileThreads) cw[i] = 0xffffffffu;
+    __syncthreads();
+    for (int i = threadIdx.x; i < nloc; i += kBwdTileThreads) {
+        const float4 rec = b.sorted[c_lo + i];
+        const int id = __float_as_int(rec.w);
+        int c0, c1, r0, r1;
+        disc_pixels(rec.x, rec.y, b.r, b.H, b.W, c0, c1, r0, r1);
+        prc[i] = max(r0, y0) | (max(c0, x0) << 16);
+        // ids are distinct, and the table is at least half empty
+        for (int h = slot_hash(id, lg_hash);; h = (h + 1) & (nhash - 1)) {
+            if (atomicCAS(&htab[h].x, -1, id) == -1) {
+                htab[h].y = i;
+                break;
             }
         }
-        __syncthreads();
-        for (int e0 = 0; e0 < nbox; e0 += kSlotLoads * kBwdTileThreads) {
-            int vi[kSlotLoads];
+    }
+    __syncthreads();
+    for (int e0 = 0; e0 < nbox; e0 += kSlotLoads * kBwdTileThreads) {
+        int vi[kSlotLoads];
 #pragma unroll
-            for (int j = 0; j < kSlotLoads; ++j) {
-                const int e = e0 + j * kBwdTileThreads + (int)threadIdx.x;
-                vi[j] = -1;
-                if (e < nbox) {
-                    const int r = small_div(e, rowl, inv_rowl);
-                    const int q = e - r * rowl;
-                    const int64_t g = ((int64_t)n * b.H + y0 + r) * b.W * K + (int64_t)x0 * K + q;
-                    vi[j] = b.idx[g];
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < kSlotLoads; ++j) {
-                const int id = vi[j];
-                if (id < 0) continue;
-                int local = -1;
-                for (int h = slot_hash(id, lg_hash);; h = (h + 1) & (nhash - 1)) {
-                    const int2 en = htab[h];
-                    if (en.x == id) {
-                        local = en.y;
-                        break;
-                    }
-                    if (en.x < 0) break;
-                }
-                if (local < 0) continue;  // another tile's point, or another chunk's
-                const int e = e0 + j * kBwdTileThreads + (int)threadIdx.x;
+        for (int j = 0; j < kSlotLoads; ++j) {
+            const int e = e0 + j * kBwdTileThreads + (int)threadIdx.x;
+            vi[j] = -1;
+            if (e < nbox) {
                 const int r = small_div(e, rowl, inv_rowl);
                 const int q = e - r * rowl;
-                const int c = small_div(q, K, inv_k);
-                const int k = q - c * K;
-                const int pr = prc[local];
-                const int dr = y0 + r - (pr & 0xffff), dc = x0 + c - (pr >> 16);
-                if (dr < 0 || dr >= ey || dc < 0 || dc >= ex) continue;  // outside the point's pixel range
-                cell[local * ncell + dr * ex + dc] = (uint8_t)k;
+                const int64_t g = ((int64_t)n * b.H + y0 + r) * b.W * K + (int64_t)x0 * K + q;
+                vi[j] = b.idx[g];
             }
         }
-        __syncthreads();
-        for (int i = threadIdx.x; i < nloc; i += kBwdTileThreads) {
-            const float4 rec = b.sorted[c_lo + i];
-            const int id = __float_as_int(rec.w);
-            const int pr = prc[i];
-            const int pr0 = pr & 0xffff, pc0 = pr >> 16;
-            const double x = rec.x, y = rec.y;
-            double gx = 0.0, gy = 0.0, gzs = 0.0;
-            const uint8_t* mine = cell + i * ncell;
-            // the cells in row-major order, eight at a time, their gradients
-            // all requested before the first is used
-            int dr = 0, dc = 0;
-            for (int c0 = 0; c0 < ncell; c0 += kCellLoads) {
-                float vz[kCellLoads], vd[kCellLoads];
-                int at[kCellLoads];  // row << 16 | column within the range, or -1
 #pragma unroll
-                for (int j = 0; j < kCellLoads; ++j) {
-                    const int k = c0 + j < ncell ? (int)mine[c0 + j] : (int)kNoSlot;
-                    at[j] = k == kNoSlot ? -1 : (dr << 16) | dc;
-                    vz[j] = vd[j] = 0.0f;
-                    if (k != kNoSlot) {
-                        const int64_t g = (((int64_t)n * b.H + pr0 + dr) * b.W + pc0 + dc) * K + k;
-                        if (b.gz) vz[j] = b.gz[g];
-                        if (b.gd) vd[j] = b.gd[g];
-                    }
-                    if (++dc == ex) {
-                        dc = 0;
-                        ++dr;
-                    }
+        for (int j = 0; j < kSlotLoads; ++j) {
+            const int id = vi[j];
+            if (id < 0) continue;
+            int local = -1;
+            for (int h = slot_hash(id, lg_hash);; h = (h + 1) & (nhash - 1)) {
+                const int2 en = htab[h];
+                if (en.x == id) {
+                    local = en.y;
+                    break;
                 }
-#pragma unroll
-                for (int j = 0; j < kCellLoads; ++j) {
-                    if (at[j] < 0) continue;
-                    const double px = pix_coord_rcp(pc0 + (at[j] & 0xffff), dW, rW);
-                    const double py = pix_coord_rcp(pr0 + (at[j] >> 16), dH, rH);
-                    gzs += (double)vz[j];
-                    const double gg = 2.0 * (double)vd[j];
-                    gx += gg * (x - px);
-                    gy += gg * (y - py);
-                }
+                if (en.x < 0) break;
             }
-            pt_write_grad(b, id, gx, gy, gzs);
+            if (local < 0) continue;  // another tile's point, or another chunk's
+            const int e = e0 + j * kBwdTileThreads + (int)threadIdx.x;
+            const int r = small_div(e, rowl, inv_rowl);
+            const int q = e - r * rowl;
+            const int c = small_div(q, K, inv_k);
+            const int k = q - c * K;
+            const int pr = prc[local];
+            const int dr = y0 + r - (pr & 0xffff), dc = x0 + c - (pr >> 16);
+            if (dr < 0 || dr >= ey || dc < 0 || dc >= ex) continue;  // outside the point's pixel range
+            cell[local * ncell + dr * ex + dc] = (uint8_t)k;
         }
-        __syncthreads();  // the next chunk or tile clears the tables
     }
+    __syncthreads();
+    for (int i = threadIdx.x; i < nloc; i += kBwdTileThreads) {
+        const float4 rec = b.sorted[c_lo + i];
+        const int id = __float_as_int(rec.w);
+        const int pr = prc[i];
+        const int pr0 = pr & 0xffff, pc0 = pr >> 16;
+        const double x = rec.x, y = rec.y;
+        double gx = 0.0, gy = 0.0, gzs = 0.0;
+        const uint8_t* mine = cell + i * ncell;
+        // the cells in row-major order, eight at a time, their gradients
+        // all requested before the first is used
+        int dr = 0, dc = 0;
+        for (int c0 = 0; c0 < ncell; c0 += kCellLoads) {
+            float vz[kCellLoads], vd[kCellLoads];
+            int at[kCellLoads];  // row << 16 | column within the range, or -1
+#pragma unroll
+            for (int j = 0; j < kCellLoads; ++j) {
+                const int k = c0 + j < ncell ? (int)mine[c0 + j] : (int)kNoSlot;
+                at[j] = k == kNoSlot ? -1 : (dr << 16) | dc;
+                vz[j] = vd[j] = 0.0f;
+                if (k != kNoSlot) {
+                    const int64_t g = (((int64_t)n * b.H + pr0 + dr) * b.W + pc0 + dc) * K + k;
+                    if (b.gz) vz[j] = b.gz[g];
+                    if (b.gd) vd[j] = b.gd[g];
+                }
+                if (++dc == ex) {
+                    dc = 0;
+                    ++dr;
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < kCellLoads; ++j) {
+                if (at[j] < 0) continue;
+                const double px = pix_coord_rcp(pc0 + (at[j] & 0xffff), dW, rW);
+                const double py = pix_coord_rcp(pr0 + (at[j] >> 16), dH, rH);
+                gzs += (double)vz[j];
+                const double gg = 2.0 * (double)vd[j];
+                gx += gg * (x - px);
+                gy += gg * (y - py);
+            }
+        }
+        pt_write_grad(b, id, gx, gy, gzs);
+    }
+    __syncthreads();  // the next chunk clears the tables
 }
 
+// A device-sized grid takes the chunks in turn: first those of the tiles that
+// have several (the first bucket of the tile order), placed by a running sum
+// over 256 of these tiles at a time, then the other tiles, a chunk each.
+// A tile's chunks one after the other in one workgroup left a cloud on
+// 16 x 16 pixels to a few compute units (4 clouds of 20,000 points there,
+// 9 cells: 366 us at K = 8 and 1,300 at K = 50, now 17 and 30).
 __global__ __launch_bounds__(kBwdTileThreads) void pt_bwd_slots_kernel(PtBwdArgs b) {
     if (!pt_bwd_usable(b)) return;
     int2* htab = reinterpret_cast<int2*>(bwd_lds);
-    int* prc = reinterpret_cast<int*>(htab + (2 << b.lg_cap));
+    int* prc = reinterpret_cast<int*>(htab + (1 << b.lg_table));
     uint8_t* cell = reinterpret_cast<uint8_t*>(prc + (1 << b.lg_cap));
-    const int ntile = b.ohist[kPtOrderBuckets - 2];
-    for (int j = blockIdx.x; j < ntile; j += gridDim.x) pt_bwd_slots_tile(b, b.order[j], htab, prc, cell);
-}
-
-// LDS bytes of the slot-major backward and its chunks' capacity, or 0 when
-// the cells of the smallest chunk do not fit.
-static size_t pt_bwd_slots_lds_bytes(const PtArgs& a, int& lg_cap) {
-    const int64_t ncell = (int64_t)(a.span_x + 1) * (a.span_y + 1);
-    if (a.K >= kNoSlot) return 0;
-    lg_cap = kSlotCapMin;
-    while (lg_cap < kSlotCapMax && 4 * a.P > a.T << lg_cap) ++lg_cap;
-    for (; lg_cap >= kSlotCapMin; --lg_cap) {
-        const size_t cap = (size_t)1 << lg_cap;
-        const size_t bytes = cap * (2 * sizeof(int2) + sizeof(int)) + ((cap * ncell + 3) & ~(size_t)3);
-        if (bytes <= kSlotLdsMax) return bytes;
+    int* word = reinterpret_cast<int*>(bwd_lds);  // (between chunks)
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, cap = 1 << b.lg_cap;
+    const int nmany = b.ohist[0], ntile = b.ohist[kPtOrderBuckets - 2];
+    int next = blockIdx.x;  // the workgroup's next chunk, counted from the first of the tiles summed last
+    int f0 = -kBwdTileThreads, total = 0;  // the first of those tiles, their chunks
+    int mine = 0, upto = 0;                // chunks of the thread's tile, of the tiles up to and with it
+    for (;;) {  // (every condition is uniform over the workgroup)
+        while (next >= total && f0 + kBwdTileThreads < nmany) {
+            next -= total;
+            f0 += kBwdTileThreads;
+            mine = 0;
+            if (f0 + tid < nmany) {
+                const int t = b.order[f0 + tid];
+                mine = (b.start[t + 1] - b.start[t] + cap - 1) >> b.lg_cap;
+            }
+            upto = mine;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int u = __shfl_up(upto, o);
+                if (lane >= o) upto += u;
+            }
+            if (lane == 63) word[w] = upto;
+            __syncthreads();
+            total = 0;
+            for (int i = 0; i < kBwdTileThreads / 64; ++i) {
+                if (i == w) upto += total;
+                total += word[i];
+            }
+            __syncthreads();
+        }
+        int t, c_lo;
+        if (next < total) {
+            if (next < upto && next >= upto - mine) {  // (one thread)
+                word[0] = b.order[f0 + tid];
+                word[1] = next - (upto - mine);
+            }
+            __syncthreads();
+            t = word[0];
+            c_lo = b.start[t] + (word[1] << b.lg_cap);
+            __syncthreads();
+        } else {
+            const int64_t j = (int64_t)nmany + (next - total);
+            if (j >= ntile) break;
+            t = b.order[j];
+            c_lo = b.start[t];
+        }
+        next += gridDim.x;
+        const int hi = b.start[t + 1];
+        if (c_lo < hi) pt_bwd_slots_chunk(b, t, c_lo, hi, htab, prc, cell);
     }
-    return 0;
-}
-
-// LDS bytes of the box-staged backward, or 0 when it does not fit.
-static size_t pt_bwd_lds_bytes(const PtArgs& a, int span_x, int span_y, bool gz, bool gd) {
-    const int64_t bw = min(kTile + span_x, a.W), bh = min(kTile + span_y, a.H);
-    const int64_t Kp = (a.K + 3) & ~3;
-    const int64_t bytes = bw * bh * Kp * 4 * (1 + (gz ? 1 : 0) + (gd ? 1 : 0));
-    return bytes <= 65536 ? (size_t)bytes : 0;
 }
 
 hipError_t launch_points_bwd(const float* pts, int64_t P, const int64_t* first, const int64_t* np, int N, int H,
@@ -1152,11 +1185,13 @@ hipError_t launch_points_bwd(const float* pts, int64_t P, const int64_t* first, 
     b.Kp = (K + 3) & ~3;
     b.reuse = reuse ? 1 : 0;
     b.sig = sig;
-    const size_t slds = pt_bwd_slots_lds_bytes(a, b.lg_cap);
-    const size_t lds = pt_bwd_lds_bytes(a, a.span_x, a.span_y, gz != nullptr, gd != nullptr);
+    b.lg_cap = a.slots.lg_cap;
+    b.lg_table = a.slots.lg_table;
+    const size_t slds = a.slots.bytes;
+    const size_t lds = pt_box_bytes(H, W, K, a.span_x, a.span_y, gz != nullptr, gd != nullptr);
     if (eb) (void)hipEventRecord(eb, s);
     if (slds > 0) {
-        const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(8, kLdsPerCu / (int64_t)slds));
+        const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(kSlotGroups, kLdsPerCu / (int64_t)slds));
         const int64_t grid = std::min<int64_t>(a.T, (int64_t)std::max(n_cus, 1) * per_cu);
         hipLaunchKernelGGL(pt_bwd_slots_kernel, dim3((unsigned)grid), dim3(kBwdTileThreads), slds, s, b);
     } else if (lds > 0) {

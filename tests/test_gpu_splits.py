@@ -1,0 +1,67 @@
+"""GPU: work that one workgroup or lane would hold up, split over the chip, and
+the forms behind a rule on sizes, against the FP64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def _t(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def _point_backward(pts, sizes, H, W, radius, K, gz=True, gd=True, seed=0):
+    """Gradient of the fragments' own ids against the oracle's; with the
+    forward's workspace and with a new one."""
+    from test_gpu_points import run_pbwd, run_pfwd
+    from _util import threads
+    from paper_2007_08501_amd import _lib
+    rng = np.random.default_rng(seed)
+    sizes = np.asarray(sizes, np.int64)
+    first = np.concatenate([[0], np.cumsum(sizes)[:-1]]).astype(np.int64)
+    N = len(sizes)
+    p, f, n = _t(pts), _t(first), _t(sizes)
+    idx, _, _, ws = run_pfwd(p, f, n, H, W, radius, K)
+    up = [rng.standard_normal((N, H, W, K)).astype(np.float32) if on else None for on in (gz, gd)]
+    dev = [None if u is None else _t(u) for u in up]
+    got = run_pbwd(p, f, n, H, W, radius, K, idx, *dev, ws, _lib.RAST_BWD_REUSE_FORWARD)
+    ws2 = _lib.alloc_workspace(_lib.rast_points_workspace_size(N, H, W, len(pts)), "cuda")
+    assert torch.equal(got, run_pbwd(p, f, n, H, W, radius, K, idx, *dev, ws2, 0))
+    full = [np.zeros((N, H, W, K), np.float32) if u is None else u for u in up]
+    ref = oracle.points_backward(pts, (H, W), idx.cpu().numpy(), *full, nthreads=threads())
+    assert (idx >= 0).sum() > 0 and np.abs(ref).max() > 0
+    # (FP64 sums, rounded once)
+    assert np.abs(got.cpu().numpy() - ref).max() <= 1e-6 * np.abs(ref).max()
+
+
+def _in_tile(rng, m, H, W, tx, ty):
+    """m points whose one-pixel discs start in tile (tx, ty): pixel columns and rows 1 to 6 of it."""
+    c = rng.uniform(8 * tx + 1.5, 8 * tx + 6.5, m)
+    r = rng.uniform(8 * ty + 1.5, 8 * ty + 6.5, m)
+    return np.c_[1 - 2 * c / W, 1 - 2 * r / H, rng.uniform(0.5, 3, m)].astype(np.float32)
+
+
+# Tiles of more points than a chunk holds (512 for the 9 cells here): exactly
+# a chunk, one point more, several chunks, beside tiles of one chunk and none.
+@pytest.mark.parametrize("counts", [[512], [513], [1024, 1, 511], [3000, 700, 513, 40], [512, 512, 5000]])
+def test_point_backward_tiles_of_several_chunks(counts):
+    rng = np.random.default_rng(sum(counts))
+    H, W, K = 64, 64, 40
+    pts = np.concatenate([_in_tile(rng, m, H, W, 1 + 2 * i, 1 + i) for i, m in enumerate(counts)])
+    _point_backward(pts, [len(pts)], H, W, float(np.float32(2.0 / W)), K)
+
+
+# More than 256 tiles of several chunks (256 points for discs of 14 pixels a
+# side, 128 for 20), so that their chunks are summed in several turns, and more
+# chunks than workgroups; several images, one without points.
+@pytest.mark.parametrize("rpx,K", [(13.0, 2), (19.0, 1)])
+def test_point_backward_many_tiles_of_several_chunks(rpx, K):
+    rng = np.random.default_rng(int(rpx))
+    H = W = 104
+    sizes = [60000, 0, 70000, 50000]
+    n = sum(sizes)
+    pts = np.c_[rng.uniform(-0.99, 0.99, (n, 2)), rng.uniform(0.5, 3, n)].astype(np.float32)
+    _point_backward(pts, sizes, H, W, float(np.float32(rpx / W)), K)
