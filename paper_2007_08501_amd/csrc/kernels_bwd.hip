@@ -6,7 +6,7 @@
 // sums the chain rule into the nine vertex coordinates of its face.  Two
 // forms.  The binned form (the forward's bins): one workgroup per cell of
 // pixels, the cell's faces in LDS, FP64 sums per face (described with its
-// kernels below).  The per-face form (no bins): sixteen lanes scan the pixels
+// kernels below).  The per-face form (no bins): a group of lanes scans the pixels
 // of face f's blur-grown bounding box (the only pixels whose slots the
 // forward can fill with f), find the slot holding f in each and sum in
 // registers -- no atomics per slot; a workgroup then merges its faces'
@@ -310,26 +310,30 @@ __device__ __forceinline__ void flush_table(float* grad, const int* keys, const 
     }
 }
 
-// A face's box is scanned by kFaceLanes lanes side by side (consecutive
-// pixels of a row: consecutive id lists), whose sums meet in a butterfly; a
-// group of lanes takes `per` faces in turn, a workgroup 16 per of them, and
+// A face's box is scanned by kLanes lanes side by side (consecutive pixels of
+// a row: consecutive id lists), whose sums meet in a butterfly; a group of
+// lanes takes `per` faces in turn, a workgroup 256 / kLanes * per of them, and
 // `per` is chosen so that small meshes still fill the chip.  Bound by the
-// latency of the id lists' reads.  With one lane per face 2,880 faces were 12
-// workgroups and each lane walked its 80 or so pixels alone: 330 us, now 26 us
-// (three meshes of up to 1,280 faces, 130 x 75 pixels, K = 5).
-constexpr int kFaceLanes = 16;
-constexpr int kFaceGroups = kBwdBlock / kFaceLanes;
-constexpr int kFaceMaxPer = kBwdBlock / kFaceGroups;  // 3 x 256 vertices at most fit the table
-static_assert(3 * kFaceGroups * kFaceMaxPer <= kHash, "a workgroup's vertices fit its table");
+// latency of the id lists' reads where boxes are large or faces few, by the
+// faces' records, which every lane of a group builds, where boxes are small:
+// four lanes there, else sixteen (launch_backward has the rule).  With one lane
+// per face 2,880 faces were 12 workgroups and each lane walked its 80 or so
+// pixels alone: 330 us, now 26 (three meshes of up to 1,280 faces, 130 x 75
+// pixels, K = 5).
+constexpr int64_t kManyFaces = 65536;
+constexpr int kFaceMax = kBwdBlock;  // faces of a workgroup at most: their 3 x 256 vertices fit the table
+static_assert(3 * kFaceMax <= kHash, "a workgroup's vertices fit its table");
 
+template <int kLanes>
 __global__ __launch_bounds__(kBwdBlock) void bwd_faces_kernel(BwdArgs a, int per) {
+    constexpr int kGroups = kBwdBlock / kLanes;
     __shared__ int keys[kHash];
     __shared__ double vals[3 * kHash];
     clear_table(keys, vals);
     __syncthreads();
-    const int sub = threadIdx.x & (kFaceLanes - 1), grp = threadIdx.x / kFaceLanes;
+    const int sub = threadIdx.x & (kLanes - 1), grp = threadIdx.x / kLanes;
     for (int it = 0; it < per; ++it) {
-        const int64_t f = ((int64_t)blockIdx.x * per + it) * kFaceGroups + grp;
+        const int64_t f = ((int64_t)blockIdx.x * per + it) * kGroups + grp;
         FaceRec R;
         int vi[3];
         float vz[3];
@@ -347,17 +351,17 @@ __global__ __launch_bounds__(kBwdBlock) void bwd_faces_kernel(BwdArgs a, int per
 #pragma unroll
         for (int j = 0; j < 3; ++j) g.gx[j] = g.gy[j] = g.gzv[j] = 0.0f;
         const float inv_w = 1.0f / (float)w;
-        for (int q = sub; q < (int)area; q += kFaceLanes) {
+        for (int q = sub; q < (int)area; q += kLanes) {
             const int dr = stage_pixel(q, inv_w);  // q / w (q <= kBigArea: the estimate is exact)
             scan_pixel(a, R, vz, (int)f, n, r0 + dr, c0 + q - dr * w, g);
         }
 #pragma unroll
-        for (int o = kFaceLanes / 2; o > 0; o >>= 1) {
+        for (int o = kLanes / 2; o > 0; o >>= 1) {
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
-                g.gx[j] += __shfl_xor(g.gx[j], o, kFaceLanes);
-                g.gy[j] += __shfl_xor(g.gy[j], o, kFaceLanes);
-                g.gzv[j] += __shfl_xor(g.gzv[j], o, kFaceLanes);
+                g.gx[j] += __shfl_xor(g.gx[j], o, kLanes);
+                g.gy[j] += __shfl_xor(g.gy[j], o, kLanes);
+                g.gzv[j] += __shfl_xor(g.gzv[j], o, kLanes);
             }
         }
         if (sub < 3) {
@@ -981,12 +985,18 @@ hipError_t launch_backward(const float* verts, int64_t V, const int32_t* faces, 
         return hipGetLastError();
     }
     if (eb) (void)hipEventRecord(eb, s);
+    // Lanes a face: four for many faces with fewer than two pixels each, else
+    // sixteen.  One / four / sixteen lanes, backward alone, K = 4: 20,480 faces
+    // on 64 images of 128 x 128 pixels 437 / 139 / 91 us; 40,960 on 8 of 256 x
+    // 256 260 / 88 / 80; 81,920 on 4 of 64 x 64 29 / 27 / 42; 163,840 on 2 of 512 x
+    // 512 321 / 210 / 211; 327,680 on one of 256 x 256 84 / 85 / 143.  And the
     // faces a group of lanes takes in turn: as many as merge in one table once
-    // there are workgroups enough (1,024, four a compute unit)
-    int per = (int)(F / (1024 * kFaceGroups));
-    per = per < 1 ? 1 : (per > kFaceMaxPer ? kFaceMaxPer : per);
-    const int64_t fpw = (int64_t)per * kFaceGroups;
-    hipLaunchKernelGGL(bwd_faces_kernel, dim3((unsigned)((F + fpw - 1) / fpw)), dim3(kBwdBlock), 0, s, a, per);
+    // there are workgroups enough (1,024, four a compute unit).
+    const int lanes = F >= kManyFaces && (int64_t)N * H * W < 2 * F ? 4 : 16, groups = kBwdBlock / lanes;
+    const int per = (int)std::min<int64_t>(std::max<int64_t>(F / (1024 * groups), 1), kFaceMax / groups);
+    const int64_t fpw = (int64_t)per * groups;
+    auto scan = lanes == 16 ? bwd_faces_kernel<16> : bwd_faces_kernel<4>;
+    hipLaunchKernelGGL(scan, dim3((unsigned)((F + fpw - 1) / fpw)), dim3(kBwdBlock), 0, s, a, per);
     hipLaunchKernelGGL(bwd_big_faces_kernel, dim3(512), dim3(kBwdBlock), 0, s, a);
     if (ee) (void)hipEventRecord(ee, s);
     return hipGetLastError();

@@ -65,3 +65,32 @@ def test_point_backward_many_tiles_of_several_chunks(rpx, K):
     n = sum(sizes)
     pts = np.c_[rng.uniform(-0.99, 0.99, (n, 2)), rng.uniform(0.5, 3, n)].astype(np.float32)
     _point_backward(pts, sizes, H, W, float(np.float32(rpx / W)), K)
+
+
+# The per-face backward takes four lanes a face from 65,536 faces with fewer than
+# two pixels each, with two faces a group of lanes in turn from 131,072, else
+# sixteen: a face fewer, exactly as many, part workgroups, boxes of a few pixels
+# and (the coarse mesh beside the fine one) of more than 256.  The suite's
+# gradient bound.
+@pytest.mark.parametrize("faces,n,image,K", [(65535, 1, 24, 4), (65536, 1, 24, 3), (70001, 1, 40, 5),
+                                             (131072, 2, 20, 2), (150003, 2, 33, 4)])
+def test_per_face_backward_lanes(faces, n, image, K):
+    from _util import compare_grad, run_bwd, threads, tie_masked_grads
+    from paper_2007_08501_amd import meshgen
+    b = meshgen.make_config(2, n_override=n + 1, level_override=6, image_override=image)
+    coarse = meshgen.make_config(2, n_override=1, level_override=0)
+    per = b.num_faces[0]
+    count = np.array([min(per, faces - 20 - i * per) for i in range(n)] + [20], np.int64)
+    first = np.concatenate([[0], np.cumsum(count)[:-1]])
+    b.faces = np.concatenate([b.faces[i * per:i * per + count[i]] for i in range(n)]
+                             + [coarse.faces + len(b.verts)]).astype(b.faces.dtype)
+    b.verts = np.concatenate([b.verts, coarse.verts]).astype(np.float32)
+    b.first_idx, b.num_faces, b.faces_per_pixel = first, count, K
+    assert len(b.faces) == faces
+    o = oracle.rasterize(b.verts, b.faces, b.first_idx, b.num_faces, b.image_size, b.blur_radius, K,
+                         nthreads=threads())
+    g = tie_masked_grads(b, o["p2f"], *meshgen.upstream_grads(b))
+    ref = oracle.backward(b.verts, b.faces, b.image_size, o["p2f"], *g)
+    assert (o["p2f"] >= faces - 20).any()
+    got = run_bwd(b, _t(o["p2f"].astype(np.int32)), *g, bs=0)
+    compare_grad(got.cpu().numpy(), ref, f"{faces} faces")
