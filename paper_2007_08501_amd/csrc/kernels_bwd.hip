@@ -271,6 +271,11 @@ __device__ __forceinline__ uint32_t vhash(int v) {
     return (((((uint32_t)v >> 4) * 2654435761u) >> (32 - 6)) << 4) | ((uint32_t)v & 15u);
 }
 static_assert(kHash == 1 << 10, "vhash yields 10 bits");
+// A run that meets another's entries goes on in the next run's, and a step that
+// is odd visits the whole table: by single entries such runs walked through each
+// other up to sixteen entries a vertex (40,960 faces, 8 meshes: the face sum 11.7
+// us, 8.6 before vertices were kept in runs, now 6.5).
+constexpr int kHashStep = 17;
 
 // Merges (vertex, grad3) into the workgroup's LDS table; falls back to a global
 // atomic when the table is full.  The sums are FP64: LDS has FP64 atomics in
@@ -286,7 +291,7 @@ __device__ __forceinline__ void lds_add(int* keys, double* vals, float* grad, in
             atomicAdd(&vals[3 * h + 2], (double)z);
             return;
         }
-        h = (h + 1) & (kHash - 1);
+        h = (h + kHashStep) & (kHash - 1);
     }
     atomicAdd(grad + 3 * (int64_t)v + 0, x);
     atomicAdd(grad + 3 * (int64_t)v + 1, y);
@@ -684,12 +689,13 @@ struct CellGeo {
 //
 // Bound by latency and vector issue about alike: two dependent round trips
 // per cell (ids, then records; ids, then gradients), overlapped by the six
-// workgroups per compute unit that the LDS block (26.6 KB) and the registers
-// (80) allow; five of each took 711 us instead of 681 (4 x 1024 x 1024 pixels,
-// K = 16) and 448 instead of 419 (32 x 512 x 512, K = 8).  Both passes and
-// their preparation: 1015 -> 784 us (K = 16), 440 -> 446 us (K = 8, bins of 16
-// pixels) and 88 -> 48 us (8 x 256 x 256, K = 4, bins of 32), against bins
-// as cells with fixed-point sums and a second, rescue pass.
+// workgroups per compute unit that the LDS block (26.6 KB) allows and that the
+// registers (80) are held to, at the price of a few spilled (2, with options 5);
+// five of each took 711 us instead of 681 (4 x 1024 x 1024 pixels, K = 16) and
+// 448 instead of 419 (32 x 512 x 512, K = 8).  The whole backward, replayed:
+// 895 -> 648 us (K = 16), 428 -> 418 (K = 8, bins of 16 pixels), 53 -> 51 (8 x
+// 256 x 256, K = 8, bins of 16) and 80 -> 41 (K = 4, bins of 32), against bins as
+// cells with fixed-point sums and a second, rescue pass.
 template <bool kOpts>
 __global__ __launch_bounds__(kP1Threads) __attribute__((amdgpu_waves_per_eu(6, 8)))
 void bwd_cells_kernel(BwdArgs a) {

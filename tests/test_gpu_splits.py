@@ -94,3 +94,37 @@ def test_per_face_backward_lanes(faces, n, image, K):
     assert (o["p2f"] >= faces - 20).any()
     got = run_bwd(b, _t(o["p2f"].astype(np.int32)), *g, bs=0)
     compare_grad(got.cpu().numpy(), ref, f"{faces} faces")
+
+
+# The vertex table of the backward's face sums (1,024 entries, the faces of a
+# workgroup): 768 vertices of their own per 256 faces, their ids scattered over
+# a large range, in runs of sixteen, in part runs that start the same bucket, and
+# all alike in their low bits.  The suite's gradient bound.
+@pytest.mark.parametrize("bs", [0, 8])
+@pytest.mark.parametrize("ids", ["scattered", "runs", "part", "strided"])
+def test_backward_vertex_table(ids, bs):
+    from _util import compare_grad, run_bwd, threads, tie_masked_grads
+    from paper_2007_08501_amd import meshgen
+    rng = np.random.default_rng(len(ids))
+    F, V, H, W, K = 800, 60000, 30, 44, 6
+    n = 3 * F
+    if ids == "scattered":
+        at = rng.permutation(V)[:n]
+    elif ids == "strided":
+        at = 16 * rng.permutation(n)
+    else:
+        m = 16 if ids == "runs" else 5
+        at = (16 * rng.permutation(V // 16)[:-(-n // m), None] + np.arange(m)).ravel()[:n]
+    xy = rng.uniform(-1, 1, (F, 1, 2)) + 10.0 ** rng.uniform(-1.5, -0.3, (F, 1, 1)) * rng.uniform(-1, 1, (F, 3, 2))
+    v = np.zeros((V, 3), np.float32)
+    v[at] = np.concatenate([xy.reshape(-1, 2), rng.uniform(1, 5, (n, 1))], 1)
+    b = meshgen.Batch(name="table", verts=v, faces=at.reshape(F, 3).astype(np.int32), first_idx=np.array([0]),
+                      num_faces=np.array([F]), verts_first_idx=np.array([0]), num_verts=np.array([V]),
+                      image_size=(H, W), faces_per_pixel=K, blur_radius=float(np.float32(1e-4)), bin_size=8,
+                      max_faces_per_bin=None)
+    o = oracle.rasterize(b.verts, b.faces, b.first_idx, b.num_faces, b.image_size, b.blur_radius, K,
+                         nthreads=threads())
+    g = tie_masked_grads(b, o["p2f"], *meshgen.upstream_grads(b, seed=3))
+    ref = oracle.backward(b.verts, b.faces, b.image_size, o["p2f"], *g)
+    got = run_bwd(b, _t(o["p2f"].astype(np.int32)), *g, bs=bs)
+    compare_grad(got.cpu().numpy(), ref, ids)
