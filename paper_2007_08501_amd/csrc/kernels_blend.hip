@@ -197,6 +197,11 @@ __global__ __launch_bounds__(256) void blend_bwd_kernel(const int32_t* __restric
                 float t = 1.0f;
 #pragma unroll
                 for (int i = 0; i < kBlendQ; ++i) {
+                    om[i] = 1.0f;
+                    pr[i] = 0.0f;
+                    // (uniform; without it 3,000,000 pixels of one slot took
+                    // 23 us, 16 with a branch on every slot as with this)
+                    if (L == 1 && i >= K) continue;
                     sigmoid_pair(sl[u].x[i], om[i], pr[i]);
                     if (!sl[u].on[i]) om[i] = 1.0f;
                     t *= om[i];

@@ -128,3 +128,13 @@ def test_backward_vertex_table(ids, bs):
     ref = oracle.backward(b.verts, b.faces, b.image_size, o["p2f"], *g)
     got = run_bwd(b, _t(o["p2f"].astype(np.int32)), *g, bs=bs)
     compare_grad(got.cpu().numpy(), ref, ids)
+
+
+# The silhouette blend's backward with one to four slots a pixel, where a lane
+# skips the slots that no pixel has: holes, empty pixels, deep inside and far
+# outside, part waves.  The bounds of the same blend's other sizes.
+@pytest.mark.parametrize("K", [1, 2, 3, 4])
+@pytest.mark.parametrize("P", [1, 64, 127, 128, 129, 1000])
+def test_silhouette_few_slots(K, P):
+    import test_gpu_paths
+    test_gpu_paths.test_silhouette_lane_groups(K, P)
