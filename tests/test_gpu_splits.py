@@ -138,3 +138,10 @@ def test_backward_vertex_table(ids, bs):
 def test_silhouette_few_slots(K, P):
     import test_gpu_paths
     test_gpu_paths.test_silhouette_lane_groups(K, P)
+
+
+# The softmax blend's instance of two channels, with the bounds of the others.
+@pytest.mark.parametrize("K,P", [(1, 1), (1, 67), (2, 64), (3, 65), (4, 130), (9, 17), (17, 9), (64, 5)])
+def test_softmax_two_channels(K, P):
+    import test_gpu_paths
+    test_gpu_paths.test_softmax_lane_groups(K, P, 2)
