@@ -393,12 +393,12 @@ __global__ __launch_bounds__(kScanThreads) void pt_scan_order_kernel(PtArgs a) {
 // in FP64 over each candidate's pixel range (the squared distance in the
 // same operations and order as a plain evaluation, so the decision is
 // reproducible bit for bit), the hits are listed per pixel, and each lane's
-// list goes through its register top-K eight keys at a time.
+// list goes through its register top-K eight or sixteen keys at a time.
 // ---------------------------------------------------------------------------
 constexpr int kPtLoads = 4;  // candidate chunks loaded at once
 
-// Candidates per batch: larger batches waste less of the last eight-key push
-// of each batch, and the 64-key queue's kernel is held to two waves per SIMD
+// Candidates per batch: larger batches waste less of the last push of each
+// batch, and the 64-key queue's kernel is held to two waves per SIMD
 // by its registers anyway; the smaller queues keep a smaller batch, whose
 // LDS lets more waves share a compute unit.
 template <int KB>
@@ -431,9 +431,8 @@ __device__ __forceinline__ double pt_d2(double x, double y, double px, double py
 
 // Pushes a lane's listed hits into its queue, NB at a time, merging within
 // the first S slots (S = KB: the whole queue).
-template <int S, int KB, class BL>
+template <int S, int NB, int KB, class BL>
 __device__ __forceinline__ void pt_push_hits(TopK<KB>& top, const BL& L, const unsigned char* my, int nl, int nmax) {
-    constexpr int NB = queue_batch(KB);
     for (int i0 = 0; i0 < nmax; i0 += NB) {
         uint64_t b[NB];
 #pragma unroll
@@ -474,18 +473,25 @@ __device__ __forceinline__ void pt_batch(const PtArgs& a, BL& L, TopK<KB>& top, 
     const int nl = L.cnt[lane];
     const unsigned char* my = L.lst + lane;
     const int nmax = wave_max(nl);
-    if constexpr (KB >= 16 && is_pow2(KB)) {
+    constexpr int NB = queue_batch(KB);
+    if constexpr (KB >= 16) {
         // every push of this batch fits the smallest prefix that holds the
-        // wave's largest queue after it (the choice is uniform over the wave)
+        // wave's largest queue after it (the choice is uniform over the wave).
+        // Eight slots take eight keys at once: 39 compare-exchanges where
+        // sixteen keys into sixteen slots take 108 (8 x 512 x 512 pixels, two
+        // hits each, K = 64: 644 -> 638 us; at K = 16 a batch of eight into
+        // sixteen slots is 59, and the further case cost as much as it gave).
         const int need = wave_max(held + nl);
-        if (need <= 16)
-            pt_push_hits<16, KB>(top, L, my, nl, nmax);
+        if (KB >= 32 && need <= 8)
+            pt_push_hits<8, 8>(top, L, my, nl, nmax);
+        else if (need <= 16)
+            pt_push_hits<16, NB>(top, L, my, nl, nmax);
         else if (need <= 32 && KB > 32)
-            pt_push_hits<(KB > 32 ? 32 : KB), KB>(top, L, my, nl, nmax);
+            pt_push_hits<(KB > 32 ? 32 : KB), NB>(top, L, my, nl, nmax);
         else
-            pt_push_hits<KB, KB>(top, L, my, nl, nmax);
+            pt_push_hits<KB, NB>(top, L, my, nl, nmax);
     } else {
-        pt_push_hits<KB, KB>(top, L, my, nl, nmax);
+        pt_push_hits<KB, NB>(top, L, my, nl, nmax);
     }
     held = min(held + nl, KB);
     L.cnt[lane] = 0;

@@ -145,3 +145,19 @@ def test_silhouette_few_slots(K, P):
 def test_softmax_two_channels(K, P):
     import test_gpu_paths
     test_gpu_paths.test_softmax_lane_groups(K, P, 2)
+
+
+# The point pass's prefixes of a long queue: every pixel holds exactly `hits`
+# points, over several batches of candidates in arbitrary order, around eight,
+# sixteen and thirty-two keys in queues of 16, 32 and 64.  Fragments are exact.
+@pytest.mark.parametrize("K", [16, 17, 32, 33, 64])
+@pytest.mark.parametrize("hits", [1, 7, 8, 9, 15, 17, 32, 33, 70])
+def test_point_queue_prefixes(hits, K):
+    from test_gpu_points import check_case
+    rng = np.random.default_rng(100 * hits + K)
+    H, W = 16, 24
+    c, r = (x.ravel() for x in np.meshgrid(np.arange(W), np.arange(H)))
+    at = np.c_[1 - (2 * c + 1) / W, 1 - (2 * r + 1) / H]
+    pts = np.repeat(at, hits, 0) + rng.uniform(-0.01, 0.01, (hits * H * W, 2))
+    pts = np.c_[pts, rng.uniform(0.5, 3, len(pts))][rng.permutation(len(pts))].astype(np.float32)
+    check_case(pts, np.array([0]), np.array([len(pts)]), H, W, 0.03, K, f"{hits} hits")
