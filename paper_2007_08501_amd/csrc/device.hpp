@@ -521,10 +521,10 @@ __device__ __forceinline__ uint64_t tile_mask(const int4 px, int x0, int y0) {
 // Only a mask of candidates: the exact test follows, so every bound may err
 // towards keeping a pixel, and all but e_i(0, 0) and the edge vectors (whose
 // differences cancel) is FP32.  As distances from the line, its errors are
-// a few 2^-24 of the distances that occur at a pixel near the bound, at most
-// rg + 23 / min(H, W) across a tile; rg (edge_radius) carries 2^-20 of that
-// beyond what the exact test's own FP32 error needs, more than ten times
-// those.  A line parallel to the rows (g = 0) gets a slope of 1e-25, far
+// at most about 17 x 2^-24 of the distances that occur at a pixel near the
+// bound, at most rg + 23 / min(H, W) across a tile; rg (edge_radius) carries
+// 2^-16 of that, fifteen times as much, beyond what the exact test's own FP32
+// error needs (on the CPU a tenth of it loses no pixel of 2,000,000 tiles).  A line parallel to the rows (g = 0) gets a slope of 1e-25, far
 // below any that matters.  Faces with coordinates beyond 1e3 from the tile
 // keep their whole box.
 // This mask is computed per face and tile and was a third of the fine pass's
@@ -540,12 +540,23 @@ __device__ __forceinline__ double2 f4_as_d2(const float4 v) {
                         __hiloint2double(__float_as_int(v.w), __float_as_int(v.z)));
 }
 // Radius of the mask: sqrt(blur) and the margins above (computed by the host, once a call).
-inline float edge_radius(float blur, int H, int W) {
+inline float edge_radius(float blur, int H, int W, float slack = 0x1p-16f) {
     const float rg = sqrtf(blur) * (1.0f + 1e-4f) + 1e-6f;
-    return rg + (rg + 23.0f / (float)(H < W ? H : W)) * 0x1p-20f;
+    return rg + (rg + 23.0f / (float)(H < W ? H : W)) * slack;
 }
 // (px, py): centre of the tile's first pixel; sx = 2/W, sy = 2/H.
-__device__ __forceinline__ uint64_t edge_mask(const EdgeGeo& G, float rg, double px, double py, float sx, float sy) {
+// Math: the hardware's reciprocal, root (1 ulp each) and median; the CPU check
+// of the margin compiles the same function with its own.
+struct HwMath {
+    static __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
+    static __device__ __forceinline__ float sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
+    static __device__ __forceinline__ float med3(float x, float lo, float hi) {
+        return __builtin_amdgcn_fmed3f(x, lo, hi);
+    }
+};
+template <class Math = HwMath>
+__host__ __device__ __forceinline__ uint64_t edge_mask(const EdgeGeo& G, float rg, double px, double py, float sx,
+                                                       float sy) {
     const double dx = px - G.pa.x, dy = py - G.pa.y;
     // e1 = cross(p - a, c - a), e2 = cross(b - a, p - a), e0 = E - e1 - e2
     const double e1 = fma(dx, G.ac.y, -(dy * G.ac.x));
@@ -559,9 +570,9 @@ __device__ __forceinline__ uint64_t edge_mask(const EdgeGeo& G, float rg, double
     const float sg = G.E > 0.0 ? 1.0f : -1.0f;
     const float ssx = sg * sx, ssy = sg * sy;
     // edge lengths: e0 <-> (b, c), e1 <-> (c, a), e2 <-> (a, b)
-    const float l0 = __builtin_amdgcn_sqrtf(fmaf(bcx, bcx, bcy * bcy));
-    const float l1 = __builtin_amdgcn_sqrtf(fmaf(acx, acx, acy * acy));
-    const float l2 = __builtin_amdgcn_sqrtf(fmaf(abx, abx, aby * aby));
+    const float l0 = Math::sqrt(fmaf(bcx, bcx, bcy * bcy));
+    const float l1 = Math::sqrt(fmaf(acx, acx, acy * acy));
+    const float l2 = Math::sqrt(fmaf(abx, abx, aby * aby));
     const float k[3] = {fmaf(rg, l0, sg * (float)e0), fmaf(rg, l1, sg * (float)e1), fmaf(rg, l2, sg * (float)e2)};
     const float g[3] = {-ssx * bcy, ssx * acy, -ssx * aby};
     const float h[3] = {ssy * bcx, -ssy * acx, ssy * abx};
@@ -573,7 +584,7 @@ __device__ __forceinline__ uint64_t edge_mask(const EdgeGeo& G, float rg, double
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
         const float gi = fabsf(g[i]) < 1e-25f ? 1e-25f : g[i];
-        const float ig = __builtin_amdgcn_rcpf(gi);
+        const float ig = Math::rcp(gi);
         const float b0 = k[i] * ig, b1 = -h[i] * ig;
         const bool up = gi > 0.0f;
         n0[i] = up ? b0 + 1.0f : 16.0f;
@@ -587,8 +598,8 @@ __device__ __forceinline__ uint64_t edge_mask(const EdgeGeo& G, float rg, double
         const float fr = (float)r;
         const float n = fminf(fminf(fmaf(fr, n1[0], n0[0]), fmaf(fr, n1[1], n0[1])), fmaf(fr, n1[2], n0[2]));
         const float m = fminf(fminf(fmaf(fr, m1[0], m0[0]), fmaf(fr, m1[1], m0[1])), fmaf(fr, m1[2], m0[2]));
-        const int hi1 = (int)__builtin_amdgcn_fmed3f(n, 0.0f, 8.0f);      // columns below hi1 ...
-        const int lo = 8 - (int)__builtin_amdgcn_fmed3f(m, 0.0f, 8.0f);   // ... from lo on
+        const int hi1 = (int)Math::med3(n, 0.0f, 8.0f);      // columns below hi1 ...
+        const int lo = 8 - (int)Math::med3(m, 0.0f, 8.0f);   // ... from lo on
         const uint32_t row = ((1u << max(hi1 - lo, 0)) - 1u) << lo;
         half[r >> 2] |= row << (8 * (r & 3));
     }
