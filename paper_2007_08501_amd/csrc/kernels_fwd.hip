@@ -497,8 +497,8 @@ __device__ __forceinline__ void write_fragments(const FineArgs& a, TileLds& L, c
         float* const st = L.stage;
         // ids, then depths
         {
-            constexpr int G = KB < kStageG1 ? KB : kStageG1;
-            constexpr int S = G + 1;  // odd stride: lane-major writes hit distinct banks
+            constexpr int G = tile_layout::stage_slots(KB, kStageG1);
+            constexpr int S = tile_layout::stage_stride(1, G);
             static_assert(64 * S * 4 <= (int)sizeof(TileLds), "id/depth staging exceeds the tile LDS");
 #pragma unroll
             for (int g0 = 0; g0 < KB; g0 += G) {
@@ -517,8 +517,8 @@ __device__ __forceinline__ void write_fragments(const FineArgs& a, TileLds& L, c
         }
         // barycentrics and signed distances
         {
-            constexpr int G = KB < kStageG2 ? KB : kStageG2;
-            constexpr int SB = 3 * G + 1, SD = G + 1;
+            constexpr int G = tile_layout::stage_slots(KB, kStageG2);
+            constexpr int SB = tile_layout::stage_stride(3, G), SD = tile_layout::stage_stride(1, G);
             static_assert(64 * SB * 4 <= (int)sizeof(TileLds), "bary staging exceeds the tile LDS");
 #pragma unroll
             for (int g0 = 0; g0 < KB; g0 += G) {

@@ -1,5 +1,6 @@
 """The kernels' own index and mask arithmetic on the CPU (tests/cpu_models)."""
 import os
+import shutil
 import subprocess
 
 import pytest
@@ -47,3 +48,25 @@ def test_edge_masks_are_tight(edge_mask):
     n, out = edge_mask(200000, 1.0)
     m, _ = edge_mask(200000, 0.0)
     assert n["lost"] == 0 and n["kept"] <= 1.1 * m["kept"], out
+
+
+def test_tile_block_model(tmp_path):
+    """The fine pass's LDS block: every offset inside it, every face tested
+    once, every fragment written once; a block a few bytes smaller fails."""
+    if shutil.which("g++") is None:
+        pytest.skip("g++ not installed")
+    exe = str(tmp_path / "tile_block_model")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined",
+                           "-fno-sanitize-recover=undefined",
+                           os.path.join(ROOT, "tests", "cpu_models", "tile_block_model.cpp"), "-o", exe])
+
+    def run(*args):
+        return subprocess.run([exe, *args], capture_output=True, text=True, timeout=300,
+                              env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0"))
+
+    ok = run()
+    assert ok.returncode == 0 and "ok: block of 6400 bytes" in ok.stdout, ok.stdout + ok.stderr
+    short = run("6392")
+    assert short.returncode == 1 and "FAILED: staged word" in short.stdout, short.stdout + short.stderr
+    few = run(str(63 * 96))
+    assert few.returncode == 1 and "FAILED: record place" in few.stdout, few.stdout + few.stderr
