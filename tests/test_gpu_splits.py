@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import oracle
+from test_point_forms import BOX, POINTS
 
 pytestmark = pytest.mark.gpu
 
@@ -161,3 +162,13 @@ def test_point_queue_prefixes(hits, K):
     pts = np.repeat(at, hits, 0) + rng.uniform(-0.01, 0.01, (hits * H * W, 2))
     pts = np.c_[pts, rng.uniform(0.5, 3, len(pts))][rng.permutation(len(pts))].astype(np.float32)
     check_case(pts, np.array([0]), np.array([len(pts)]), H, W, 0.03, K, f"{hits} hits")
+
+
+# The point backward's forms for large discs, each reached by the rule
+# (test_point_forms.py evaluates it for these sizes), one gradient or both.
+@pytest.mark.parametrize("H,W,K,sizes,radius,gz,gd", BOX + POINTS)
+def test_point_backward_large_discs(H, W, K, sizes, radius, gz, gd):
+    rng = np.random.default_rng(H + W + K)
+    n = sum(sizes)
+    pts = np.c_[rng.uniform(-0.95, 0.95, (n, 2)), rng.uniform(0.5, 3, n)].astype(np.float32)
+    _point_backward(pts, sizes, H, W, float(np.float32(radius)), K, gz, gd)

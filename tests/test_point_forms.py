@@ -7,6 +7,16 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
+# (H, W, K, points of each cloud, radius, gradients of zbuf and dists): calls that
+# take the box-staged and the one-thread-per-point form, on the GPU in
+# test_gpu_splits.py
+BOX = [(64, 64, 4, [300], 0.36, True, True), (64, 64, 8, [250, 0, 90], 0.36, False, True),
+       (64, 64, 7, [300], 0.37, True, False), (43, 70, 3, [40, 200], 0.5, True, True),
+       (40, 96, 1, [200], 0.4, True, True)]
+POINTS = [(64, 64, 8, [300], 0.36, True, True), (64, 64, 32, [400], 0.36, True, True),
+          (43, 70, 6, [100, 0, 120], 0.6, True, True), (40, 96, 64, [150], 0.5, False, True),
+          (33, 40, 16, [200], 1.1, True, False)]
+
 MAIN = r"""
 #include <cstdio>
 #include <cstdlib>
@@ -61,3 +71,9 @@ def test_sizes_of_the_gpu_tests(rule):
         assert rule(1, 64, 64, 40, P, 2.0 / 64)[:2] == ("slots", 512)
     assert rule(4, 104, 104, 2, 180000, 13.0 / 104)[:2] == ("slots", 256)
     assert rule(4, 104, 104, 1, 180000, 19.0 / 104)[:2] == ("slots", 128)
+
+
+@pytest.mark.parametrize("form,cases", [("box", BOX), ("points", POINTS)])
+def test_forms_of_large_discs(rule, form, cases):
+    for H, W, K, sizes, r, gz, gd in cases:
+        assert rule(len(sizes), H, W, K, sum(sizes), r, gz, gd)[0] == form, (H, W, K, r)
