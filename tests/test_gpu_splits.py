@@ -172,3 +172,20 @@ def test_point_backward_large_discs(H, W, K, sizes, radius, gz, gd):
     n = sum(sizes)
     pts = np.c_[rng.uniform(-0.95, 0.95, (n, 2)), rng.uniform(0.5, 3, n)].astype(np.float32)
     _point_backward(pts, sizes, H, W, float(np.float32(radius)), K, gz, gd)
+
+
+# Scan and tile order of the points in one workgroup up to 15,360 tiles in all,
+# else in six launches; counts in LDS up to 16,384 tiles, else by one global
+# atomic a point.  At each limit and past it, with one cloud and with several,
+# an empty one among them.  Fragments are exact.
+@pytest.mark.parametrize("H,W,sizes", [(960, 1024, [150]), (640, 768, [100, 80]), (568, 568, [70, 0, 90]),
+                                       (576, 576, [90, 0, 60]), (512, 512, [60, 0, 80, 30]), (1024, 1024, [150]),
+                                       (1024, 1032, [120]), (960, 1024, [150, 0, 90])])
+def test_point_sort_limits(H, W, sizes):
+    from test_gpu_points import check_case
+    rng = np.random.default_rng(H + len(sizes))
+    n = sum(sizes)
+    pts = np.c_[rng.uniform(-0.95, 0.95, (n, 2)), rng.uniform(0.5, 3, n)].astype(np.float32)
+    first = np.concatenate([[0], np.cumsum(sizes)[:-1]]).astype(np.int64)
+    o = check_case(pts, first, np.array(sizes, dtype=np.int64), H, W, 0.02, 2, f"{H}x{W}")
+    assert (o["idx"] >= 0).any()
