@@ -189,3 +189,23 @@ def test_point_sort_limits(H, W, sizes):
     first = np.concatenate([[0], np.cumsum(sizes)[:-1]]).astype(np.int64)
     o = check_case(pts, first, np.array(sizes, dtype=np.int64), H, W, 0.02, 2, f"{H}x{W}")
     assert (o["idx"] >= 0).any()
+
+
+# Crowded cells with K above 16, whose slots do not fit a workgroup's registers:
+# a cell that names more than 160 faces (a chunk), or more than its table
+# holds, is read again through its bin's list, also where the bin is larger
+# than the cell.  The suite's gradient bound.
+@pytest.mark.parametrize("F,K,bs", [(1500, 24, 8), (4000, 24, 16), (4000, 64, 8), (1500, 64, 16), (6000, 64, 24)])
+def test_crowded_cells_of_long_queues(F, K, bs):
+    from test_gpu_parity import crowded_batch
+    from _util import compare_grad, run_bwd, threads, tie_masked_grads
+    from paper_2007_08501_amd import meshgen
+    b = crowded_batch(F, seed=F + K, size=24, K=K)
+    p2f = oracle.rasterize(b.verts, b.faces, b.first_idx, b.num_faces, b.image_size, b.blur_radius, K,
+                           nthreads=threads())["p2f"]
+    cells = p2f.reshape(3, 8, 3, 8, K).transpose(0, 2, 1, 3, 4).reshape(9, -1)
+    assert max(len(np.unique(c[c >= 0])) for c in cells) > 160
+    g = tie_masked_grads(b, p2f, *meshgen.upstream_grads(b))
+    ref = oracle.backward(b.verts, b.faces, b.image_size, p2f, *g, nthreads=threads())
+    got = run_bwd(b, _t(p2f.astype(np.int32)), *g, bs=bs)
+    compare_grad(got.cpu().numpy(), ref, f"F {F} K {K} bins {bs}")
