@@ -56,20 +56,12 @@ struct BinSig {
     int w[kSigWords];
 };
 
-// Pixel centre in NDC: x = 1 - (2c+1)/W, y = 1 - (2r+1)/H.  The FP32 value
-// (exact for power-of-two sizes) is used for box tests and tile extents, the
-// FP64 value for edge functions.
-__device__ __forceinline__ float pix_x(int c, int W) { return 1.0f - (float)(2 * c + 1) / (float)W; }
-__device__ __forceinline__ float pix_y(int r, int H) { return 1.0f - (float)(2 * r + 1) / (float)H; }
-
+// Pixel centre in NDC: x = 1 - (2c+1)/W, y = 1 - (2r+1)/H.
 struct Pix {
-    float xf, yf;  // FP32 centre
-    double x, y;   // FP64 centre
+    double x, y;
 };
 __device__ __forceinline__ Pix make_pix(int r, int c, int H, int W) {
     Pix p;
-    p.xf = pix_x(c, W);
-    p.yf = pix_y(r, H);
     p.x = 1.0 - (double)(2 * c + 1) / (double)W;
     p.y = 1.0 - (double)(2 * r + 1) / (double)H;
     return p;
@@ -317,8 +309,7 @@ __device__ __forceinline__ void pix_range(float vmin, float vmax, int size, int&
 
 // Bins [bx0, bx1] x [by0, by1] (bin_size bs) whose pixels may count a face
 // with pixel ranges px; false when it counts nowhere on the image (a face
-// that never counts has empty ranges).  The binning pass and the backward use
-// this same function, so they agree on every face's bins.
+// that never counts has empty ranges).
 __device__ __forceinline__ bool face_bins_of_px(const int4 px, int bs, int& bx0, int& bx1, int& by0, int& by1) {
     if (px.y < px.x || px.w < px.z) return false;
     bx0 = px.x / bs;
@@ -326,10 +317,6 @@ __device__ __forceinline__ bool face_bins_of_px(const int4 px, int bs, int& bx0,
     by0 = px.z / bs;
     by1 = px.w / bs;
     return true;
-}
-__device__ __forceinline__ bool face_bins(const FaceRec& R, int bs, int& bx0, int& bx1, int& by0, int& by1) {
-    if (!R.ok()) return false;
-    return face_bins_of_px(R.px, bs, bx0, bx1, by0, by1);
 }
 
 // Sort key: ascending z, then ascending face id, as one unsigned 64-bit
@@ -408,6 +395,7 @@ constexpr int queue_batch(int kb) { return kb >= 32 ? 16 : 8; }
 // with compile-time constants.
 template <int KB>
 struct TopK {
+    static_assert(is_pow2(KB), "the merge's stages halve the queue");
     uint64_t q[KB];
     __device__ __forceinline__ void init() {
 #pragma unroll
@@ -439,23 +427,10 @@ struct TopK {
                 if (!(i & d)) cex(q[i], q[i + d]);
         }
     }
-    // Adds NB keys: batched merge for power-of-two queues, else one at a time.
+    // Adds NB keys.
     template <int NB>
     __device__ __forceinline__ void push(uint64_t (&b)[NB]) {
-        if constexpr (is_pow2(KB)) {
-            merge<KB>(b);
-        } else {
-#pragma unroll
-            for (int u = 0; u < NB; ++u) insert(b[u]);
-        }
-    }
-    // Branch-free insertion: every slot is a compare-exchange with the
-    // travelling key, so the array is only indexed with compile-time
-    // constants; `want` masks lanes with nothing to insert.
-    __device__ __forceinline__ void insert(uint64_t key, bool want = true) {
-        if (!want) key = kEmptyKey;
-#pragma unroll
-        for (int i = 0; i < KB; ++i) cex(q[i], key);
+        merge<KB>(b);
     }
 };
 

@@ -530,7 +530,6 @@ __device__ __forceinline__ void add_slot(const BwdArgs& a, const SlotRec& R, int
 #pragma unroll
     for (int jj = 0; jj < 3; ++jj) g.gx[jj] = g.gy[jj] = g.gzv[jj] = 0.0f;
     Pix p;
-    p.xf = p.yf = 0.0f;  // (the recomputation reads only the FP64 centre)
     p.x = pix_coord_rcp(col, dW, rW);
     p.y = pix_coord_rcp(row, dH, rH);
     slot_grad_up<SlotRec, kOpts>(a, R, vz, p, up, g);
