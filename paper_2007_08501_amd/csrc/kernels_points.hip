@@ -287,12 +287,12 @@ __device__ __forceinline__ int pt_tile_bucket(const PtArgs& a, const int* start,
     const int n = t / per_img;
     const int tt = t - n * per_img;
     const int ty = tt / a.tiles_x, tx = tt - ty * a.tiles_x;
-    if (start[t + 1] - start[t] > a.chunk) return 0;
     int w = 0;
     for (int yy = max(ty - a.ry, 0); yy <= ty; ++yy) {
         const int64_t row = ((int64_t)n * a.tiles_y + yy) * a.tiles_x;
         w += start[row + tx + 1] - start[row + max(tx - a.rx, 0)];
     }
+    if (w > a.chunk && start[t + 1] - start[t] > a.chunk) return 0;
     const unsigned v = (unsigned)w + 1u;
     const int lg = 31 - __clz(v);
     const int level = min(2 * lg + (lg > 0 ? (int)((v >> (lg - 1)) & 1u) : 0), kPtOrderBuckets - 1);
@@ -955,9 +955,8 @@ __global__ __launch_bounds__(kBwdTileThreads) void pt_bwd_tile_kernel(PtBwdArgs 
 // as the point-major form does.  Points beyond the chunk's capacity (128 to
 // 1,024 points, pt_slots) are further chunks, each reading the box again.
 // Bound by the latency of the id rows and the hash probes, so by the workgroups
-// that a compute unit holds: six by the registers.
+// that a compute unit holds: seven by the registers (72).
 constexpr int kSlotLoads = 16;  // slots loaded per thread before any is used
-constexpr int kCellLoads = 6;   // cells whose gradients are requested together
 constexpr uint8_t kNoSlot = 0xff;
 static_assert(RAST_KMAX < kNoSlot, "a cell holds a slot number or kNoSlot");
 static_assert(kPtTile == kTile, "the rule's tiles are the kernels'");
@@ -966,7 +965,9 @@ __device__ __forceinline__ int slot_hash(int id, int lg_hash) {
     return (int)(((uint32_t)id * 2654435761u) >> (32 - lg_hash));
 }
 
-// One chunk: the points [c_lo, hi) of tile t, at most 1 << b.lg_cap of them taken.
+// One chunk: the points [c_lo, hi) of tile t, at most 1 << b.lg_cap of them
+// taken; kLoads cells of a point have their gradients requested together.
+template <int kLoads>
 __device__ __forceinline__ void pt_bwd_slots_chunk(const PtBwdArgs& b, int t, int c_lo, int hi, int2* htab, int* prc,
                                                    uint8_t* cell) {
     const int per_img = b.tiles_x * b.tiles_y;
@@ -1053,11 +1054,11 @@ __device__ __forceinline__ void pt_bwd_slots_chunk(const PtBwdArgs& b, int t, in
         // the cells in row-major order, eight at a time, their gradients
         // all requested before the first is used
         int dr = 0, dc = 0;
-        for (int c0 = 0; c0 < ncell; c0 += kCellLoads) {
-            float vz[kCellLoads], vd[kCellLoads];
-            int at[kCellLoads];  // row << 16 | column within the range, or -1
+        for (int c0 = 0; c0 < ncell; c0 += kLoads) {
+            float vz[kLoads], vd[kLoads];
+            int at[kLoads];  // row << 16 | column within the range, or -1
 #pragma unroll
-            for (int j = 0; j < kCellLoads; ++j) {
+            for (int j = 0; j < kLoads; ++j) {
                 const int k = c0 + j < ncell ? (int)mine[c0 + j] : (int)kNoSlot;
                 at[j] = k == kNoSlot ? -1 : (dr << 16) | dc;
                 vz[j] = vd[j] = 0.0f;
@@ -1072,7 +1073,7 @@ __device__ __forceinline__ void pt_bwd_slots_chunk(const PtBwdArgs& b, int t, in
                 }
             }
 #pragma unroll
-            for (int j = 0; j < kCellLoads; ++j) {
+            for (int j = 0; j < kLoads; ++j) {
                 if (at[j] < 0) continue;
                 const double px = pix_coord_rcp(pc0 + (at[j] & 0xffff), dW, rW);
                 const double py = pix_coord_rcp(pr0 + (at[j] >> 16), dH, rH);
@@ -1092,8 +1093,10 @@ __device__ __forceinline__ void pt_bwd_slots_chunk(const PtBwdArgs& b, int t, in
 // over 256 of these tiles at a time, then the other tiles, a chunk each.
 // A tile's chunks one after the other in one workgroup left a cloud on
 // 16 x 16 pixels to a few compute units (4 clouds of 20,000 points there,
-// 9 cells: 366 us at K = 8 and 1,300 at K = 50, now 17 and 30).
-__global__ __launch_bounds__(kBwdTileThreads) void pt_bwd_slots_kernel(PtBwdArgs b) {
+// 9 cells: 366 us at K = 8 and 1,320 at K = 50, now 17 and 31).
+template <int kLoads>
+__global__ __launch_bounds__(kBwdTileThreads) __attribute__((amdgpu_waves_per_eu(kSlotGroups)))
+void pt_bwd_slots_kernel(PtBwdArgs b) {
     if (!pt_bwd_usable(b)) return;
     int2* htab = reinterpret_cast<int2*>(bwd_lds);
     int* prc = reinterpret_cast<int*>(htab + (1 << b.lg_table));
@@ -1146,7 +1149,7 @@ __global__ __launch_bounds__(kBwdTileThreads) void pt_bwd_slots_kernel(PtBwdArgs
         }
         next += gridDim.x;
         const int hi = b.start[t + 1];
-        if (c_lo < hi) pt_bwd_slots_chunk(b, t, c_lo, hi, htab, prc, cell);
+        if (c_lo < hi) pt_bwd_slots_chunk<kLoads>(b, t, c_lo, hi, htab, prc, cell);
     }
 }
 
@@ -1199,7 +1202,12 @@ hipError_t launch_points_bwd(const float* pts, int64_t P, const int64_t* first, 
     if (slds > 0) {
         const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(kSlotGroups, kLdsPerCu / (int64_t)slds));
         const int64_t grid = std::min<int64_t>(a.T, (int64_t)std::max(n_cus, 1) * per_cu);
-        hipLaunchKernelGGL(pt_bwd_slots_kernel, dim3((unsigned)grid), dim3(kBwdTileThreads), slds, s, b);
+        // cells requested together: three leave nothing idle with 1 to 9 cells,
+        // eight are fewer round trips with more.  Three / eight: 8 clouds of 7,532
+        // points, 499 x 469 pixels, 1 cell, K = 8 30 / 33 us; 4 of 20,000, 256 x
+        // 256, 9 cells 26 / 28, 36 cells 47 / 47, 400 cells 566 / 512.
+        auto slots = (a.span_x + 1) * (a.span_y + 1) <= 12 ? pt_bwd_slots_kernel<3> : pt_bwd_slots_kernel<8>;
+        hipLaunchKernelGGL(slots, dim3((unsigned)grid), dim3(kBwdTileThreads), slds, s, b);
     } else if (lds > 0) {
         // as many workgroups as the compute units hold at once (LDS-bound)
         const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(8, kLdsPerCu / (int64_t)lds));

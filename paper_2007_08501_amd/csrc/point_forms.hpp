@@ -14,8 +14,8 @@ namespace rast {
 constexpr int kPtTile = 8;                        // pixels a side of a tile
 constexpr int kSlotCapMin = 7, kSlotCapMax = 10;  // log2 of the points per chunk
 constexpr size_t kSlotLdsMax = 64 * 1024;
-constexpr int kSlotGroups = 6;                    // workgroups of a compute unit, by the kernel's registers
-constexpr size_t kSlotLdsShare = 26 * 1024;       // LDS of each of them
+constexpr int kSlotGroups = 7;                    // workgroups of a compute unit, by the kernel's registers
+constexpr size_t kSlotLdsShare = 23040;           // LDS of each of them
 constexpr int64_t kBoxLdsMax = 64 * 1024;
 
 // Pixel columns (or rows) a disc reaches past its first: at most
@@ -34,7 +34,8 @@ inline int pt_span(float radius, int size) {
 // points, so that the room costs nothing, and a cloud that covers a part of the
 // image has tiles far above the mean.  The table is at most half full, a
 // quarter where there is room for that too (4 clouds of 20,000 points on 77 x
-// 77 pixels, 36 cells, K = 8: 31 us half full, 24 a quarter).
+// 77 pixels, 36 cells, K = 8: 31 us half full, 24 a quarter; on 16 x 16 pixels,
+// 9 cells, K = 50: 58 and 31).
 struct PtSlots {
     int lg_cap, lg_table;
     size_t bytes;
