@@ -476,20 +476,26 @@ __device__ __forceinline__ void pt_batch(const PtArgs& a, BL& L, TopK<KB>& top, 
     constexpr int NB = queue_batch(KB);
     if constexpr (KB >= 16) {
         // every push of this batch fits the smallest prefix that holds the
-        // wave's largest queue after it (the choice is uniform over the wave).
-        // Eight slots take eight keys at once: 39 compare-exchanges where
-        // sixteen keys into sixteen slots take 108 (8 x 512 x 512 pixels, two
-        // hits each, K = 64: 644 -> 638 us; at K = 16 a batch of eight into
-        // sixteen slots is 59, and the further case cost as much as it gave).
+        // wave's largest queue after it (the choice is uniform over the wave)
         const int need = wave_max(held + nl);
-        if (KB >= 32 && need <= 8)
-            pt_push_hits<8, 8>(top, L, my, nl, nmax);
-        else if (need <= 16)
+        if constexpr (KB == 16) {
             pt_push_hits<16, NB>(top, L, my, nl, nmax);
-        else if (need <= 32 && KB > 32)
-            pt_push_hits<(KB > 32 ? 32 : KB), NB>(top, L, my, nl, nmax);
-        else
-            pt_push_hits<KB, NB>(top, L, my, nl, nmax);
+        } else {
+            // Eight slots take eight keys at once: 39 compare-exchanges where
+            // sixteen keys into sixteen slots take 108 (8 x 512 x 512 pixels,
+            // two hits each, K = 64: 641 -> 634 us; at K = 16 a batch is eight
+            // keys, 59 into sixteen slots, and the further case cost as much
+            // as it gave).  The full queue is asked for first: the same calls
+            // the other way round cost full tiles a percent.
+            if (need > 32 || (KB == 32 && need > 16))
+                pt_push_hits<KB, NB>(top, L, my, nl, nmax);
+            else if (need > 16)
+                pt_push_hits<(KB > 32 ? 32 : KB), NB>(top, L, my, nl, nmax);
+            else if (need > 8)
+                pt_push_hits<16, NB>(top, L, my, nl, nmax);
+            else
+                pt_push_hits<8, 8>(top, L, my, nl, nmax);
+        }
     } else {
         pt_push_hits<KB, NB>(top, L, my, nl, nmax);
     }
