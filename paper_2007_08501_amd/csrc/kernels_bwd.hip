@@ -325,7 +325,7 @@ __device__ __forceinline__ void flush_table(float* grad, const int* keys, const 
 // per face 2,880 faces were 12 workgroups and each lane walked its 80 or so
 // pixels alone: 330 us, now 26 (three meshes of up to 1,280 faces, 130 x 75
 // pixels, K = 5).
-constexpr int64_t kManyFaces = 65536;
+constexpr int64_t kManyFaces = 16384;
 constexpr int kFaceMax = kBwdBlock;  // faces of a workgroup at most: their 3 x 256 vertices fit the table
 static_assert(3 * kFaceMax <= kHash, "a workgroup's vertices fit its table");
 
@@ -992,9 +992,10 @@ hipError_t launch_backward(const float* verts, int64_t V, const int32_t* faces, 
     if (eb) (void)hipEventRecord(eb, s);
     // Lanes a face: four for many faces with fewer than two pixels each, else
     // sixteen.  One / four / sixteen lanes, backward alone, K = 4: 20,480 faces
-    // on 64 images of 128 x 128 pixels 437 / 139 / 91 us; 40,960 on 8 of 256 x
-    // 256 260 / 88 / 80; 81,920 on 4 of 64 x 64 29 / 27 / 42; 163,840 on 2 of 512 x
-    // 512 321 / 210 / 211; 327,680 on one of 256 x 256 84 / 85 / 143.  And the
+    // on 64 images of 128 x 128 pixels 437 / 139 / 91 us, on 4 of 64 x 64 33 / 21 /
+    // 25; 40,960 on 8 of 256 x 256 260 / 88 / 80, of 96 x 96 43 / 26 / 35; 81,920 on 4
+    // of 64 x 64 29 / 27 / 42; 163,840 on 2 of 512 x 512 321 / 210 / 211; 327,680 on
+    // one of 256 x 256 84 / 85 / 143.  And the
     // faces a group of lanes takes in turn: as many as merge in one table once
     // there are workgroups enough (1,024, four a compute unit).
     const int lanes = F >= kManyFaces && (int64_t)N * H * W < 2 * F ? 4 : 16, groups = kBwdBlock / lanes;

@@ -68,13 +68,13 @@ def test_point_backward_many_tiles_of_several_chunks(rpx, K):
     _point_backward(pts, sizes, H, W, float(np.float32(rpx / W)), K)
 
 
-# The per-face backward takes four lanes a face from 65,536 faces with fewer than
+# The per-face backward takes four lanes a face from 16,384 faces with fewer than
 # two pixels each, with two faces a group of lanes in turn from 131,072, else
 # sixteen: a face fewer, exactly as many, part workgroups, boxes of a few pixels
 # and (the coarse mesh beside the fine one) of more than 256.  The suite's
 # gradient bound.
-@pytest.mark.parametrize("faces,n,image,K", [(65535, 1, 24, 4), (65536, 1, 24, 3), (70001, 1, 40, 5),
-                                             (131072, 2, 20, 2), (150003, 2, 33, 4)])
+@pytest.mark.parametrize("faces,n,image,K", [(16383, 1, 24, 4), (16384, 1, 24, 3), (16384, 1, 160, 3),
+                                             (70001, 1, 40, 5), (131072, 2, 20, 2), (150003, 2, 33, 4)])
 def test_per_face_backward_lanes(faces, n, image, K):
     from _util import compare_grad, run_bwd, threads, tie_masked_grads
     from paper_2007_08501_amd import meshgen
