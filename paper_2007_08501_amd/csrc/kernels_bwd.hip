@@ -62,6 +62,7 @@ struct BwdArgs {
     float inv_k;           // 1 / K
     int lgw, lgh;          // the binned form's cells: log2 of their width and height in pixels
     int ncy, ncx;          // rows and columns of cells per image
+    int cross;             // the bins are not a multiple of the cells: a cell touches up to four
     int reuse;         // records and bins come from the forward: check its signature first
     BinSig sig;        // the signature this call expects
 };
@@ -652,7 +653,10 @@ __device__ __forceinline__ void gather_named(const BwdArgs& a, CellLds& L, int n
 struct CellGeo {
     int n, cx, cy, r0, c0, cols, nslots;
     float inv_cols;
-    int64_t sbase, bin;  // bin: the forward's bin that holds the cell
+    int64_t sbase;
+    int64_t bin;   // the forward's bin of the cell's first pixel
+    int bx, by;    // its column and row
+    int nbx, nby;  // columns and rows of bins that the cell touches
     __device__ __forceinline__ CellGeo(const BwdArgs& a, int64_t cell) {
         const int per_img = a.ncy * a.ncx;
         n = (int)(cell / per_img);
@@ -662,10 +666,25 @@ struct CellGeo {
         r0 = cy << a.lgh;
         c0 = cx << a.lgw;
         cols = min(1 << a.lgw, a.W - c0);
-        nslots = min(1 << a.lgh, a.H - r0) * cols * a.K;
+        const int rows = min(1 << a.lgh, a.H - r0);
+        nslots = rows * cols * a.K;
         inv_cols = 1.0f / (float)cols;
         sbase = (((int64_t)n * a.H + r0) * a.W + c0) * a.K;
-        bin = ((int64_t)n * a.nby + r0 / a.bs) * a.nbx + c0 / a.bs;
+        by = r0 / a.bs;
+        bx = c0 / a.bs;
+        bin = ((int64_t)n * a.nby + by) * a.nbx + bx;
+        nbx = nby = 1;
+        if (a.cross) {  // (uniform)
+            nby += (r0 + rows - 1) / a.bs - by;
+            nbx += (c0 + cols - 1) / a.bs - bx;
+        }
+    }
+    // No face reaches the cell's bins.
+    __device__ __forceinline__ bool empty(const BwdArgs& a) const {
+        int any = a.counts[bin];
+        if (a.cross)
+            for (int i = 1; i < nbx * nby; ++i) any |= a.counts[bin + (int64_t)(i / nbx) * a.nbx + i % nbx];
+        return any == 0;
     }
 };
 
@@ -704,7 +723,7 @@ void bwd_cells_kernel(BwdArgs a) {
     // mostly the same face records)
     const int64_t cell = xcd_item(blockIdx.x, (int64_t)a.N * a.ncy * a.ncx);
     const CellGeo c(a, cell);
-    if (a.counts[c.bin] == 0) return;  // no face reaches the bin: no slot to read
+    if (c.empty(a)) return;  // no slot to read
     const double dW = (double)a.W, dH = (double)a.H, rW = 1.0 / dW, rH = 1.0 / dH;
     const int t = threadIdx.x;
     int fq[kP1Unroll], rq[kP1Unroll], cq[kP1Unroll];
@@ -768,12 +787,10 @@ void bwd_cells_again_kernel(BwdArgs a) {
     const int ncell = kAll ? 1 : a.hdr[kHdrCrowded];
     for (int i = kAll ? 0 : (int)blockIdx.x; i < ncell; i += gridDim.x) {
         const CellGeo c(a, kAll ? xcd_item(blockIdx.x, (int64_t)a.N * a.ncy * a.ncx) : (int64_t)a.crowded[i]);
-        const int* list = a.lists + c.bin * a.M;
-        const int listed = min(a.counts[c.bin], a.M);
-        if (listed == 0) continue;  // no face reaches the bin
+        if (c.empty(a)) continue;
         bool named = false;
         // (a list that fits one chunk and is the cell's own needs no naming)
-        if (kAll && !(listed <= kP1Chunk && a.bs == kTile)) {
+        if (kAll && !(a.bs == kTile && a.counts[c.bin] <= kP1Chunk)) {
             for (int q = t; q < kP1Table; q += kP1Threads) L.key[q] = -1;
             if (t == 0) L.count = L.fail = 0;
             __syncthreads();
@@ -789,55 +806,66 @@ void bwd_cells_again_kernel(BwdArgs a) {
                 gather_named(a, L, c.n, c.cx, c.cy, L.count);
             }
         }
-        const int cnt = named ? L.count : listed;
-        for (int base = 0; base < cnt; base += kP1Chunk) {
-            const int m = min(kP1Chunk, cnt - base), rep = replicas(m);
-            __syncthreads();  // (the last chunk is flushed, count and fail are read)
-            if (!named) {
-                for (int q = t; q < kP1Table; q += kP1Threads) L.key[q] = -1;
-                for (int q = t; q < 9 * (m << rep); q += kP1Threads) L.acc[q] = 0.0;
-                __syncthreads();
-                if (t < m) {
-                    const int f = list[base + t];
-                    const FaceRec& G = a.recs[f];
-                    L.rec.put(t, G, f);
-                    L.dst[t] = partial_row(a, G, f, c.cx, c.cy);
-                    uint32_t h = fhash(f);
-                    for (int probe = 0; probe < kP1Table; ++probe) {
-                        if (atomicCAS(&L.key[h], -1, f) == -1) {
-                            L.val[h] = (unsigned char)t;
-                            break;
+        // (named: the faces are in the table, in one chunk)
+        for (int bi = 0; bi < (named ? 1 : c.nbx * c.nby); ++bi) {
+            const int ox = bi % c.nbx, oy = bi / c.nbx;
+            const int64_t bin = c.bin + (int64_t)oy * a.nbx + ox;
+            const int* list = a.lists + bin * a.M;
+            const int cnt = named ? L.count : min(a.counts[bin], a.M);
+            for (int base = 0; base < cnt; base += kP1Chunk) {
+                const int m = min(kP1Chunk, cnt - base), rep = replicas(m);
+                __syncthreads();  // (the last chunk is flushed, count and fail are read)
+                if (!named) {
+                    for (int q = t; q < kP1Table; q += kP1Threads) L.key[q] = -1;
+                    for (int q = t; q < 9 * (m << rep); q += kP1Threads) L.acc[q] = 0.0;
+                    __syncthreads();
+                    if (t < m) {
+                        const int f = list[base + t];
+                        const FaceRec& G = a.recs[f];
+                        L.rec.put(t, G, f);
+                        // a face listed in several of the cell's bins counts in its first
+                        if (max(G.px.x / a.bs, c.bx) == c.bx + ox && max(G.px.z / a.bs, c.by) == c.by + oy) {
+                            L.dst[t] = partial_row(a, G, f, c.cx, c.cy);
+                            uint32_t h = fhash(f);
+                            for (int probe = 0; probe < kP1Table; ++probe) {
+                                if (atomicCAS(&L.key[h], -1, f) == -1) {
+                                    L.val[h] = (unsigned char)t;
+                                    break;
+                                }
+                                h = (h + 1) & (kP1Table - 1);
+                            }
+                        } else {
+                            L.dst[t] = -2;
                         }
-                        h = (h + 1) & (kP1Table - 1);
+                    }
+                    __syncthreads();
+                }
+                for (int q0 = 0; q0 < c.nslots; q0 += kP1Group) {
+                    int64_t sq[kP1Unroll];
+                    int fq[kP1Unroll], rq[kP1Unroll], cq[kP1Unroll];
+#pragma unroll
+                    for (int u = 0; u < kP1Unroll; ++u) {
+                        const int q = q0 + u * kP1Threads + t;
+                        const SlotPlace w(q, a.K, c.cols, a.inv_k, c.inv_cols);
+                        rq[u] = c.r0 + w.pr;
+                        cq[u] = c.c0 + w.pc;
+                        sq[u] = c.sbase + ((int64_t)(w.pr * a.W + w.pc) * a.K + w.k);
+                        fq[u] = q < c.nslots ? a.p2f[sq[u]] : -1;
+                    }
+#pragma unroll
+                    for (int u = 0; u < kP1Unroll; ++u) {
+                        if (fq[u] < 0) continue;
+                        const int j = find_face(L, fq[u]);
+                        if (j < 0) continue;
+                        const SlotRec R = L.rec.get(j);
+                        if (R.face >= 0)
+                            add_slot<kOpts>(a, R, rq[u], cq[u], dW, rW, dH, rH, load_up(a, sq[u]),
+                                            acc_row(L, j, cq[u], rep));
                     }
                 }
                 __syncthreads();
+                flush_faces(a, L, m);
             }
-            for (int q0 = 0; q0 < c.nslots; q0 += kP1Group) {
-                int64_t sq[kP1Unroll];
-                int fq[kP1Unroll], rq[kP1Unroll], cq[kP1Unroll];
-#pragma unroll
-                for (int u = 0; u < kP1Unroll; ++u) {
-                    const int q = q0 + u * kP1Threads + t;
-                    const SlotPlace w(q, a.K, c.cols, a.inv_k, c.inv_cols);
-                    rq[u] = c.r0 + w.pr;
-                    cq[u] = c.c0 + w.pc;
-                    sq[u] = c.sbase + ((int64_t)(w.pr * a.W + w.pc) * a.K + w.k);
-                    fq[u] = q < c.nslots ? a.p2f[sq[u]] : -1;
-                }
-#pragma unroll
-                for (int u = 0; u < kP1Unroll; ++u) {
-                    if (fq[u] < 0) continue;
-                    const int j = find_face(L, fq[u]);
-                    if (j < 0) continue;
-                    const SlotRec R = L.rec.get(j);
-                    if (R.face >= 0)
-                        add_slot<kOpts>(a, R, rq[u], cq[u], dW, rW, dH, rH, load_up(a, sq[u]),
-                                        acc_row(L, j, cq[u], rep));
-                }
-            }
-            __syncthreads();
-            flush_faces(a, L, m);
         }
         __syncthreads();  // (the next cell clears the tables)
     }
@@ -942,7 +970,7 @@ hipError_t launch_backward(const float* verts, int64_t V, const int32_t* faces, 
     a.M = M;
     a.inv_k = 1.0f / (float)K;
     a.crowded = order;
-    a.lgw = a.lgh = a.ncy = a.ncx = 0;
+    a.lgw = a.lgh = a.ncy = a.ncx = a.cross = 0;
     a.reuse = reuse ? 1 : 0;
     a.sig = sig;
     if (bs > 0) {
@@ -967,9 +995,10 @@ hipError_t launch_backward(const float* verts, int64_t V, const int32_t* faces, 
         a.lgw = a.lgh = 3;
         while ((int64_t)K << (a.lgw + a.lgh + 1) <= kP1Group && a.lgh < 5) {
             int& lg = a.lgw == a.lgh ? a.lgw : a.lgh;
-            if (bs % (2 << lg) != 0) break;
+            if (bs % 16 != 0 ? (2 << lg) > bs : bs % (2 << lg) != 0) break;
             ++lg;
         }
+        a.cross = bs % (1 << a.lgw) != 0 ? 1 : 0;
         a.ncy = (H + (1 << a.lgh) - 1) >> a.lgh;
         a.ncx = (W + (1 << a.lgw) - 1) >> a.lgw;
         if (eb) (void)hipEventRecord(eb, s);

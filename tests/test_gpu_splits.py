@@ -209,3 +209,47 @@ def test_crowded_cells_of_long_queues(F, K, bs):
     ref = oracle.backward(b.verts, b.faces, b.image_size, p2f, *g, nthreads=threads())
     got = run_bwd(b, _t(p2f.astype(np.int32)), *g, bs=bs)
     compare_grad(got.cpu().numpy(), ref, f"F {F} K {K} bins {bs}")
+
+
+# Bins that the backward's cells do not divide (odd multiples of 8: cells of 16
+# or 32 pixels touch up to four bins), on images that cut bins and cells; empty
+# bins beside filled ones.  The suite's gradient bound, and the same gradient
+# as with bins of 8 up to the order of the sums.
+@pytest.mark.parametrize("bs,K,level,image", [(24, 1, 3, (77, 50)), (24, 3, 2, (100, 130)), (24, 8, 3, (61, 90)),
+                                              (24, 16, 3, (45, 61)), (40, 1, 1, (130, 90)), (40, 2, 3, (83, 125)),
+                                              (40, 8, 2, (90, 41)), (56, 1, 3, (120, 70))])
+def test_cells_that_cross_bins(bs, K, level, image):
+    from _util import compare_grad, run_bwd, threads, tie_masked_grads
+    from paper_2007_08501_amd import meshgen
+    b = meshgen.make_config(2, n_override=3, level_override=level)
+    b.verts = b.verts.copy()
+    b.verts[:, :2] *= 0.6  # (leaves the outer bins empty)
+    b.image_size, b.faces_per_pixel = image, K
+    o = oracle.rasterize(b.verts, b.faces, b.first_idx, b.num_faces, b.image_size, b.blur_radius, K,
+                         nthreads=threads())
+    g = tie_masked_grads(b, o["p2f"], *meshgen.upstream_grads(b))
+    ref = oracle.backward(b.verts, b.faces, b.image_size, o["p2f"], *g)
+    p2f = _t(o["p2f"].astype(np.int32))
+    got = run_bwd(b, p2f, *g, bs=bs).cpu().numpy()
+    compare_grad(got, ref, f"bins {bs} K {K}")
+    other = run_bwd(b, p2f, *g, bs=8).cpu().numpy()
+    assert np.abs(got - other).max() <= 1e-5 * np.abs(ref).max()
+
+
+# The same with cells that name more than 160 faces, read again through the
+# lists of all their bins: a face in several of them counts once.
+@pytest.mark.parametrize("F,K,bs", [(2500, 8, 24), (6000, 8, 24), (1200, 2, 40), (9000, 3, 24)])
+def test_crowded_cells_that_cross_bins(F, K, bs):
+    from test_gpu_parity import crowded_batch
+    from _util import compare_grad, run_bwd, threads, tie_masked_grads
+    from paper_2007_08501_amd import meshgen
+    b = crowded_batch(F, seed=F + K, size=48, K=K)
+    p2f = oracle.rasterize(b.verts, b.faces, b.first_idx, b.num_faces, b.image_size, b.blur_radius, K,
+                           nthreads=threads())["p2f"]
+    h, w = {8: (8, 16), 3: (16, 16), 2: (16, 32)}[K]
+    cells = [p2f[0, r:r + h, c:c + w] for r in range(0, 48, h) for c in range(0, 48, w)]
+    assert max(len(np.unique(c[c >= 0])) for c in cells) > 160
+    g = tie_masked_grads(b, p2f, *meshgen.upstream_grads(b))
+    ref = oracle.backward(b.verts, b.faces, b.image_size, p2f, *g, nthreads=threads())
+    got = run_bwd(b, _t(p2f.astype(np.int32)), *g, bs=bs)
+    compare_grad(got.cpu().numpy(), ref, f"F {F} K {K} bins {bs}")
