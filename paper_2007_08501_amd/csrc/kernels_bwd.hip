@@ -62,6 +62,7 @@ struct BwdArgs {
     float inv_k;           // 1 / K
     int lgw, lgh;          // the binned form's cells: log2 of their width and height in pixels
     int ncy, ncx;          // rows and columns of cells per image
+    int max_rep;           // log2 of the rows of sums per face at most (replicas)
     int cross;             // the bins are not a multiple of the cells: a cell touches up to four
     int reuse;         // records and bins come from the forward: check its signature first
     BinSig sig;        // the signature this call expects
@@ -569,8 +570,18 @@ static_assert(sizeof(CellLds) <= 21 * 1280, "six workgroups share a compute unit
 // the same faces, the more so the larger the faces are and the fewer a cell
 // names.  So a chunk of m faces has as many rows per face as there is room for,
 // 1 << replicas(m) of them, and a slot adds to the one of its pixel's column.
-__device__ __forceinline__ int replicas(int m) {
-    return 8 * m <= kP1Rows ? 3 : (4 * m <= kP1Rows ? 2 : (2 * m <= kP1Rows ? 1 : 0));
+// But no more than the pixels that a wave holds need (64 / K of them, of which
+// a face is in part): a row is cleared and summed whether it is used or not.
+// Four meshes of 1,280 faces, 578 x 706 pixels, backward, bins of 16, for eight /
+// four / two / one row at most: K = 1 38 / 39 / 45 / 55 us, K = 4 60 / 58 / 62 / 76, K =
+// 8 113 / 97 / 92 / 97, K = 16 217 / 178 / 164 / 156; 4 of 327,680 at 1024 x 1024, K =
+// 16 650 / 648 / 652 / 604.
+// (kOne: the call has one row per face, known to the compiler)
+template <bool kOne>
+__device__ __forceinline__ int replicas(const BwdArgs& a, int m) {
+    if (kOne) return 0;
+    const int room = 8 * m <= kP1Rows ? 3 : (4 * m <= kP1Rows ? 2 : (2 * m <= kP1Rows ? 1 : 0));
+    return min(room, a.max_rep);
 }
 
 // Coordinate sum x of face j of a chunk (over its rows).
@@ -583,8 +594,9 @@ __device__ __forceinline__ double face_sum(const CellLds& L, int j, int rep, int
 // Writes the sums of the chunk's m faces, lanes running over a face's nine
 // words, to their partial rows, and marks those; the sums of a face without
 // rows go to its vertices, three neighbouring atomics each.
+template <bool kOne>
 __device__ __forceinline__ void flush_faces(const BwdArgs& a, const CellLds& L, int m) {
-    const int rep = replicas(m);
+    const int rep = replicas<kOne>(a, m);
     for (int i = threadIdx.x; i < 9 * m; i += kP1Threads) {
         const int j = stage_pixel(i, 1.0f / 9.0f), x = i - 9 * j;
         const int dst = L.dst[j];
@@ -636,8 +648,9 @@ __device__ __forceinline__ int find_face(const CellLds& L, int f) {
 // Records of the table's faces, one thread per entry, and where their sums
 // go; zeroed sums.  A face of another image or one that never counts is marked
 // by its id.
+template <bool kOne>
 __device__ __forceinline__ void gather_named(const BwdArgs& a, CellLds& L, int n, int cx, int cy, int m) {
-    for (int i = threadIdx.x; i < 9 * (m << replicas(m)); i += kP1Threads) L.acc[i] = 0.0;
+    for (int i = threadIdx.x; i < 9 * (m << replicas<kOne>(a, m)); i += kP1Threads) L.acc[i] = 0.0;
     for (int i = threadIdx.x; i < kP1Table; i += kP1Threads) {
         const int f = L.key[i];
         if (f < 0) continue;
@@ -703,18 +716,19 @@ struct CellGeo {
 // gathered, and leaves the others to bwd_cells_again_kernel, whose code would
 // cost it registers.  kOpts: the call has perspective-correct or clipped
 // barycentrics (an instance of its own, so that their register needs do not
-// lower the occupancy of the plain one).
+// lower the occupancy of the plain one); kOne: one row of sums per face.
 //
 // Bound by latency and vector issue about alike: two dependent round trips
 // per cell (ids, then records; ids, then gradients), overlapped by the six
 // workgroups per compute unit that the LDS block (26.6 KB) allows and that the
-// registers (80) are held to, at the price of a few spilled (2, with options 5);
-// five of each took 711 us instead of 681 (4 x 1024 x 1024 pixels, K = 16) and
-// 448 instead of 419 (32 x 512 x 512, K = 8).  The whole backward, replayed:
-// 895 -> 648 us (K = 16), 428 -> 418 (K = 8, bins of 16 pixels), 53 -> 51 (8 x
-// 256 x 256, K = 8, bins of 16) and 80 -> 41 (K = 4, bins of 32), against bins as
-// cells with fixed-point sums and a second, rescue pass.
-template <bool kOpts>
+// registers (80) are held to, at the price of a few spilled (20 bytes a lane, 24
+// with options, none without options where kOne holds); five of each took 711
+// us instead of 681 (4 x 1024 x 1024 pixels, K = 16) and 448 instead of 419 (32 x
+// 512 x 512, K = 8).  The whole backward, replayed: 895 -> 609 us (K = 16), 430 ->
+// 401 (K = 8, bins of 16 pixels), 53 -> 51 (8 x 256 x 256, K = 8, bins of 16) and 80
+// -> 41 (K = 4, bins of 32), against bins as cells with fixed-point sums and a
+// second, rescue pass.
+template <bool kOpts, bool kOne>
 __global__ __launch_bounds__(kP1Threads) __attribute__((amdgpu_waves_per_eu(6, 8)))
 void bwd_cells_kernel(BwdArgs a) {
     __shared__ CellLds L;
@@ -758,9 +772,9 @@ void bwd_cells_kernel(BwdArgs a) {
         if (t == 0) a.crowded[atomicAdd(&a.hdr[kHdrCrowded], 1)] = (int)cell;
         return;
     }
-    gather_named(a, L, c.n, c.cx, c.cy, U);
+    gather_named<kOne>(a, L, c.n, c.cx, c.cy, U);
     __syncthreads();
-    const int rep = replicas(U);
+    const int rep = replicas<kOne>(a, U);
 #pragma unroll
     for (int u = 0; u < kP1Unroll; ++u) {
         if (fq[u] < 0) continue;
@@ -770,7 +784,7 @@ void bwd_cells_kernel(BwdArgs a) {
             add_slot<kOpts>(a, R, rq[u], cq[u], dW, rW, dH, rH, up[u], acc_row(L, j, cq[u], rep));
     }
     __syncthreads();
-    flush_faces(a, L, U);
+    flush_faces<kOne>(a, L, U);
 }
 
 // Cells that are read again: those the first kernel left (kAll false; a grid
@@ -780,6 +794,7 @@ void bwd_cells_kernel(BwdArgs a) {
 template <bool kOpts, bool kAll>
 __global__ __launch_bounds__(kP1Threads) __attribute__((amdgpu_waves_per_eu(5, 8)))
 void bwd_cells_again_kernel(BwdArgs a) {
+    constexpr bool kOne = kAll;  // (K above 16)
     __shared__ CellLds L;
     if (!bins_usable(a)) return;
     const double dW = (double)a.W, dH = (double)a.H, rW = 1.0 / dW, rH = 1.0 / dH;
@@ -803,7 +818,7 @@ void bwd_cells_again_kernel(BwdArgs a) {
             named = L.count <= kP1Chunk && !L.fail;
             if (named) {
                 if (L.count == 0) return;  // no slot is filled
-                gather_named(a, L, c.n, c.cx, c.cy, L.count);
+                gather_named<kOne>(a, L, c.n, c.cx, c.cy, L.count);
             }
         }
         // (named: the faces are in the table, in one chunk)
@@ -813,7 +828,7 @@ void bwd_cells_again_kernel(BwdArgs a) {
             const int* list = a.lists + bin * a.M;
             const int cnt = named ? L.count : min(a.counts[bin], a.M);
             for (int base = 0; base < cnt; base += kP1Chunk) {
-                const int m = min(kP1Chunk, cnt - base), rep = replicas(m);
+                const int m = min(kP1Chunk, cnt - base), rep = replicas<kOne>(a, m);
                 __syncthreads();  // (the last chunk is flushed, count and fail are read)
                 if (!named) {
                     for (int q = t; q < kP1Table; q += kP1Threads) L.key[q] = -1;
@@ -864,7 +879,7 @@ void bwd_cells_again_kernel(BwdArgs a) {
                     }
                 }
                 __syncthreads();
-                flush_faces(a, L, m);
+                flush_faces<kOne>(a, L, m);
             }
         }
         __syncthreads();  // (the next cell clears the tables)
@@ -970,7 +985,7 @@ hipError_t launch_backward(const float* verts, int64_t V, const int32_t* faces, 
     a.M = M;
     a.inv_k = 1.0f / (float)K;
     a.crowded = order;
-    a.lgw = a.lgh = a.ncy = a.ncx = a.cross = 0;
+    a.lgw = a.lgh = a.ncy = a.ncx = a.cross = a.max_rep = 0;
     a.reuse = reuse ? 1 : 0;
     a.sig = sig;
     if (bs > 0) {
@@ -998,6 +1013,8 @@ hipError_t launch_backward(const float* verts, int64_t V, const int32_t* faces, 
             if (bs % 16 != 0 ? (2 << lg) > bs : bs % (2 << lg) != 0) break;
             ++lg;
         }
+        // rows of sums per face: eight for K = 1 and 2, four to 7, two to 15, then one
+        a.max_rep = K < 4 ? 3 : (K < 8 ? 2 : (K < 16 ? 1 : 0));
         a.cross = bs % (1 << a.lgw) != 0 ? 1 : 0;
         a.ncy = (H + (1 << a.lgh) - 1) >> a.lgh;
         a.ncx = (W + (1 << a.lgw) - 1) >> a.lgw;
@@ -1005,7 +1022,8 @@ hipError_t launch_backward(const float* verts, int64_t V, const int32_t* faces, 
         const bool o = (opts & (kOptPersp | kOptClip)) != 0;
         const int64_t ncells = (int64_t)N * a.ncy * a.ncx;
         if ((int64_t)K << (a.lgw + a.lgh) <= kP1Group) {
-            auto cells = o ? bwd_cells_kernel<true> : bwd_cells_kernel<false>;
+            auto cells = a.max_rep == 0 ? (o ? bwd_cells_kernel<true, true> : bwd_cells_kernel<false, true>)
+                                        : (o ? bwd_cells_kernel<true, false> : bwd_cells_kernel<false, false>);
             auto again = o ? bwd_cells_again_kernel<true, false> : bwd_cells_again_kernel<false, false>;
             hipLaunchKernelGGL(cells, dim3((unsigned)ncells), dim3(kP1Threads), 0, s, a);
             hipLaunchKernelGGL(again, dim3((unsigned)std::min<int64_t>(ncells, kAgainGrid)), dim3(kP1Threads), 0, s, a);

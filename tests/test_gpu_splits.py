@@ -253,3 +253,23 @@ def test_crowded_cells_that_cross_bins(F, K, bs):
     ref = oracle.backward(b.verts, b.faces, b.image_size, p2f, *g, nthreads=threads())
     got = run_bwd(b, _t(p2f.astype(np.int32)), *g, bs=bs)
     compare_grad(got.cpu().numpy(), ref, f"F {F} K {K} bins {bs}")
+
+
+# The backward's rows of sums per face: eight up to K = 3, four to 7, two to 15,
+# then one, and fewer where a cell names many faces.  Few large faces (every
+# lane of a wave names the same) and many small ones; the suite's gradient bound.
+@pytest.mark.parametrize("K", [3, 4, 7, 8, 15, 16, 17])
+@pytest.mark.parametrize("level", [0, 3])
+@pytest.mark.parametrize("options", [0, 0x300])
+def test_rows_of_sums(K, level, options):
+    from _util import compare_grad, run_bwd, run_fwd, to_dev
+    from paper_2007_08501_amd import meshgen
+    b = meshgen.make_config(2, n_override=2, level_override=level)
+    b.image_size, b.faces_per_pixel = (50, 70), K
+    d = to_dev(b)
+    out, _ = run_fwd(b, 16, dev_inputs=d, options=options)
+    g = [_t(x) for x in meshgen.upstream_grads(b)]
+    per_face = run_bwd(b, out.pix_to_face, *g, dev_inputs=d, bs=0, flags=options)
+    for bs in (8, 16, 32):
+        got = run_bwd(b, out.pix_to_face, *g, dev_inputs=d, bs=bs, flags=options)
+        compare_grad(got.cpu().numpy(), per_face.cpu().numpy(), f"bins {bs}")
