@@ -1386,6 +1386,27 @@ __global__ __launch_bounds__(256) void composite_fwd_kernel(CompArgs a, float* _
     }
 }
 
+// Whether any lane of the wave holds a slot that takes part.
+__device__ __forceinline__ bool comp_any(const int (&id)[kCompQ]) {
+    bool any = false;
+#pragma unroll
+    for (int i = 0; i < kCompQ; ++i) any = any || id[i] >= 0;
+    return __any(any) != 0;
+}
+
+// Stores a value for each of the lane's slots of pixel p.
+__device__ __forceinline__ void comp_store(const CompArgs& a, int64_t p, int sub, const float (&v)[kCompQ],
+                                           float* __restrict__ out) {
+    const int64_t o = p * a.K + kCompQ * sub;
+    if (p < a.npix && kCompQ * (sub + 1) <= a.K) {
+        *reinterpret_cast<f32x4_a4*>(out + o) = f32x4_a4{v[0], v[1], v[2], v[3]};  // one 16-byte store
+    } else {
+#pragma unroll
+        for (int i = 0; i < kCompQ; ++i)
+            if (p < a.npix && kCompQ * sub + i < a.K) out[o + i] = v[i];
+    }
+}
+
 // Opacity gradients of the lane's slots of pixel p (stored), and what the
 // feature gradients are made of: the slots' ids, their weights wf and the
 // pixel's upstream gradient g (dL/df of slot i's point collects wf[i] g).
@@ -1395,9 +1416,15 @@ __device__ __forceinline__ void composite_bwd_pixel(const CompArgs& a, const flo
                                                     float (&wf)[kCompQ], float (&g)[CB]) {
     const float chain = a.from_d ? -a.inv_r2 : 1.0f;
     float al[kCompQ];
-    comp_slots(a, p, sub, id, al);
 #pragma unroll
     for (int c = 0; c < CB; ++c) g[c] = (p < a.npix && c < a.D) ? gimg[p * a.D + c] : 0.0f;
+    comp_slots(a, p, sub, id, al);
+    if (!comp_any(id)) {  // (uniform) nothing but empty slots
+#pragma unroll
+        for (int i = 0; i < kCompQ; ++i) wf[i] = 0.0f;
+        comp_store(a, p, sub, wf, gw);
+        return;
+    }
     float gk[kCompQ], fr[kCompQ][CB];
     if constexpr (FEAT) comp_rows(a, id, fr);
 #pragma unroll
@@ -1466,17 +1493,9 @@ __device__ __forceinline__ void composite_bwd_pixel(const CompArgs& a, const flo
             wf[i] = al[i] * invS;
         }
     }
-    const int64_t o = p * a.K + kCompQ * sub;
-    if (p < a.npix && kCompQ * (sub + 1) <= a.K) {
-        f32x4_a4 v;
 #pragma unroll
-        for (int i = 0; i < kCompQ; ++i) v[i] = id[i] >= 0 ? dal[i] * chain : 0.0f;
-        *reinterpret_cast<f32x4_a4*>(gw + o) = v;  // one 16-byte store
-    } else {
-#pragma unroll
-        for (int i = 0; i < kCompQ; ++i)
-            if (p < a.npix && kCompQ * sub + i < a.K) gw[o + i] = id[i] >= 0 ? dal[i] * chain : 0.0f;
-    }
+    for (int i = 0; i < kCompQ; ++i) dal[i] = id[i] >= 0 ? dal[i] * chain : 0.0f;
+    comp_store(a, p, sub, dal, gw);
 }
 
 template <int L, int CB, bool FEAT>
@@ -1497,8 +1516,8 @@ __global__ __launch_bounds__(256) void composite_bwd_kernel(CompArgs a, const fl
 // pixels, so a workgroup takes a span of consecutive pixels (about 2,048
 // slots), adds the span's terms per point in an LDS hash table, in FP64 (LDS
 // adds FP64 in hardware, FP32 in a compare-and-swap loop), and sends each
-// point's row out once, lanes running over the words of the rows.  A point
-// that finds no place within kFeatProbe entries adds to its row directly.
+// point's row out once, lanes running over the words of the rows it holds.  A
+// point that finds no place within kFeatProbe entries adds to its row directly.
 // Bound by the rate of global float atomics before (one per slot and channel,
 // each on a line of its own: 465 us at 4 x 270 x 401 pixels, K = 16, 3
 // channels); now 60 us there, by the tables' LDS atomics.
@@ -1515,11 +1534,15 @@ __global__ __launch_bounds__(256) void composite_bwd_feat_kernel(CompArgs a, con
     const int table = 1 << lg_table;
     double* vals = feat_lds;                              // table rows of D
     int* keys = reinterpret_cast<int*>(vals + table * a.D);  // point ids (-1: free)
+    uint16_t* used = reinterpret_cast<uint16_t*>(keys + table);  // the rows that hold a point
+    __shared__ int nused;
     const float inv_d = 1.0f / (float)a.D;
+    // the table is cleared once, then each span's rows as they go out
+    for (int i = threadIdx.x; i < table; i += 256) keys[i] = -1;
+    for (int i = threadIdx.x; i < table * a.D; i += 256) vals[i] = 0.0;
+    if (threadIdx.x == 0) nused = 0;
+    __syncthreads();
     for (int64_t s0 = (int64_t)blockIdx.x * span; s0 < a.npix; s0 += (int64_t)gridDim.x * span) {
-        for (int i = threadIdx.x; i < table; i += 256) keys[i] = -1;
-        for (int i = threadIdx.x; i < table * a.D; i += 256) vals[i] = 0.0;
-        __syncthreads();
         for (int q = wave * PPW; q < span; q += 4 * PPW) {
             int id[kCompQ];
             float wf[kCompQ], g[CB];
@@ -1532,6 +1555,7 @@ __global__ __launch_bounds__(256) void composite_bwd_feat_kernel(CompArgs a, con
                 bool placed = false;
                 for (int probe = 0; probe < kFeatProbe && !placed; ++probe) {
                     const int prev = atomicCAS(&keys[h], -1, id[i]);
+                    if (prev == -1) used[atomicAdd(&nused, 1)] = (uint16_t)h;
                     placed = prev == -1 || prev == id[i];
                     if (!placed) h = (h + 1) & (uint32_t)(table - 1);
                 }
@@ -1547,12 +1571,19 @@ __global__ __launch_bounds__(256) void composite_bwd_feat_kernel(CompArgs a, con
             }
         }
         __syncthreads();
-        for (int i = threadIdx.x; i < table * a.D; i += 256) {
-            const int h = (int)(((float)i + 0.5f) * inv_d);  // i / D (i < 2^13: exact)
-            const int point = keys[h];
-            if (point >= 0) atomicAdd(gf + (int64_t)point * a.D + (i - h * a.D), (float)vals[i]);
+        const int rows = nused;
+        if (rows > 0) {  // (uniform)
+            for (int i = threadIdx.x; i < rows * a.D; i += 256) {
+                const int r = (int)(((float)i + 0.5f) * inv_d), c = i - r * a.D;  // i / D (i < 2^13: exact)
+                const int at = used[r] * a.D + c;
+                atomicAdd(gf + (int64_t)keys[used[r]] * a.D + c, (float)vals[at]);
+                vals[at] = 0.0;
+            }
+            __syncthreads();
+            for (int r = threadIdx.x; r < rows; r += 256) keys[used[r]] = -1;
+            if (threadIdx.x == 0) nused = 0;
         }
-        __syncthreads();  // (the next span clears the table)
+        __syncthreads();  // (the next span finds the table clear)
     }
 }
 
@@ -1587,12 +1618,12 @@ static hipError_t comp_launch(const CompArgs& a, bool bwd, const float* gimg, fl
     if (a.K <= kCompQ * L) {                                                                           \
         const dim3 grid(comp_blocks(a.npix, L));                                                       \
         if (bwd && gf) {                                                                               \
-            /* a span of whole rounds of the workgroup; 34 to 36 KB of table */                        \
+            /* a span of whole rounds of the workgroup; at most 38 KB of table */                      \
             constexpr int round = 4 * (64 / L);                                                        \
             const int64_t most = std::max<int64_t>(1, a.npix / (512 * round)); /* spans for the chip */ \
             const int span = (int)std::min<int64_t>(most, std::max(1, kFeatSlots / (a.K * round))) * round; \
             const int lg = CB <= 4 ? 10 : 9;                                                           \
-            const size_t lds = ((size_t)a.D * sizeof(double) + sizeof(int)) << lg;                     \
+            const size_t lds = ((size_t)a.D * sizeof(double) + sizeof(int) + sizeof(uint16_t)) << lg;  \
             const int64_t spans = (a.npix + span - 1) / span;                                          \
             hipLaunchKernelGGL((composite_bwd_feat_kernel<L, CB>),                                     \
                                dim3((unsigned)std::min<int64_t>(spans, 16384)), dim3(256), lds, s, a, gimg, gw, gf, \

@@ -273,3 +273,41 @@ def test_rows_of_sums(K, level, options):
     for bs in (8, 16, 32):
         got = run_bwd(b, out.pix_to_face, *g, dev_inputs=d, bs=bs, flags=options)
         compare_grad(got.cpu().numpy(), per_face.cpu().numpy(), f"bins {bs}")
+
+
+# Compositing where nearly all slots are empty: waves and spans of pixels without
+# any, spans with one point, more spans than workgroups (a workgroup's table is
+# clear again for its next one), and a last part span.  The bound of the feature
+# gradients elsewhere; opacity gradients are zero at empty slots.
+@pytest.mark.parametrize("K,D,npix,filled", [(4, 3, 9_000_001, 4000), (16, 2, 300_001, 700), (50, 8, 50_003, 90),
+                                             (64, 1, 4099, 1)])
+@pytest.mark.parametrize("norm", [False, True])
+def test_compositing_of_nearly_empty_slots(K, D, npix, filled, norm):
+    from paper_2007_08501_amd.points import alpha_composite, norm_composite
+    rng = np.random.default_rng(K + D)
+    P = 500
+    rows = np.unique(np.concatenate([rng.integers(0, npix, filled), [0, npix - 1]]))
+    sub = np.full((len(rows), K), -1, np.int32)
+    n = rng.integers(1, min(K, 4) + 1, len(rows))
+    for i, m in enumerate(n):
+        sub[i, :m] = rng.integers(0, P, m)
+    al = rng.uniform(0.1, 0.9, sub.shape).astype(np.float32)
+    f = rng.uniform(-1, 1, (P, D)).astype(np.float32)
+    g = rng.standard_normal((len(rows), D)).astype(np.float32)
+    idx = torch.full((npix, K), -1, dtype=torch.int32, device="cuda")
+    w = torch.zeros((npix, K), device="cuda")
+    up = torch.randn((npix, D), device="cuda")
+    at = _t(rows)
+    idx[at], w[at], up[at] = _t(sub), _t(al), _t(g)
+    ft, wt = _t(f).requires_grad_(True), w.requires_grad_(True)
+    img = (norm_composite if norm else alpha_composite)(idx, wt, ft)
+    gw, gf = torch.autograd.grad(img, (wt, ft), up)
+    args = sub, al.astype(np.float64), f.astype(np.float64)
+    ref = (oracle.norm_composite if norm else oracle.alpha_composite)(*args)
+    back = oracle.norm_composite_backward if norm else oracle.alpha_composite_backward
+    rw, rf = back(*args, g)
+    _, size = back(*args, np.abs(g))
+    assert np.abs(img.detach()[at].cpu().numpy() - ref).max() <= 1e-5
+    assert (np.abs(gf.cpu().numpy() - rf) <= 8e-6 * np.abs(size) + 1e-30).all()
+    assert np.abs(gw[at].cpu().numpy() - rw).max() <= 1e-5 * np.abs(rw).max()
+    assert (gw[idx < 0] == 0).all() and int((img.detach() != 0).any(-1).sum()) <= len(rows)
