@@ -57,8 +57,9 @@ bool make_layout(int N, int H, int W, int64_t F, int bs, int M, Layout* L) {
         L->hist = off;
         off = align_up(off + 64 * 4);
     }
-    // backward only: per-face partial sums, one per bin of the face's range
-    // (F x 4 x 9 floats), and the list of large faces (F ints)
+    // backward only: per-face partial sums, one row per cell of pixels of the
+    // face's range (F x 4 x 9 floats), and the faces' row masks, or the list of
+    // large faces (F ints)
     L->partial = off;
     if ((size_t)F > big / 144) return false;
     off = align_up(off + (size_t)F * 144);

@@ -448,10 +448,12 @@ __global__ __launch_bounds__(kBwdBlock) void bwd_big_faces_kernel(BwdArgs a) {
 // (vertex, coordinate) per workgroup.  Faces spanning more than four cells
 // go to grad_verts directly.
 //
-// Cells are 8, 16 or 32 pixels wide and high, independent of the bins but for
-// dividing them: the largest whose slots the workgroup holds at once (1,024).
-// Larger bins as cells had their slots scanned once per 160 listed faces, on
-// too few workgroups.
+// Cells are 8, 16 or 32 pixels wide and high: the largest whose slots the
+// workgroup holds at once (1,024) and that divides the bins, or, for bins that
+// are an odd multiple of 8, that is no larger than a bin (such a cell reaches
+// into up to four bins).  Larger bins as cells had their slots scanned once per
+// 160 listed faces, on too few workgroups; cells of 8 in bins of 24 were four
+// times the workgroups (4 x 578 x 706 pixels, K = 1, backward: 83 us, now 42).
 // ---------------------------------------------------------------------------
 constexpr int kP1Threads = 256;
 constexpr int kP1Chunk = 160;    // faces staged in LDS per pass over a cell's slots
@@ -707,9 +709,9 @@ struct CellGeo {
 // is recomputed once.  A crowded cell (silhouettes) then costs no more than a
 // quiet one, and no list is read.  Slot ids outside [0, F), of a face that
 // never counts or of another image are ignored.  The listed way (any other
-// cell): the list of the cell's bin is taken in chunks of kP1Chunk faces, each
+// cell): the lists of the cell's bins are taken in chunks of kP1Chunk faces, each
 // chunk's records and hash table built, and every slot of the cell looked up
-// in it.
+// in it; a face listed in several of the bins counts in the first of them.
 //
 // This kernel takes cells of at most kP1Group slots the direct way, ids and
 // gradients in registers, the gradients in flight while the records are
@@ -722,8 +724,9 @@ struct CellGeo {
 // per cell (ids, then records; ids, then gradients), overlapped by the six
 // workgroups per compute unit that the LDS block (26.6 KB) allows and that the
 // registers (80) are held to, at the price of a few spilled (20 bytes a lane, 24
-// with options, none without options where kOne holds); five of each took 711
-// us instead of 681 (4 x 1024 x 1024 pixels, K = 16) and 448 instead of 419 (32 x
+// with options, none without options where kOne holds); with five of each the
+// kernel took 711 us instead of 681 (4 x 1024 x 1024 pixels, K = 16; by one row of
+// sums a face and a cheaper hash step since then 520) and 448 instead of 419 (32 x
 // 512 x 512, K = 8).  The whole backward, replayed: 895 -> 609 us (K = 16), 430 ->
 // 401 (K = 8, bins of 16 pixels), 53 -> 51 (8 x 256 x 256, K = 8, bins of 16) and 80
 // -> 41 (K = 4, bins of 32), against bins as cells with fixed-point sums and a
@@ -1002,8 +1005,8 @@ hipError_t launch_backward(const float* verts, int64_t V, const int32_t* faces, 
         // mask bytes = F words), in one launch
         e = launch_prep(grad, V * 3, big, F, hdr, s);
         if (e != hipSuccess) return e;
-        // the largest cell that divides the bins and whose slots fit a
-        // workgroup's registers, wider before higher (K = 16: 8 x 8, K = 8: 16 x
+        // the largest cell that divides the bins (or, in bins of an odd multiple
+        // of 8, is no larger than one) and whose slots fit a workgroup's registers, wider before higher (K = 16: 8 x 8, K = 8: 16 x
         // 8, K = 1: 32 x 32); 8 x 8 where none does.  Half the size at K = 8
         // took 611 us instead of 448 (32 x 512 x 512 pixels), twice the size on
         // 512 threads 495.

@@ -814,7 +814,7 @@ __global__ __launch_bounds__(64) void raster_persistent_kernel(FineArgs a, const
 // order[]: tiles sorted by the count of their bin, descending, using a
 // counting sort over count buckets (64 buckets of width ceil((M+1)/64)), with
 // one global atomic per distinct bucket of a wave (per-thread atomics on the
-// 64 counters serialised: about 1 ms at config 3).
+// 64 counters serialised: about 1 ms at 32 images of 512 x 512 pixels).
 __device__ __forceinline__ int tile_bucket(const int* __restrict__ counts, int t, int tiles_x, int tiles_y, int bs,
                                            int nby, int nbx, int M) {
     const int per_img = tiles_x * tiles_y;

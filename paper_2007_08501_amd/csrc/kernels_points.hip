@@ -1057,7 +1057,7 @@ __device__ __forceinline__ void pt_bwd_slots_chunk(const PtBwdArgs& b, int t, in
         const double x = rec.x, y = rec.y;
         double gx = 0.0, gy = 0.0, gzs = 0.0;
         const uint8_t* mine = cell + i * ncell;
-        // the cells in row-major order, eight at a time, their gradients
+        // the cells in row-major order, kLoads at a time, their gradients
         // all requested before the first is used
         int dr = 0, dc = 0;
         for (int c0 = 0; c0 < ncell; c0 += kLoads) {
@@ -1243,9 +1243,9 @@ hipError_t launch_points_bwd(const float* pts, int64_t P, const int64_t* first, 
 //           applied to 0 -- a suffix scan with no division by 1 - alpha_k, so
 //           a fully opaque slot is no special case;  dL/df_k = alpha_k T_k g.
 //   Norm:   dL/dalpha_k = (g_k - <g, out>) / S,  dL/df_k = alpha_k g / S.
-// Feature gradients are scattered to the point rows with float atomics.  With
-// no feature table every feature is 1 (silhouette compositing) and nothing is
-// gathered.
+// Feature gradients are added per point in LDS first (composite_bwd_feat_kernel).
+// With no feature table every feature is 1 (silhouette compositing) and nothing
+// is gathered.
 // ---------------------------------------------------------------------------
 constexpr int kCompQ = 4;  // consecutive slots per lane
 // four words at 4-byte alignment (one 16-byte global load)
